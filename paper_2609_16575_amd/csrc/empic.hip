@@ -61,6 +61,7 @@ void grid_info(const empic_grid_desc *d, GridP &g, TileInfo &ti) {
     }
     g.dt = d->dt;
     g.V = (long long)g.ext[0] * g.ext[1] * g.ext[2];
+    for (int a = 0; a < 2; ++a) g.div[a] = make_fastdiv((uint32_t)g.ext[a]);
     ti.ntiles = ti.nt[0] * ti.nt[1] * ti.nt[2];
     ti.NK = (long long)ti.ntiles * TC;
 }
@@ -357,15 +358,17 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
     field_ptrs<T>(s, E, B, J, Bb);
     const bool absorbing = s->g.bc[0] == EMPIC_BC_ABSORBING || s->g.bc[1] == EMPIC_BC_ABSORBING ||
                            s->g.bc[2] == EMPIC_BC_ABSORBING;
-    const bool pec = s->g.bc[0] == EMPIC_BC_PEC || s->g.bc[1] == EMPIC_BC_PEC ||
-                     s->g.bc[2] == EMPIC_BC_PEC;
     TimedEvent t;
     ev_begin(s, t, 1);
     // 1. Faraday + temporal centring of B; J (FP64) or its fixed-point sums
-    // (FP32) zeroed for this step's deposit
+    // (FP32) zeroed for this step's deposit.  Without species nothing reads
+    // the centred B and nothing deposits.
     constexpr bool f32 = sizeof(T) == 4;
-    launch_faraday<T>(s->g, E, B, Bb, f32 ? nullptr : J, f32 ? s->jfix : nullptr, true,
-                      s->stream, f32 ? s->fb_count : nullptr);
+    const bool plasma = s->nsp > 0;
+    T *planes = absorbing ? (T *)s->mur : nullptr;
+    launch_faraday<T>(s->g, E, B, plasma ? Bb : nullptr, plasma && !f32 ? J : nullptr,
+                      plasma && f32 ? s->jfix : nullptr, true, s->stream,
+                      f32 ? s->fb_count : nullptr, planes, s->L.mur_stride);
     ev_end(s, t);
     // 2. gather, Boris, move, ZigZag for every species
     if constexpr (sizeof(T) == 4) {
@@ -403,20 +406,17 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
     ev_begin(s, t, 1);
     const long long *const *jf = f32 ? (const long long *const *)s->jfix : nullptr;
     const double jinv = 1.0 / s->jscale;
-    if (s->filter_passes || s->filter_comp) {
-        if (f32) {
-            launch_j_from_fixed(s->g, (float *const *)J, jf, jinv, s->stream);
-            jf = nullptr;
-        }
+    JMode jmode = !plasma ? J_NONE : (f32 ? J_FIXED : J_READ);
+    if (plasma && (s->filter_passes || s->filter_comp)) {
+        if (f32) launch_j_from_fixed(s->g, (float *const *)J, jf, jinv, s->stream);
+        jmode = J_READ;
         T *tmp[3];
         for (int c = 0; c < 3; ++c) tmp[c] = (T *)s->filt + (size_t)c * s->g.V;
         launch_filter<T>(s->g, J, tmp, s->filter_passes, s->filter_comp, s->stream);
     }
-    if (absorbing) launch_mur_save<T>(s->g, E, (T *)s->mur, s->L.mur_stride, s->stream);
-    launch_ampere<T>(s->g, E, B, J, jf, jinv, s->stream);
+    launch_ampere<T>(s->g, E, B, J, jmode, jf, jinv, s->stream);  // sets the PEC faces too
     if (s->laser.enabled) launch_laser<T>(s->g, E, s->laser, (s->nstep + 0.5) * s->g.dt, s->stream);
-    if (absorbing) launch_mur_apply<T>(s->g, E, (const T *)s->mur, s->L.mur_stride, s->stream);
-    if (pec) launch_pec<T>(s->g, E, s->stream);
+    if (absorbing) launch_mur_apply<T>(s->g, E, planes, s->L.mur_stride, s->stream);
     if (s->port.enabled) launch_port<T>(s->g, E, s->port, (s->nstep + 1) * s->g.dt, s->stream);
     ev_end(s, t);
     s->nstep += 1;

@@ -1,13 +1,21 @@
 // fields.hip -- Yee FDTD kernels for gfx950 (Sec. 2.3 of KEMPIC-3D).
 //
-// One thread per grid point, x fastest across a wavefront so that every
-// component load and store is coalesced; a thread updates all three
-// components at its point.  Periodic neighbours wrap; on a walled (absorbing
-// or PEC) axis the validity rules below keep every neighbour inside the
-// stored array.
+// One thread per grid point on the flat index (x fastest), so that every
+// component load and store of a wave is 256 contiguous bytes whatever the
+// grid's width; a thread updates all three components at its point.
+// Workgroups of one XCD take a contiguous run of the grid, so that the y and
+// z neighbours of a stencil come from that XCD's own L2.  Periodic neighbours
+// wrap; on a walled (absorbing or PEC) axis the validity rules below keep
+// every neighbour inside the stored array.
 //
 // Bytes per cell (FP32): Faraday reads E, B (24) and writes B, Bbar (24) and
-// zeroes J (12); Ampere reads E, B, J (36) and writes E (12).
+// zeroes the int64 sums of J (24); Ampere reads those, E and B (48) and
+// writes E, J (24).  Without particles there is no Bbar and there are no
+// sums: 36 and 48.
+// Bound by HBM.  The vacuum waveguide on 91 x 46 x 3001 nodes: 0.645 ms per
+// step with one 64 x 4 workgroup per patch of rows (the second of two per
+// row 42 % full), the sums zeroed and read, and the Mur and PEC planes in
+// kernels of their own; 0.255 ms now, 4.2 TB/s (a large copy: 4.7).
 #include <cmath>
 #include <utility>
 
@@ -23,15 +31,21 @@ struct Pt {
     long long st[3];  // strides
 };
 
-__device__ inline bool make_point(const GridP &g, Pt &q) {
-    q.idx[0] = blockIdx.x * blockDim.x + threadIdx.x;
-    q.idx[1] = blockIdx.y * blockDim.y + threadIdx.y;
-    q.idx[2] = blockIdx.z;
-    if (q.idx[0] >= g.ext[0] || q.idx[1] >= g.ext[1]) return false;
+constexpr int PT_THREADS = 256;
+
+__device__ __forceinline__ bool make_point(const GridP &g, Pt &q) {
+    const uint32_t nb8 = gridDim.x >> 3;
+    const uint32_t b = (blockIdx.x & 7u) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous
+    const uint32_t p = b * PT_THREADS + threadIdx.x;
+    if (p >= (uint32_t)g.V) return false;
+    const uint32_t r = fastdiv(p, g.div[0]), k = fastdiv(r, g.div[1]);
+    q.idx[0] = (int)(p - r * g.div[0].d);
+    q.idx[1] = (int)(r - k * g.div[1].d);
+    q.idx[2] = (int)k;
     q.st[0] = 1;
     q.st[1] = g.ext[0];
     q.st[2] = (long long)g.ext[0] * g.ext[1];
-    q.p = q.idx[0] + q.st[1] * q.idx[1] + q.st[2] * q.idx[2];
+    q.p = p;
     return true;
 }
 
@@ -62,14 +76,49 @@ __device__ inline bool ampere_E(const GridP &g, const Pt &q, int c) {
     return true;
 }
 
+// on a PEC face with E_c tangential to it: stays zero
+__device__ inline bool pec_zero(const GridP &g, const int idx[3], int c) {
+    bool z = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        z = z || (g.bc[a] == EMPIC_BC_PEC && a != c && (idx[a] == 0 || idx[a] == g.n[a]));
+    return z;
+}
+
+// First-order Mur faces (READING of the boundary module: tangential E on the
+// faces of an absorbing axis) need E^n on the node planes 0, 1, n - 1, n of
+// the axis after Ampere has updated E in place.  Faraday reads E^n everywhere
+// and saves them: planes[a][c'][q][point], q = the plane, point = i_b1 +
+// ext[b1] * i_b2 over the other two axes.
 template <typename T>
-__global__ void k_faraday(GridP g, const T *__restrict__ Ex, const T *__restrict__ Ey,
-                          const T *__restrict__ Ez, T *__restrict__ Bx, T *__restrict__ By,
-                          T *__restrict__ Bz, T *__restrict__ Bbx, T *__restrict__ Bby,
-                          T *__restrict__ Bbz, T *__restrict__ Jx, T *__restrict__ Jy,
-                          T *__restrict__ Jz, unsigned long long *__restrict__ Jfx,
-                          unsigned long long *__restrict__ Jfy, unsigned long long *__restrict__ Jfz,
-                          unsigned *__restrict__ fb_reset, int write_B) {
+__device__ __forceinline__ void mur_save(const GridP &g, const Pt &q, const T *const E[3],
+                                         T *planes, long long pstride) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (g.bc[a] != EMPIC_BC_ABSORBING) continue;
+        const int i = q.idx[a], n = g.n[a];
+        if (i > 1 && i < n - 1) continue;
+        const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
+        const long long t = q.idx[b1] + (long long)g.ext[b1] * q.idx[b2];
+        const int at[4] = {0, 1, n - 1, n};  // with n = 2 plane 1 is saved as both
+#pragma unroll
+        for (int ci = 0; ci < 2; ++ci) {
+            const T v = E[ci == 0 ? b1 : b2][q.p];
+#pragma unroll
+            for (int qq = 0; qq < 4; ++qq)
+                if (i == at[qq]) planes[(((long long)a * 2 + ci) * 4 + qq) * pstride + t] = v;
+        }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(PT_THREADS) void k_faraday(
+    GridP g, const T *__restrict__ Ex, const T *__restrict__ Ey, const T *__restrict__ Ez,
+    T *__restrict__ Bx, T *__restrict__ By, T *__restrict__ Bz, T *__restrict__ Bbx,
+    T *__restrict__ Bby, T *__restrict__ Bbz, T *__restrict__ Jx, T *__restrict__ Jy,
+    T *__restrict__ Jz, unsigned long long *__restrict__ Jfx,
+    unsigned long long *__restrict__ Jfy, unsigned long long *__restrict__ Jfz,
+    unsigned *__restrict__ fb_reset, int write_B, T *__restrict__ planes, long long pstride) {
     Pt q;
     if (!make_point(g, q)) return;
     const long long p = q.p;
@@ -88,6 +137,10 @@ __global__ void k_faraday(GridP g, const T *__restrict__ Ex, const T *__restrict
         Jfy[p] = 0ull;
         Jfz[p] = 0ull;
     }
+    if (planes) {
+        const T *const E[3] = {Ex, Ey, Ez};
+        mur_save(g, q, E, planes, pstride);
+    }
     // evaluated in FP64 and rounded once per stored value (see k_ampere)
     const double dt = g.dt;
     const double ix = g.inv_d[0], iy = g.inv_d[1], iz = g.inv_d[2];
@@ -97,8 +150,8 @@ __global__ void k_faraday(GridP g, const T *__restrict__ Ex, const T *__restrict
                             ((double)Ey[p + up(g, q, 2)] - (double)Ey[p]) * iz;
         const double old = (double)Bx[p], nw = old - dt * curl;
         if (write_B) Bx[p] = (T)nw;
-        Bbx[p] = (T)(0.5 * (old + nw));
-    } else {
+        if (Bbx) Bbx[p] = (T)(0.5 * (old + nw));
+    } else if (Bbx) {
         Bbx[p] = T(0);
     }
     if (valid_B(g, q, 1)) {
@@ -106,8 +159,8 @@ __global__ void k_faraday(GridP g, const T *__restrict__ Ex, const T *__restrict
                             ((double)Ez[p + up(g, q, 0)] - (double)Ez[p]) * ix;
         const double old = (double)By[p], nw = old - dt * curl;
         if (write_B) By[p] = (T)nw;
-        Bby[p] = (T)(0.5 * (old + nw));
-    } else {
+        if (Bbx) Bby[p] = (T)(0.5 * (old + nw));
+    } else if (Bbx) {
         Bby[p] = T(0);
     }
     if (valid_B(g, q, 2)) {
@@ -115,8 +168,8 @@ __global__ void k_faraday(GridP g, const T *__restrict__ Ex, const T *__restrict
                             ((double)Ex[p + up(g, q, 1)] - (double)Ex[p]) * iy;
         const double old = (double)Bz[p], nw = old - dt * curl;
         if (write_B) Bz[p] = (T)nw;
-        Bbz[p] = (T)(0.5 * (old + nw));
-    } else {
+        if (Bbx) Bbz[p] = (T)(0.5 * (old + nw));
+    } else if (Bbx) {
         Bbz[p] = T(0);
     }
 }
@@ -127,15 +180,15 @@ __device__ __forceinline__ T j_from_fixed(long long x, double jinv) {
     return (T)((double)x * jinv);
 }
 
-// With Jf (the FP32 path): J is first formed from the fixed-point sums and
-// written out, at every point, then used.
-template <typename T>
-__global__ void k_ampere(GridP g, T *__restrict__ Ex, T *__restrict__ Ey, T *__restrict__ Ez,
-                         const T *__restrict__ Bx, const T *__restrict__ By,
-                         const T *__restrict__ Bz, T *__restrict__ Jx, T *__restrict__ Jy,
-                         T *__restrict__ Jz, const long long *__restrict__ Jfx,
-                         const long long *__restrict__ Jfy, const long long *__restrict__ Jfz,
-                         double jinv) {
+// MODE J_FIXED (the FP32 path): J is first formed from the fixed-point sums
+// and written out, at every point, then used; J_NONE: J is zero.  Tangential
+// E on PEC faces is set to zero here (launch_mur_apply leaves it so).
+template <typename T, int MODE>
+__global__ __launch_bounds__(PT_THREADS) void k_ampere(
+    GridP g, T *__restrict__ Ex, T *__restrict__ Ey, T *__restrict__ Ez, const T *__restrict__ Bx,
+    const T *__restrict__ By, const T *__restrict__ Bz, T *__restrict__ Jx, T *__restrict__ Jy,
+    T *__restrict__ Jz, const long long *__restrict__ Jfx, const long long *__restrict__ Jfy,
+    const long long *__restrict__ Jfz, double jinv) {
     Pt q;
     if (!make_point(g, q)) return;
     const long long p = q.p;
@@ -143,18 +196,20 @@ __global__ void k_ampere(GridP g, T *__restrict__ Ex, T *__restrict__ Ey, T *__r
     // rounding of J, of curl - J and of the two-part update add up coherently
     // on a quiet plasma (every cell of a wave front rounds alike).  The kernel
     // is bound by memory, and gfx950 issues FP64 at the FP32 (unpacked) rate.
-    double jx, jy, jz;
-    if (Jfx) {
+    double jx = 0.0, jy = 0.0, jz = 0.0;
+    if constexpr (MODE == J_FIXED) {
         jx = (double)Jfx[p] * jinv;
         jy = (double)Jfy[p] * jinv;
         jz = (double)Jfz[p] * jinv;
-        Jx[p] = (T)jx;
-        Jy[p] = (T)jy;
-        Jz[p] = (T)jz;
-    } else {
+    }
+    if constexpr (MODE == J_READ) {
         jx = (double)Jx[p];
         jy = (double)Jy[p];
         jz = (double)Jz[p];
+    } else {
+        Jx[p] = (T)jx;
+        Jy[p] = (T)jy;
+        Jz[p] = (T)jz;
     }
     const double dt = g.dt;
     const double ix = g.inv_d[0], iy = g.inv_d[1], iz = g.inv_d[2];
@@ -163,16 +218,22 @@ __global__ void k_ampere(GridP g, T *__restrict__ Ex, T *__restrict__ Ey, T *__r
         const double curl = ((double)Bz[p] - (double)Bz[p + dn(g, q, 1)]) * iy -
                             ((double)By[p] - (double)By[p + dn(g, q, 2)]) * iz;
         Ex[p] = (T)((double)Ex[p] + dt * (curl - jx));
+    } else if (pec_zero(g, q.idx, 0)) {
+        Ex[p] = T(0);
     }
     if (ampere_E(g, q, 1)) {
         const double curl = ((double)Bx[p] - (double)Bx[p + dn(g, q, 2)]) * iz -
                             ((double)Bz[p] - (double)Bz[p + dn(g, q, 0)]) * ix;
         Ey[p] = (T)((double)Ey[p] + dt * (curl - jy));
+    } else if (pec_zero(g, q.idx, 1)) {
+        Ey[p] = T(0);
     }
     if (ampere_E(g, q, 2)) {
         const double curl = ((double)By[p] - (double)By[p + dn(g, q, 0)]) * ix -
                             ((double)Bx[p] - (double)Bx[p + dn(g, q, 1)]) * iy;
         Ez[p] = (T)((double)Ez[p] + dt * (curl - jz));
+    } else if (pec_zero(g, q.idx, 2)) {
+        Ez[p] = T(0);
     }
 }
 
@@ -203,32 +264,8 @@ __global__ void k_j_from_fixed(GridP g, float *__restrict__ Jx, float *__restric
     Jz[p] = j_from_fixed<float>(Jfz[p], jinv);
 }
 
-// ---------------------------------------------------------------------------
-// First-order Mur faces (READING of the boundary module: tangential E on the
-// faces of an absorbing axis).  planes[a][c'][q][point], q = index 0, 1, n-1,
-// n along a, point = i_b1 + ext[b1] * i_b2 over the other two axes.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void k_mur_save(GridP g, int a, T *Ex, T *Ey, T *Ez, T *planes, long long pstride) {
-    const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
-    const long long npt = (long long)g.ext[b1] * g.ext[b2];
-    const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (t >= npt) return;
-    const int i1 = (int)(t % g.ext[b1]), i2 = (int)(t / g.ext[b1]);
-    T *E[3] = {Ex, Ey, Ez};
-    long long st[3] = {1, g.ext[0], (long long)g.ext[0] * g.ext[1]};
-    const int qidx[4] = {0, 1, g.n[a] - 1, g.n[a]};
-    int ci = 0;
-    for (int c = 0; c < 3; ++c) {
-        if (c == a) continue;
-        for (int qq = 0; qq < 4; ++qq) {
-            const long long p = st[b1] * i1 + st[b2] * i2 + st[a] * qidx[qq];
-            planes[(((long long)a * 2 + ci) * 4 + qq) * pstride + t] = E[c][p];
-        }
-        ++ci;
-    }
-}
-
+// The Mur faces of one axis from the saved planes of E^n (mur_save); points
+// that a PEC face holds at zero stay zero.
 template <typename T>
 __global__ void k_mur_apply(GridP g, int a, T *Ex, T *Ey, T *Ez, const T *planes,
                             long long pstride) {
@@ -240,17 +277,22 @@ __global__ void k_mur_apply(GridP g, int a, T *Ex, T *Ey, T *Ez, const T *planes
     T *E[3] = {Ex, Ey, Ez};
     long long st[3] = {1, g.ext[0], (long long)g.ext[0] * g.ext[1]};
     const T coef = (T)((g.dt - g.d[a]) / (g.dt + g.d[a]));
+    int idx[3];
+    idx[a] = 0;
+    idx[b1] = i1;
+    idx[b2] = i2;
     int ci = 0;
     for (int c = 0; c < 3; ++c) {
         if (c == a) continue;
         const T *pl = planes + ((long long)a * 2 + ci) * 4 * pstride;
+        ++ci;
+        if (pec_zero(g, idx, c)) continue;
         const long long base = st[b1] * i1 + st[b2] * i2;
         // face at index 0: E_0^{n+1} = E_1^n + coef (E_1^{n+1} - E_0^n)
         E[c][base] = pl[1 * pstride + t] + coef * (E[c][base + st[a]] - pl[0 * pstride + t]);
         // face at index n: E_n^{n+1} = E_{n-1}^n + coef (E_{n-1}^{n+1} - E_n^n)
         const long long pn = base + st[a] * g.n[a];
         E[c][pn] = pl[2 * pstride + t] + coef * (E[c][pn - st[a]] - pl[3 * pstride + t]);
-        ++ci;
     }
 }
 
@@ -275,26 +317,6 @@ __global__ void k_laser(GridP g, T *Ey, empic_laser_desc L, double t_half) {
     const double Jy = -2.0 * einc / g.d[0];
     const long long p = L.i_s + (long long)g.ext[0] * (j + (long long)g.ext[1] * k);
     Ey[p] -= (T)(g.dt * Jy);
-}
-
-// Perfectly conducting walls: tangential E on both faces of axis a set to
-// zero (after Ampere, which leaves them alone).  One thread per face point.
-template <typename T>
-__global__ void k_pec(GridP g, int a, T *Ex, T *Ey, T *Ez) {
-    const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
-    const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (t >= (long long)g.ext[b1] * g.ext[b2]) return;
-    int idx[3];
-    idx[b1] = (int)(t % g.ext[b1]);
-    idx[b2] = (int)(t / g.ext[b1]);
-    const long long st[3] = {1, g.ext[0], (long long)g.ext[0] * g.ext[1]};
-    T *E[3] = {Ex, Ey, Ez};
-    for (int side = 0; side < 2; ++side) {
-        idx[a] = side ? g.n[a] : 0;
-        const long long p = idx[0] + st[1] * idx[1] + st[2] * idx[2];
-        E[b1][p] = T(0);
-        E[b2][p] = T(0);
-    }
 }
 
 // Waveguide port (hard source): E_comp = e0 sin(pi s/L) g(t) sin(omega t) on
@@ -426,7 +448,11 @@ __global__ void k_field_energy(GridP g, const T *__restrict__ Ex, const T *__res
     }
 }
 
-dim3 point_grid(const GridP &g) { return dim3((g.ext[0] + 63) / 64, (g.ext[1] + 3) / 4, g.ext[2]); }
+// workgroups of the point kernels: a multiple of 8 for the XCD-contiguous map
+dim3 point_grid(const GridP &g) {
+    const long long nb = (g.V + PT_THREADS - 1) / PT_THREADS;
+    return dim3((unsigned)((nb + 7) / 8 * 8));
+}
 
 }  // namespace
 
@@ -446,18 +472,21 @@ dim3 reduction_grid(const GridP &g) {
 template <typename T>
 void launch_faraday(const GridP &g, T *const E[3], T *const B[3], T *const Bbar[3],
                     T *const J[3], unsigned long long *const Jf[3], bool write_B, hipStream_t s,
-                    unsigned *fb_reset) {
-    hipLaunchKernelGGL(k_faraday<T>, point_grid(g), dim3(64, 4), 0, s, g, E[0], E[1], E[2], B[0],
-                       B[1], B[2], Bbar[0], Bbar[1], Bbar[2], J ? J[0] : nullptr,
-                       J ? J[1] : nullptr, J ? J[2] : nullptr, Jf ? Jf[0] : nullptr,
-                       Jf ? Jf[1] : nullptr, Jf ? Jf[2] : nullptr, fb_reset, write_B ? 1 : 0);
+                    unsigned *fb_reset, T *mur_planes, long long plane_stride) {
+    hipLaunchKernelGGL(k_faraday<T>, point_grid(g), dim3(PT_THREADS), 0, s, g, E[0], E[1], E[2],
+                       B[0], B[1], B[2], Bbar ? Bbar[0] : nullptr, Bbar ? Bbar[1] : nullptr,
+                       Bbar ? Bbar[2] : nullptr, J ? J[0] : nullptr, J ? J[1] : nullptr,
+                       J ? J[2] : nullptr, Jf ? Jf[0] : nullptr, Jf ? Jf[1] : nullptr,
+                       Jf ? Jf[2] : nullptr, fb_reset, write_B ? 1 : 0, mur_planes, plane_stride);
 }
 
 template <typename T>
-void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3],
+void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], JMode mode,
                    const long long *const Jf[3], double jinv, hipStream_t s) {
-    hipLaunchKernelGGL(k_ampere<T>, point_grid(g), dim3(64, 4), 0, s, g, E[0], E[1], E[2], B[0],
-                       B[1], B[2], J[0], J[1], J[2], Jf ? Jf[0] : nullptr, Jf ? Jf[1] : nullptr,
+    const auto k = mode == J_FIXED ? k_ampere<T, J_FIXED>
+                                   : (mode == J_NONE ? k_ampere<T, J_NONE> : k_ampere<T, J_READ>);
+    hipLaunchKernelGGL(k, point_grid(g), dim3(PT_THREADS), 0, s, g, E[0], E[1], E[2], B[0], B[1],
+                       B[2], J[0], J[1], J[2], Jf ? Jf[0] : nullptr, Jf ? Jf[1] : nullptr,
                        Jf ? Jf[2] : nullptr, jinv);
 }
 
@@ -475,19 +504,8 @@ void launch_copy6(const float *const src[6], float *const dst[6], long long n, h
 
 void launch_j_from_fixed(const GridP &g, float *const J[3], const long long *const Jf[3],
                          double jinv, hipStream_t s) {
-    hipLaunchKernelGGL(k_j_from_fixed, point_grid(g), dim3(64, 4), 0, s, g, J[0], J[1], J[2],
+    hipLaunchKernelGGL(k_j_from_fixed, point_grid(g), dim3(PT_THREADS), 0, s, g, J[0], J[1], J[2],
                        Jf[0], Jf[1], Jf[2], jinv);
-}
-
-template <typename T>
-void launch_mur_save(const GridP &g, T *const E[3], T *planes, long long pstride, hipStream_t s) {
-    for (int a = 0; a < 3; ++a) {
-        if (g.bc[a] != EMPIC_BC_ABSORBING) continue;
-        const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
-        const long long npt = (long long)g.ext[b1] * g.ext[b2];
-        hipLaunchKernelGGL(k_mur_save<T>, dim3((unsigned)((npt + 255) / 256)), dim3(256), 0, s, g,
-                           a, E[0], E[1], E[2], planes, pstride);
-    }
 }
 
 template <typename T>
@@ -510,7 +528,7 @@ void launch_filter(const GridP &g, T *const F[3], T *const tmp[3], int passes, i
         for (int k = 0; k < passes + (compensate ? 1 : 0); ++k) {
             const bool comp = k == passes;
             const T a = comp ? T(-0.25) : T(0.25), b = comp ? T(1.5) : T(0.5);
-            hipLaunchKernelGGL(k_filter_pass<T>, point_grid(g), dim3(64, 4), 0, s, g, ax, cur[0],
+            hipLaunchKernelGGL(k_filter_pass<T>, point_grid(g), dim3(PT_THREADS), 0, s, g, ax, cur[0],
                                cur[1], cur[2], oth[0], oth[1], oth[2], a, b);
             for (int c = 0; c < 3; ++c) std::swap(cur[c], oth[c]);
         }
@@ -522,21 +540,10 @@ void launch_filter(const GridP &g, T *const F[3], T *const tmp[3], int passes, i
 template <typename T>
 void launch_window_shift(const GridP &g, T *const F[3], T *const tmp[3], int ax, int cells,
                          bool isB, hipStream_t s) {
-    hipLaunchKernelGGL(k_window_shift<T>, point_grid(g), dim3(64, 4), 0, s, g, ax, cells,
+    hipLaunchKernelGGL(k_window_shift<T>, point_grid(g), dim3(PT_THREADS), 0, s, g, ax, cells,
                        isB ? 1 : 0, F[0], F[1], F[2], tmp[0], tmp[1], tmp[2]);
     for (int c = 0; c < 3; ++c)
         (void)hipMemcpyAsync(F[c], tmp[c], (size_t)g.V * sizeof(T), hipMemcpyDeviceToDevice, s);
-}
-
-template <typename T>
-void launch_pec(const GridP &g, T *const E[3], hipStream_t s) {
-    for (int a = 0; a < 3; ++a) {
-        if (g.bc[a] != EMPIC_BC_PEC) continue;
-        const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
-        const long long npt = (long long)g.ext[b1] * g.ext[b2];
-        hipLaunchKernelGGL(k_pec<T>, dim3((unsigned)((npt + 255) / 256)), dim3(256), 0, s, g, a,
-                           E[0], E[1], E[2]);
-    }
 }
 
 template <typename T>
@@ -568,15 +575,13 @@ void launch_field_energy(const GridP &g, T *const E[3], T *const B[3], double *p
 #define EMPIC_INST(T)                                                                          \
     template void launch_faraday<T>(const GridP &, T *const[3], T *const[3], T *const[3],      \
                                     T *const[3], unsigned long long *const[3], bool,           \
-                                    hipStream_t, unsigned *);                                  \
+                                    hipStream_t, unsigned *, T *, long long);                  \
     template void launch_ampere<T>(const GridP &, T *const[3], T *const[3], T *const[3],       \
-                                   const long long *const[3], double, hipStream_t);            \
-    template void launch_mur_save<T>(const GridP &, T *const[3], T *, long long, hipStream_t); \
+                                   JMode, const long long *const[3], double, hipStream_t);     \
     template void launch_mur_apply<T>(const GridP &, T *const[3], const T *, long long,        \
                                       hipStream_t);                                            \
     template void launch_laser<T>(const GridP &, T *const[3], const empic_laser_desc &, double, \
                                   hipStream_t);                                                \
-    template void launch_pec<T>(const GridP &, T *const[3], hipStream_t);                      \
     template void launch_window_shift<T>(const GridP &, T *const[3], T *const[3], int, int,    \
                                          bool, hipStream_t);                                   \
     template void launch_filter<T>(const GridP &, T *const[3], T *const[3], int, int,          \

@@ -9,6 +9,25 @@
 
 namespace empic {
 
+// Unsigned division by a constant d >= 1 set up on the host:
+// x / d = mulhi(x, mul) >> sh for x < 2^31, with sh = ceil(log2 d) - 1 and
+// mul = ceil(2^(32 + sh) / d) (the error of mul, below d / 2^(32 + sh), stays
+// under 1/d for every x < 2^31); d = 1 is a flag.
+struct FastDiv {
+    uint32_t d = 1, mul = 0, sh = 0;
+};
+__host__ inline FastDiv make_fastdiv(uint32_t d) {
+    FastDiv f;
+    f.d = d;
+    if (d <= 1) return f;
+    while ((1ull << (f.sh + 1)) < d) ++f.sh;
+    f.mul = (uint32_t)(((1ull << (32 + f.sh)) + d - 1) / d);
+    return f;
+}
+__host__ __device__ inline uint32_t fastdiv(uint32_t x, const FastDiv &f) {
+    return f.d == 1 ? x : (uint32_t)(((uint64_t)x * f.mul) >> 32) >> f.sh;
+}
+
 // ---------------------------------------------------------------------------
 // Grid parameters passed by value to every kernel.
 // ---------------------------------------------------------------------------
@@ -20,6 +39,7 @@ struct GridP {
     double inv_d[3];
     double dt;
     long long V;  // ext0 * ext1 * ext2
+    FastDiv div[2];  // by ext0, ext1 (point kernels: flat index -> i, j, k)
     int shape_order = 1;  // 1: CIC weighting (the paper's); 2: b_2 weighting, EZ current
 };
 
@@ -179,31 +199,30 @@ dim3 reduction_grid(const GridP &g);
 // ---------------------------------------------------------------------------
 // Launchers (defined in the kernel translation units).
 // ---------------------------------------------------------------------------
-// Faraday + centring of B; zeroes J (FP64 path) or the fixed-point Jf (FP32
-// path) when given
+// Faraday + centring of B (Bbar null: B alone); zeroes J (FP64 path) or the
+// fixed-point Jf (FP32 path) when given; with mur_planes, saves the E planes
+// that launch_mur_apply needs
 template <typename T>
 void launch_faraday(const GridP &g, T *const E[3], T *const B[3], T *const Bbar[3],
                     T *const J[3], unsigned long long *const Jf[3], bool write_B, hipStream_t s,
-                    unsigned *fb_reset = nullptr);
-// Ampere-Maxwell; with Jf, J is first set to Jf * jinv (FP32 path)
+                    unsigned *fb_reset = nullptr, T *mur_planes = nullptr,
+                    long long plane_stride = 0);
+// Ampere-Maxwell and the PEC faces; J_FIXED: J is first set to Jf * jinv
+// (FP32 path), J_NONE: to zero (no particles), J_READ: taken as it is
+enum JMode { J_READ, J_FIXED, J_NONE };
 template <typename T>
-void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3],
+void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], JMode mode,
                    const long long *const Jf[3], double jinv, hipStream_t s);
 void launch_j_from_fixed(const GridP &g, float *const J[3], const long long *const Jf[3],
                          double jinv, hipStream_t s);
 // dst[a][i] = src[a][i], six arrays of n floats, one launch
 void launch_copy6(const float *const src[6], float *const dst[6], long long n, hipStream_t s);
 template <typename T>
-void launch_mur_save(const GridP &g, T *const E[3], T *planes, long long plane_stride,
-                     hipStream_t s);
-template <typename T>
 void launch_mur_apply(const GridP &g, T *const E[3], const T *planes, long long plane_stride,
                       hipStream_t s);
 template <typename T>
 void launch_laser(const GridP &g, T *const E[3], const empic_laser_desc &L, double t_half,
                   hipStream_t s);
-template <typename T>
-void launch_pec(const GridP &g, T *const E[3], hipStream_t s);
 // moving window: fields `cells` planes back along ax (tmp: three arrays)
 template <typename T>
 void launch_window_shift(const GridP &g, T *const F[3], T *const tmp[3], int ax, int cells,
