@@ -397,7 +397,8 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
         ev_begin(s, t, 0);
         for (int i = 0; i < s->nsp; ++i)
             launch_push_f64(s->g, (double *const *)E, (double *const *)Bb, (double *const *)J,
-                            species_params(s, i, 0), s->sp[i].host_count, s->fault, s->stream);
+                            species_params(s, i, 0), s->sp[i].host_count, s->counts, s->rank, s->fault,
+                            s->stream);
         ev_end(s, t);
     }
     // 3. current filter, Ampere-Maxwell, external source, absorbing faces.
@@ -597,6 +598,7 @@ bool init_handle(empic_sim *s, const empic_grid_desc *g, const Layout &L, int32_
     launch_fill_i32((int32_t *)(s->ws + L.fault), 16, 0, s->stream);
     launch_fill_i32((int32_t *)(s->ws + L.fb_mask),
                     (long long)max_species * ((max_capacity + 31) / 32), 0, s->stream);
+    if (es == 8) launch_fill_i32(s->counts, s->ti.NK + 1, 0, s->stream);  // FP64 binning
     launch_fill_i32((int32_t *)(s->ws + L.Bbar), (long long)(3 * s->g.V * es / 4), 0, s->stream);
     bool ok = true;
     if (g->sort_every < 0 && g->precision == EMPIC_FP32_CELLREL) {

@@ -277,10 +277,12 @@ void launch_sort(const GridP &g, const TileInfo &ti, const SpeciesP &cur, const 
                  int32_t *counts, int32_t *scan_blocks, int32_t *rank, int32_t *tile_off,
                  uint32_t *fault, bool tiles_valid, int32_t *perm, hipStream_t s);
 
-// FP64 plain path
+// FP64 plain path.  counts: at least 3 ntiles + 1 words for 8 x 8 x 4 tiles,
+// zero before the first call (and left so in their first ntiles); slots: one
+// word per particle
 void launch_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
-                     double *const J[3], const SpeciesP &sp, long long count, uint32_t *fault,
-                     hipStream_t s);
+                     double *const J[3], const SpeciesP &sp, long long count, int32_t *counts,
+                     int32_t *slots, uint32_t *fault, hipStream_t s);
 void launch_dry_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
                          const SpeciesP &sp, long long count, double *partial_slot,
                          uint32_t *fault, hipStream_t s);

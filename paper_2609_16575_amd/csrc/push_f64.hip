@@ -1,74 +1,77 @@
 // push_f64.hip -- plain FP64 particle step for gfx950: global FP64 positions,
-// unsorted, one thread per particle, fields gathered straight from global
-// memory and the ZigZag current scattered with global FP64 atomics
-// (hardware global_atomic_add_f64).  Same operations, in the same order, as
-// the paper's cycle (Sec. 2.4-2.5): staggered CIC gather of E^n and of the
-// centred B^n, relativistic Boris push, x += dt u/gamma, ZigZag deposit.
+// kept in the caller's order.  Same operations as the paper's cycle (Sec.
+// 2.4-2.5): staggered CIC gather of E^n and of the centred B^n, relativistic
+// Boris push, x += dt u/gamma, ZigZag deposit.  Periodic grids only
+// (empic_create refuses walls on this path).
 //
 // Bytes per particle: 48 read + 48 written (+ 8 with a per-particle weight).
+//
+// k_push_f64: one thread per particle in storage order, fields gathered
+// straight from global memory, the current scattered with global FP64
+// atomics.
+// k_bin_* and k_push_f64_tiles: the particles' slots are first binned by 8 x 8
+// x 4 tiles of cells into an index list (two passes over the positions; the
+// particles themselves stay where they are), then one workgroup per tile
+// pushes its particles from LDS windows of E, B and J.  Global FP64 atomics
+// are what bounds the direct kernel: 24 G/s on scattered addresses, against
+// 1600-2200 G/s for FP64 atomics in LDS.  64^3 cells, 2 x 2.1 M particles: see
+// F64_TILED_MIN below.
 #include "internal.hpp"
 
 namespace empic {
 
 namespace {
 
-// linear index of (i,j,k); periodic axes wrap, absorbing axes give -1 outside
-__device__ inline long long at64(const GridP &g, long long i, long long j, long long k) {
-    long long p[3] = {i, j, k};
-    for (int a = 0; a < 3; ++a) {
-        if (g.bc[a] == EMPIC_BC_PERIODIC) {
-            const long long n = g.n[a];
-            p[a] = ((p[a] % n) + n) % n;
-        } else if (p[a] < 0 || p[a] >= g.ext[a]) {
-            return -1;
-        }
-    }
-    return p[0] + (long long)g.ext[0] * (p[1] + (long long)g.ext[1] * p[2]);
+// index i of axis a wrapped into the grid
+__device__ __forceinline__ int wrap64(const GridP &g, int a, long long i) {
+    const long long n = g.n[a];
+    if ((unsigned long long)i < (unsigned long long)n) return (int)i;
+    if (i == -1) return (int)n - 1;
+    if (i == n) return 0;
+    const long long m = i % n;
+    return (int)(m < 0 ? m + n : m);
 }
 
-// staggered CIC interpolation of one component (stag[a] = 1: half-cell)
-__device__ inline double gather_one(const GridP &g, const double *__restrict__ F,
-                                    const int sx, const int sy, const int sz, const double xi[3]) {
-    const int st[3] = {sx, sy, sz};
-    long long i0[3];
-    double f[3];
-    for (int a = 0; a < 3; ++a) {
-        const double t = xi[a] - 0.5 * st[a];
-        const double fl = floor(t);
-        i0[a] = (long long)fl;
-        f[a] = t - fl;
-    }
+// Interpolation points of one axis: offsets (index times the axis' stride) of
+// the two node points and of the two half-cell points, and the fractions
+struct Axis64 {
+    int n[2], h[2];
+    double fn, fh;
+};
+
+// staggered CIC interpolation of one component; sx, sy, sz: half-cell
+__device__ __forceinline__ double gather_one(const double *F, bool sx, bool sy, bool sz,
+                                             const Axis64 ax[3]) {
+    const double fx = sx ? ax[0].fh : ax[0].fn, fy = sy ? ax[1].fh : ax[1].fn,
+                 fz = sz ? ax[2].fh : ax[2].fn;
     double s = 0.0;
+#pragma unroll
     for (int oz = 0; oz < 2; ++oz)
+#pragma unroll
         for (int oy = 0; oy < 2; ++oy)
+#pragma unroll
             for (int ox = 0; ox < 2; ++ox) {
-                const long long ip = at64(g, i0[0] + ox, i0[1] + oy, i0[2] + oz);
-                if (ip < 0) continue;
-                const double w = (ox ? f[0] : 1.0 - f[0]) * (oy ? f[1] : 1.0 - f[1]) *
-                                 (oz ? f[2] : 1.0 - f[2]);
-                s += w * F[ip];
+                const int p = (sx ? ax[0].h[ox] : ax[0].n[ox]) + (sy ? ax[1].h[oy] : ax[1].n[oy]) +
+                              (sz ? ax[2].h[oz] : ax[2].n[oz]);
+                const double w = (ox ? fx : 1.0 - fx) * (oy ? fy : 1.0 - fy) * (oz ? fz : 1.0 - fz);
+                s += w * F[p];
             }
     return s;
 }
 
-struct F64Fields {
-    const double *E[3];
-    const double *Bb[3];
-    double *J[3];
-};
-
-__device__ inline void gather_all(const GridP &g, const F64Fields &f, const double xi[3],
-                                  double Ep[3], double Bp[3]) {
-    Ep[0] = gather_one(g, f.E[0], 1, 0, 0, xi);
-    Ep[1] = gather_one(g, f.E[1], 0, 1, 0, xi);
-    Ep[2] = gather_one(g, f.E[2], 0, 0, 1, xi);
-    Bp[0] = gather_one(g, f.Bb[0], 0, 1, 1, xi);
-    Bp[1] = gather_one(g, f.Bb[1], 1, 0, 1, xi);
-    Bp[2] = gather_one(g, f.Bb[2], 1, 1, 0, xi);
+// E and centred B at a particle; F[q]: the six component arrays
+__device__ __forceinline__ void gather_all(const double *const F[6], const Axis64 ax[3],
+                                           double Ep[3], double Bp[3]) {
+    Ep[0] = gather_one(F[0], true, false, false, ax);
+    Ep[1] = gather_one(F[1], false, true, false, ax);
+    Ep[2] = gather_one(F[2], false, false, true, ax);
+    Bp[0] = gather_one(F[3], false, true, true, ax);
+    Bp[1] = gather_one(F[4], true, false, true, ax);
+    Bp[2] = gather_one(F[5], true, true, false, ax);
 }
 
 // relativistic Boris (standard t/s rotation), r = q dt / (2 m)
-__device__ inline void boris(double u[3], const double E[3], const double B[3], double r) {
+__device__ __forceinline__ void boris(double u[3], const double E[3], const double B[3], double r) {
     double um[3], t[3], s[3], up[3], upl[3];
     for (int a = 0; a < 3; ++a) um[a] = u[a] + r * E[a];
     const double gm = sqrt(1.0 + um[0] * um[0] + um[1] * um[1] + um[2] * um[2]);
@@ -84,110 +87,155 @@ __device__ inline void boris(double u[3], const double E[3], const double B[3], 
     for (int a = 0; a < 3; ++a) u[a] = upl[a] + r * E[a];
 }
 
-__device__ inline void add_edge(const GridP &g, double *J, int c, long long i, long long j,
-                                long long k, double v) {
-    const long long ip = at64(g, i, j, k);
-    if (ip < 0) return;
-    const long long p[3] = {i, j, k};
-    if (g.bc[c] != EMPIC_BC_PERIODIC && p[c] >= g.n[c]) return;  // half-cell padding
-    atomicAdd(J + ip, v);
-}
-
-// one straight segment inside one cell: line integral of the bilinear weights
-__device__ inline void deposit_segment(const GridP &g, const F64Fields &f, const long long cell[3],
-                                       const double s[3], const double e[3], double qsp) {
-    const double dV = g.d[0] * g.d[1] * g.d[2];
+// one straight segment inside one cell: line integral of the bilinear weights,
+// v[4 c + o1 + 2 o2] for the edge of component c at (o1, o2) along its two
+// other axes c + 1, c + 2; amp[c] = q w d_c / (dt dV)
+__device__ __forceinline__ void segment64(const double cell[3], const double s[3],
+                                          const double e[3], const double amp[3], double v[12]) {
     double dxi[3], W[3];
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
         dxi[a] = e[a] - s[a];
-        W[a] = 0.5 * (s[a] + e[a]) - (double)cell[a];
+        W[a] = 0.5 * (s[a] + e[a]) - cell[a];
     }
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
         const int b1 = (c + 1) % 3, b2 = (c + 2) % 3;
-        const double amp = qsp * dxi[c] * g.d[c] / (g.dt * dV);
+        const double A = amp[c] * dxi[c];
         const double cross = dxi[b1] * dxi[b2] / 12.0;
-        for (int o2 = 0; o2 < 2; ++o2)
-            for (int o1 = 0; o1 < 2; ++o1) {
-                const double w1 = o1 ? W[b1] : 1.0 - W[b1];
-                const double w2 = o2 ? W[b2] : 1.0 - W[b2];
-                const double sg = (o1 == o2) ? 1.0 : -1.0;
-                long long p[3] = {cell[0], cell[1], cell[2]};
-                p[b1] += o1;
-                p[b2] += o2;
-                add_edge(g, f.J[c], c, p[0], p[1], p[2], amp * (w1 * w2 + sg * cross));
-            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double w1 = (q & 1) ? W[b1] : 1.0 - W[b1];
+            const double w2 = (q >> 1) ? W[b2] : 1.0 - W[b2];
+            const double sg = ((q & 1) == (q >> 1)) ? 1.0 : -1.0;
+            v[4 * c + q] = A * (w1 * w2 + sg * cross);
+        }
     }
 }
 
-// ZigZag: relay point per axis, two segments each inside one cell
-__device__ inline void zigzag(const GridP &g, const F64Fields &f, const double xi1[3],
-                              const double xi2[3], double qsp) {
-    long long c1[3], c2[3];
-    double xr[3];
+struct F64Args {
+    const double *F[6];  // E, centred B
+    double *J[3];
+    double kc[3];        // q d_c / (dt dV) (times the weight per particle)
+    double r;            // q dt / (2 m)
+};
+
+// the 12 edge values of a segment in cell (i, j, k) (any index) to global J
+__device__ __forceinline__ void add_global(const GridP &g, const F64Args &A, const double cell[3],
+                                           const double v[12]) {
+    int o[3][2];
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const long long i1 = (long long)floor(xi1[a]);
-        const long long i2 = (long long)floor(xi2[a]);
-        const double lo = (double)((i1 < i2 ? i1 : i2) + 1);
-        const double hi = (double)(i1 > i2 ? i1 : i2);
+        const long long i = (long long)cell[a];
+        const int st = a == 0 ? 1 : (a == 1 ? g.ext[0] : g.ext[0] * g.ext[1]);
+        o[a][0] = wrap64(g, a, i) * st;
+        o[a][1] = wrap64(g, a, i + 1) * st;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int b1 = (c + 1) % 3, b2 = (c + 2) % 3;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            atomicAdd(A.J[c] + o[c][0] + o[b1][q & 1] + o[b2][q >> 1], v[4 * c + q]);
+    }
+}
+
+// ZigZag: relay point per axis, two segments each inside one cell.  add(cell,
+// v) takes the 12 values of a cell; both segments of a move inside one cell
+// are added at once.
+template <class Add>
+__device__ __forceinline__ void zigzag(const double xi1[3], const double xi2[3],
+                                       const double f1[3], const double f2[3],
+                                       const double amp[3], Add add) {
+    double xr[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double lo = fmin(f1[a], f2[a]) + 1.0, hi = fmax(f1[a], f2[a]);
         const double mid = 0.5 * (xi1[a] + xi2[a]);
         xr[a] = fmin(lo, fmax(hi, mid));
-        c1[a] = i1;
-        c2[a] = i2;
     }
-    deposit_segment(g, f, c1, xi1, xr, qsp);
-    deposit_segment(g, f, c2, xr, xi2, qsp);
+    double vA[12], vB[12];
+    segment64(f1, xi1, xr, amp, vA);
+    segment64(f2, xr, xi2, amp, vB);
+    if (f1[0] == f2[0] && f1[1] == f2[1] && f1[2] == f2[2]) {
+#pragma unroll
+        for (int q = 0; q < 12; ++q) vA[q] += vB[q];
+        add(f1, vA);
+    } else {
+        add(f1, vA);
+        add(f2, vB);
+    }
+}
+
+// the move after the Boris push: fault bits, xi2, and x += dt u / gamma
+// (periodic wrap)
+__device__ __forceinline__ void move64(const GridP &g, const double un[3], double gm,
+                                       const double xi1[3], double xi2[3], double pos[3],
+                                       uint32_t &bits) {
+    if (!isfinite(gm)) bits |= EMPIC_FAULT_NONFINITE;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        xi2[a] = xi1[a] + g.dt * un[a] / (gm * g.d[a]);
+        if (fabs(xi2[a] - xi1[a]) >= 1.0) bits |= EMPIC_FAULT_FAST;
+        const double L = g.n[a] * g.d[a];
+        double x = pos[a] + g.dt * un[a] / gm;
+        if (x >= L) x -= L;
+        if (x < 0.0) {
+            x += L;
+            if (x >= L) x = 0.0;
+        }
+        pos[a] = x;
+    }
 }
 
 template <bool DRY>
-__global__ __launch_bounds__(256) void k_push_f64(GridP g, F64Fields f, SpeciesP sp,
+__global__ __launch_bounds__(256) void k_push_f64(GridP g, F64Args A, SpeciesP sp,
                                                   long long count, uint32_t *fault,
                                                   double *partial) {
     __shared__ double sm[16];
-    const double r = sp.q * g.dt / (2.0 * sp.m);
     double *X = (double *)sp.pos[0], *Y = (double *)sp.pos[1], *Z = (double *)sp.pos[2];
     double *UX = (double *)sp.u[0], *UY = (double *)sp.u[1], *UZ = (double *)sp.u[2];
     const double *W = (const double *)sp.w;
-    double L[3];
-    for (int a = 0; a < 3; ++a) L[a] = g.n[a] * g.d[a];
     double ksum = 0.0;
+    uint32_t bits = 0;
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < count; p += stride) {
         double pos[3] = {X[p], Y[p], Z[p]};
-        if (isnan(pos[0])) continue;  // removed by an absorbing face
+        if (isnan(pos[0])) continue;
         const double wp = (sp.per_particle_w && W) ? W[p] : sp.w_species;
-        double xi1[3], Ep[3], Bp[3];
-        for (int a = 0; a < 3; ++a) xi1[a] = pos[a] / g.d[a];
-        gather_all(g, f, xi1, Ep, Bp);
+        double xi1[3], f1[3], Ep[3], Bp[3];
+        Axis64 ax[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int st = a == 0 ? 1 : (a == 1 ? g.ext[0] : g.ext[0] * g.ext[1]);
+            xi1[a] = pos[a] / g.d[a];
+            f1[a] = floor(xi1[a]);
+            const double t = xi1[a] - 0.5, fh = floor(t);
+            const long long in = (long long)f1[a], ih = (long long)fh;
+            ax[a].n[0] = wrap64(g, a, in) * st;
+            ax[a].n[1] = wrap64(g, a, in + 1) * st;
+            ax[a].h[0] = wrap64(g, a, ih) * st;
+            ax[a].h[1] = wrap64(g, a, ih + 1) * st;
+            ax[a].fn = xi1[a] - f1[a];
+            ax[a].fh = t - fh;
+        }
+        gather_all(A.F, ax, Ep, Bp);
         double un[3] = {UX[p], UY[p], UZ[p]};
-        boris(un, Ep, Bp, r);
+        boris(un, Ep, Bp, A.r);
         const double uu = un[0] * un[0] + un[1] * un[1] + un[2] * un[2];
         const double gm = sqrt(1.0 + uu);
         if (DRY) {
             ksum += wp * sp.m * uu / (gm + 1.0);
             continue;
         }
-        if (!isfinite(gm)) atomicOr(fault, (uint32_t)EMPIC_FAULT_NONFINITE);
-        double xi2[3];
-        for (int a = 0; a < 3; ++a) {
-            xi2[a] = xi1[a] + g.dt * un[a] / (gm * g.d[a]);
-            if (fabs(xi2[a] - xi1[a]) >= 1.0) atomicOr(fault, (uint32_t)EMPIC_FAULT_FAST);
-        }
-        zigzag(g, f, xi1, xi2, sp.q * wp);
-        bool dead = false;
-        for (int a = 0; a < 3; ++a) {
-            double x = pos[a] + g.dt * un[a] / gm;
-            if (g.bc[a] == EMPIC_BC_PERIODIC) {
-                if (x >= L[a]) x -= L[a];
-                if (x < 0.0) {
-                    x += L[a];
-                    if (x >= L[a]) x = 0.0;
-                }
-            } else if (x < 0.0 || x >= L[a]) {
-                dead = true;
-            }
-            pos[a] = x;
-        }
-        X[p] = dead ? __builtin_nan("") : pos[0];
+        double xi2[3], f2[3];
+        move64(g, un, gm, xi1, xi2, pos, bits);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) f2[a] = floor(xi2[a]);
+        const double amp[3] = {wp * A.kc[0], wp * A.kc[1], wp * A.kc[2]};
+        zigzag(xi1, xi2, f1, f2, amp,
+               [&](const double cell[3], const double v[12]) { add_global(g, A, cell, v); });
+        X[p] = pos[0];
         Y[p] = pos[1];
         Z[p] = pos[2];
         UX[p] = un[0];
@@ -197,6 +245,212 @@ __global__ __launch_bounds__(256) void k_push_f64(GridP g, F64Fields f, SpeciesP
     if (DRY) {
         const double s = block_reduce<false>(ksum, sm);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    } else if (bits) {
+        atomicOr(fault, bits);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Binned path
+// ---------------------------------------------------------------------------
+// 8 x 8 x 4 tiles; the field window holds cells -1 .. 8 (the half-cell points
+// reach one cell down, the node points one up), the current window -1 .. 9
+// (a move of less than a cell, and the far edges)
+constexpr int T64X = 8, T64Y = 8, T64Z = 4;
+constexpr int F64X = T64X + 2, F64Y = T64Y + 2, F64Z = T64Z + 2, F64V = F64X * F64Y * F64Z;
+constexpr int J64X = T64X + 3, J64Y = T64Y + 3, J64Z = T64Z + 3, J64V = J64X * J64Y * J64Z;
+constexpr int BIN_T = 1024, BIN_PER = 8;      // particles of one workgroup of the binning passes
+constexpr int BIN_LDS = 16384;                // tiles whose counters fit in LDS (64 KB)
+
+struct Tiles64 {
+    int nt[3];
+    int ntiles;
+    int32_t *counts, *offs, *cursor;  // ntiles, ntiles + 1, ntiles
+    int32_t *perm;                    // slots grouped by tile
+};
+
+// tile of slot p, -1: skipped (NaN)
+__device__ __forceinline__ int tile64(const GridP &g, const Tiles64 &t, const SpeciesP &sp,
+                                      long long p) {
+    const double x = ((const double *)sp.pos[0])[p];
+    if (isnan(x)) return -1;
+    const double y = ((const double *)sp.pos[1])[p], z = ((const double *)sp.pos[2])[p];
+    const int i = wrap64(g, 0, (long long)floor(x / g.d[0])),
+              j = wrap64(g, 1, (long long)floor(y / g.d[1])),
+              k = wrap64(g, 2, (long long)floor(z / g.d[2]));
+    return i / T64X + t.nt[0] * (j / T64Y + t.nt[1] * (k / T64Z));
+}
+
+// FILL = false: tile populations into counts.  FILL = true: slots into perm,
+// from the tiles' cursors.  With the counters in LDS (dyn), a workgroup makes
+// one global atomic per tile that it meets.
+template <bool FILL, bool LDS>
+__global__ __launch_bounds__(BIN_T) void k_bin(GridP g, Tiles64 t, SpeciesP sp, long long count) {
+    extern __shared__ int hist[];
+    const long long p0 = blockIdx.x * (long long)(BIN_T * BIN_PER) + threadIdx.x;
+    int tl[BIN_PER], rk[BIN_PER];
+#pragma unroll
+    for (int k = 0; k < BIN_PER; ++k) {
+        const long long p = p0 + (long long)k * BIN_T;
+        tl[k] = p < count ? tile64(g, t, sp, p) : -1;
+    }
+    if constexpr (LDS) {
+        for (int e = threadIdx.x; e < t.ntiles; e += BIN_T) hist[e] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < BIN_PER; ++k)
+            if (tl[k] >= 0) rk[k] = atomicAdd(hist + tl[k], 1);
+        __syncthreads();
+        for (int e = threadIdx.x; e < t.ntiles; e += BIN_T) {
+            const int h = hist[e];
+            if (h) hist[e] = atomicAdd((FILL ? t.cursor : t.counts) + e, h);
+        }
+        if constexpr (FILL) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < BIN_PER; ++k)
+                if (tl[k] >= 0) t.perm[hist[tl[k]] + rk[k]] = (int32_t)(p0 + (long long)k * BIN_T);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < BIN_PER; ++k)
+            if (tl[k] >= 0) {
+                const int d = atomicAdd((FILL ? t.cursor : t.counts) + tl[k], 1);
+                if (FILL) t.perm[d] = (int32_t)(p0 + (long long)k * BIN_T);
+            }
+    }
+}
+
+// exclusive scan of the populations into offs and cursor (one workgroup); the
+// populations are cleared for the next species or step
+__global__ __launch_bounds__(1024) void k_bin_scan(Tiles64 t) {
+    __shared__ int sm[16];
+    int carry = 0;
+    for (int base = 0; base < t.ntiles; base += 1024) {
+        const int e = base + threadIdx.x;
+        const int v = e < t.ntiles ? t.counts[e] : 0;
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        int x = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) sm[wid] = x;
+        __syncthreads();
+        int off = carry, tot = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wid) off += sm[w];
+            tot += sm[w];
+        }
+        __syncthreads();
+        if (e < t.ntiles) {
+            t.offs[e] = t.cursor[e] = off + x - v;
+            t.counts[e] = 0;
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) t.offs[t.ntiles] = carry;
+}
+
+__global__ __launch_bounds__(256, 2) void k_push_f64_tiles(GridP g, F64Args A, Tiles64 t,
+                                                           SpeciesP sp, uint32_t *fault) {
+    __shared__ double sF[6 * F64V];
+    __shared__ double sJ[3 * J64V];
+    const int nb8 = gridDim.x >> 3;
+    const int tile = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
+    if (tile >= t.ntiles) return;
+    const int beg = t.offs[tile], end = t.offs[tile + 1];
+    if (beg >= end) return;
+    const int tx = tile % t.nt[0], tyz = tile / t.nt[0];
+    const int org[3] = {tx * T64X, (tyz % t.nt[1]) * T64Y, (tyz / t.nt[1]) * T64Z};
+    const int tid = threadIdx.x;
+    for (int e = tid; e < F64V; e += 256) {
+        const int lz = e / (F64X * F64Y), r = e - lz * (F64X * F64Y), ly = r / F64X, lx = r - ly * F64X;
+        const int o = wrap64(g, 0, org[0] - 1 + lx) +
+                      g.ext[0] * (wrap64(g, 1, org[1] - 1 + ly) + g.ext[1] * wrap64(g, 2, org[2] - 1 + lz));
+#pragma unroll
+        for (int q = 0; q < 6; ++q) sF[q * F64V + e] = A.F[q][o];
+    }
+    for (int e = tid; e < 3 * J64V; e += 256) sJ[e] = 0.0;
+    __syncthreads();
+    const double *const F[6] = {sF, sF + F64V, sF + 2 * F64V, sF + 3 * F64V, sF + 4 * F64V, sF + 5 * F64V};
+    double *X[3] = {(double *)sp.pos[0], (double *)sp.pos[1], (double *)sp.pos[2]};
+    double *U[3] = {(double *)sp.u[0], (double *)sp.u[1], (double *)sp.u[2]};
+    const double *W = sp.per_particle_w ? (const double *)sp.w : nullptr;
+    uint32_t bits = 0;
+    for (int q = beg + tid; q < end; q += 256) {
+        const int p = t.perm[q];
+        double pos[3], un[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            pos[a] = X[a][p];
+            un[a] = U[a][p];
+        }
+        const double wp = W ? W[p] : sp.w_species;
+        double xi1[3], f1[3], Ep[3], Bp[3];
+        int l[3];
+        Axis64 ax[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int st = a == 0 ? 1 : (a == 1 ? F64X : F64X * F64Y);
+            xi1[a] = pos[a] / g.d[a];
+            f1[a] = floor(xi1[a]);
+            const double th = xi1[a] - 0.5, fh = floor(th);
+            l[a] = wrap64(g, a, (long long)f1[a]) - org[a];  // 0 .. tile side - 1
+            const int h = l[a] + 1 - (fh < f1[a] ? 1 : 0);   // window index of the half-cell point
+            ax[a].n[0] = (l[a] + 1) * st;
+            ax[a].n[1] = (l[a] + 2) * st;
+            ax[a].h[0] = h * st;
+            ax[a].h[1] = (h + 1) * st;
+            ax[a].fn = xi1[a] - f1[a];
+            ax[a].fh = th - fh;
+        }
+        gather_all(F, ax, Ep, Bp);
+        boris(un, Ep, Bp, A.r);
+        const double gm = sqrt(1.0 + (un[0] * un[0] + un[1] * un[1] + un[2] * un[2]));
+        double xi2[3], f2[3];
+        move64(g, un, gm, xi1, xi2, pos, bits);
+        bool near = true;  // the move ends in this cell or one next to it
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            f2[a] = floor(xi2[a]);
+            near = near && fabs(f2[a] - f1[a]) <= 1.0;
+        }
+        const double amp[3] = {wp * A.kc[0], wp * A.kc[1], wp * A.kc[2]};
+        zigzag(xi1, xi2, f1, f2, amp, [&](const double cell[3], const double v[12]) {
+            if (!near) {
+                add_global(g, A, cell, v);
+                return;
+            }
+            const int b = (l[0] + 1 + (int)(cell[0] - f1[0])) +
+                          J64X * ((l[1] + 1 + (int)(cell[1] - f1[1])) +
+                                  J64Y * (l[2] + 1 + (int)(cell[2] - f1[2])));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int s1 = c == 0 ? J64X : (c == 1 ? J64X * J64Y : 1);
+                const int s2 = c == 0 ? J64X * J64Y : (c == 1 ? 1 : J64X);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    atomicAdd(sJ + c * J64V + b + (e & 1) * s1 + (e >> 1) * s2, v[4 * c + e]);
+            }
+        });
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            X[a][p] = pos[a];
+            U[a][p] = un[a];
+        }
+    }
+    if (bits) atomicOr(fault, bits);
+    __syncthreads();
+    for (int e = tid; e < J64V; e += 256) {
+        const int lz = e / (J64X * J64Y), r = e - lz * (J64X * J64Y), ly = r / J64X, lx = r - ly * J64X;
+        const int o = wrap64(g, 0, org[0] - 1 + lx) +
+                      g.ext[0] * (wrap64(g, 1, org[1] - 1 + ly) + g.ext[1] * wrap64(g, 2, org[2] - 1 + lz));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double v = sJ[c * J64V + e];
+            if (v != 0.0) atomicAdd(A.J[c] + o, v);
+        }
     }
 }
 
@@ -239,8 +493,10 @@ __global__ void k_rho_f64(GridP g, SpeciesP sp, long long count, double *rho) {
     for (int oz = 0; oz < 2; ++oz)
         for (int oy = 0; oy < 2; ++oy)
             for (int ox = 0; ox < 2; ++ox) {
-                const long long ip = at64(g, i0[0] + ox, i0[1] + oy, i0[2] + oz);
-                if (ip < 0) continue;
+                const long long ip =
+                    wrap64(g, 0, i0[0] + ox) +
+                    (long long)g.ext[0] * (wrap64(g, 1, i0[1] + oy) +
+                                           (long long)g.ext[1] * wrap64(g, 2, i0[2] + oz));
                 const double wt = (ox ? f[0] : 1.0 - f[0]) * (oy ? f[1] : 1.0 - f[1]) *
                                   (oz ? f[2] : 1.0 - f[2]);
                 atomicAdd(rho + ip, qsp / dV * wt);
@@ -276,20 +532,68 @@ inline unsigned nblk(long long n, int t) { return (unsigned)((n + t - 1) / t); }
 
 }  // namespace
 
+namespace {
+F64Args args64(const GridP &g, double *const E[3], double *const Bbar[3], double *const J[3],
+               const SpeciesP &sp) {
+    F64Args A{};
+    const double dV = g.d[0] * g.d[1] * g.d[2];
+    for (int a = 0; a < 3; ++a) {
+        A.F[a] = E[a];
+        A.F[3 + a] = Bbar[a];
+        A.J[a] = J ? J[a] : nullptr;
+        A.kc[a] = sp.q * g.d[a] / (g.dt * dV);
+    }
+    A.r = sp.q * g.dt / (2.0 * sp.m);
+    return A;
+}
+}  // namespace
+
+// From this many particles on the binned path is taken.  One step of 8
+// particles per cell, fresh and after 600 steps of mixing (direct | binned):
+// 55 k particles (4 per cell): 49, 43 | 62, 60 us (its four launches cost more than it saves);
+// 131 k: 94, 77 | 64, 63; 2.1 M: 1133, 868 | 156, 183; 7.1 M: 3914, 2854 |
+// 486, 667.  (2.1 M took 2912 us for the push alone with 64-bit modulo index
+// arithmetic and 24 global atomics per particle.)  The binned push is bound by
+// its scattered 8-byte particle accesses once the plasma has mixed: the
+// storage order is the caller's.
+constexpr long long F64_TILED_MIN = 98304;
+
 void launch_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
-                     double *const J[3], const SpeciesP &sp, long long count, uint32_t *fault,
-                     hipStream_t s) {
+                     double *const J[3], const SpeciesP &sp, long long count, int32_t *counts,
+                     int32_t *slots, uint32_t *fault, hipStream_t s) {
     if (count <= 0) return;
-    F64Fields f{{E[0], E[1], E[2]}, {Bbar[0], Bbar[1], Bbar[2]}, {J[0], J[1], J[2]}};
-    hipLaunchKernelGGL(k_push_f64<false>, dim3(nblk(count, 256)), dim3(256), 0, s, g, f, sp,
-                       count, fault, nullptr);
+    const F64Args A = args64(g, E, Bbar, J, sp);
+    if (count < F64_TILED_MIN) {
+        hipLaunchKernelGGL(k_push_f64<false>, dim3(nblk(count, 256)), dim3(256), 0, s, g, A, sp,
+                           count, fault, nullptr);
+        return;
+    }
+    Tiles64 t;
+    t.nt[0] = (g.n[0] + T64X - 1) / T64X;
+    t.nt[1] = (g.n[1] + T64Y - 1) / T64Y;
+    t.nt[2] = (g.n[2] + T64Z - 1) / T64Z;
+    t.ntiles = t.nt[0] * t.nt[1] * t.nt[2];
+    t.counts = counts;
+    t.offs = counts + t.ntiles;
+    t.cursor = t.offs + t.ntiles + 1;
+    t.perm = slots;
+    const dim3 nb(nblk(count, BIN_T * BIN_PER));
+    const bool lds = t.ntiles <= BIN_LDS;
+    const unsigned shm = lds ? (unsigned)t.ntiles * 4u : 0u;
+    hipLaunchKernelGGL(lds ? (k_bin<false, true>) : (k_bin<false, false>), nb, dim3(BIN_T), shm, s,
+                       g, t, sp, count);
+    hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, t);
+    hipLaunchKernelGGL(lds ? (k_bin<true, true>) : (k_bin<true, false>), nb, dim3(BIN_T), shm, s, g,
+                       t, sp, count);
+    hipLaunchKernelGGL(k_push_f64_tiles, dim3(8 * ((t.ntiles + 7) / 8)), dim3(256), 0, s, g, A, t,
+                       sp, fault);
 }
 
 void launch_dry_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
                          const SpeciesP &sp, long long count, double *partial_slot,
                          uint32_t *fault, hipStream_t s) {
-    F64Fields f{{E[0], E[1], E[2]}, {Bbar[0], Bbar[1], Bbar[2]}, {nullptr, nullptr, nullptr}};
-    hipLaunchKernelGGL(k_push_f64<true>, dim3(RED_BLOCKS), dim3(256), 0, s, g, f, sp, count,
+    const F64Args A = args64(g, E, Bbar, nullptr, sp);
+    hipLaunchKernelGGL(k_push_f64<true>, dim3(RED_BLOCKS), dim3(256), 0, s, g, A, sp, count,
                        fault, partial_slot);
 }
 
