@@ -409,11 +409,11 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
     const double jinv = 1.0 / s->jscale;
     JMode jmode = !plasma ? J_NONE : (f32 ? J_FIXED : J_READ);
     if (plasma && (s->filter_passes || s->filter_comp)) {
-        if (f32) launch_j_from_fixed(s->g, (float *const *)J, jf, jinv, s->stream);
         jmode = J_READ;
         T *tmp[3];
         for (int c = 0; c < 3; ++c) tmp[c] = (T *)s->filt + (size_t)c * s->g.V;
-        launch_filter<T>(s->g, J, tmp, s->filter_passes, s->filter_comp, s->stream);
+        launch_filter<T>(s->g, J, f32 ? jf : nullptr, jinv, J, tmp, s->filter_passes,
+                         s->filter_comp, s->stream);
     }
     launch_ampere<T>(s->g, E, B, J, jmode, jf, jinv, s->stream);  // sets the PEC faces too
     if (s->laser.enabled) launch_laser<T>(s->g, E, s->laser, (s->nstep + 0.5) * s->g.dt, s->stream);
@@ -1277,12 +1277,9 @@ empic_status empic_step_vjp(empic_sim *s, const empic_state *st, const empic_adj
     float *lJdep[3] = {lE[0], lE[1], lE[2]};
     if (s->filter_passes || s->filter_comp) {
         float *fl[3];
-        for (int a = 0; a < 3; ++a) {
-            fl[a] = (float *)s->filt + (size_t)a * s->g.V;
-            EMPIC_HIP(hipMemcpyAsync(fl[a], lE[a], (size_t)s->g.V * 4, hipMemcpyDeviceToDevice,
-                                     s->stream));
-        }
-        launch_filter<float>(s->g, fl, tB, s->filter_passes, s->filter_comp, s->stream);
+        for (int a = 0; a < 3; ++a) fl[a] = (float *)s->filt + (size_t)a * s->g.V;
+        launch_filter<float>(s->g, lE, nullptr, 1.0, fl, tB, s->filter_passes, s->filter_comp,
+                             s->stream);
         for (int a = 0; a < 3; ++a) lJdep[a] = fl[a];
     }
     launch_step_vjp(s->g, s->ti, E, Bb, lE, lJdep, lB, lEg, lBb, tB, sp, tiles, lx, lu, s->nsp,

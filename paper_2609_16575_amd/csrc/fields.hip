@@ -343,38 +343,144 @@ __global__ void k_port(GridP g, T *Ec, empic_port_desc P, double amp) {
     Ec[p] = (T)(amp * sin(3.14159265358979323846 * sw / L));
 }
 
-// One pass of the current filter along axis ax: dst = a src[-1] + b src + a src[+1]
-// per component on its own sub-grid; periodic axes wrap, on a walled axis
-// values beyond the stored ones (entry n of a half-cell component is
-// padding) count as zero.
+// The current filter: per axis x, y, z, `passes` binomial passes dst = (src[-1]
+// + 2 src + src[+1])/4, then the compensator; every pass rounds to T.  Each
+// component on its own sub-grid: periodic axes wrap, on a walled axis values
+// beyond the stored ones (entry n of a half-cell component is padding) count
+// as zero in every pass.
 template <typename T>
-__global__ void k_filter_pass(GridP g, int ax, const T *__restrict__ s0, const T *__restrict__ s1,
-                              const T *__restrict__ s2, T *__restrict__ d0, T *__restrict__ d1,
-                              T *__restrict__ d2, T a, T b) {
+__device__ __forceinline__ T filter_point(T lo, T mid, T hi, bool comp) {
+    const T a = comp ? T(-0.25) : T(0.25), b = comp ? T(1.5) : T(0.5);
+    return a * lo + b * mid + a * hi;
+}
+
+// One pass along axis AX (filters too wide for k_filter_tile)
+template <typename T, int AX>
+__global__ __launch_bounds__(PT_THREADS) void k_filter_pass(
+    GridP g, const T *__restrict__ s0, const T *__restrict__ s1, const T *__restrict__ s2,
+    T *__restrict__ d0, T *__restrict__ d1, T *__restrict__ d2, bool comp) {
     Pt q;
     if (!make_point(g, q)) return;
     const T *src[3] = {s0, s1, s2};
     T *dst[3] = {d0, d1, d2};
     const long long p = q.p;
-    const bool per = g.bc[ax] == EMPIC_BC_PERIODIC;
+    const bool per = g.bc[AX] == EMPIC_BC_PERIODIC;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         // stored values of component c along every axis
-        bool valid = true;
-        for (int a2 = 0; a2 < 3; ++a2)
-            if (g.bc[a2] != EMPIC_BC_PERIODIC && a2 == c && q.idx[a2] == g.n[a2]) valid = false;
-        if (!valid) {
+        if (g.bc[c] != EMPIC_BC_PERIODIC && q.idx[c] == g.n[c]) {
             dst[c][p] = T(0);
             continue;
         }
-        const int L = (!per && ax == c) ? g.n[ax] : g.ext[ax];
-        const int i = q.idx[ax];
+        const int L = (!per && AX == c) ? g.n[AX] : g.ext[AX];
+        const int i = q.idx[AX];
         T lo = T(0), hi = T(0);
-        if (i > 0) lo = src[c][p - q.st[ax]];
-        else if (per) lo = src[c][p + (long long)(L - 1) * q.st[ax]];
-        if (i < L - 1) hi = src[c][p + q.st[ax]];
-        else if (per) hi = src[c][p - (long long)(L - 1) * q.st[ax]];
-        dst[c][p] = a * lo + b * src[c][p] + a * hi;
+        if (i > 0) lo = src[c][p - q.st[AX]];
+        else if (per) lo = src[c][p + (long long)(L - 1) * q.st[AX]];
+        if (i < L - 1) hi = src[c][p + q.st[AX]];
+        else if (per) hi = src[c][p - (long long)(L - 1) * q.st[AX]];
+        dst[c][p] = filter_point(lo, src[c][p], hi, comp);
+    }
+}
+
+// The whole filter of M passes per axis in one launch: a workgroup takes one
+// component of a 32 x 8 x 4 patch with M points around it through LDS, the
+// passes ping-ponging between two buffers.  Bound by LDS and latency, not by
+// HBM (the patch's halo comes from L2).  FIXED: the source is the int64
+// current sums (J = sum x jinv rounded once, as k_j_from_fixed).  One binomial
+// pass and the compensator on 75 x 49 x 53 took the conversion and six passes
+// of 27.6 us, whose arrays a run-time axis index kept in scratch: 171 us.  In
+// one launch with each pass over the shrinking window, its coordinates worked
+// out by divisions: 25.4 us; with fixed points per thread as below: 15.9 us.
+constexpr int FTX = 32, FTY = 8, FTZ = 4;
+template <typename T>
+struct FilterPtr {
+    const T *src[3];
+    const long long *fix[3];
+    T *dst[3];
+};
+template <typename T, int M, bool FIXED>
+__global__ __launch_bounds__(256) void k_filter_tile(GridP g, FilterPtr<T> P, int passes,
+                                                     double jinv) {
+    constexpr int WX = FTX + 2 * M, WY = FTY + 2 * M, WZ = FTZ + 2 * M, V = WX * WY * WZ;
+    __shared__ T buf[2][V];
+    __shared__ int sX[WX], sY[WY], sZ[WZ];  // offsets of the window's rows, -1: counts as zero
+    const int c = blockIdx.y, tid = threadIdx.x;
+    const int ntx = (g.ext[0] + FTX - 1) / FTX, nty = (g.ext[1] + FTY - 1) / FTY;
+    const int bx = blockIdx.x % ntx, byz = blockIdx.x / ntx;
+    const int org[3] = {bx * FTX, (byz % nty) * FTY, (byz / nty) * FTZ};
+    if (tid < WX + WY + WZ) {
+        const int a = tid < WX ? 0 : (tid < WX + WY ? 1 : 2);
+        const int l = tid - (a == 0 ? 0 : (a == 1 ? WX : WX + WY));
+        const int n = a == 0 ? g.n[0] : (a == 1 ? g.n[1] : g.n[2]);
+        const int ext = a == 0 ? g.ext[0] : (a == 1 ? g.ext[1] : g.ext[2]);
+        const int bc = a == 0 ? g.bc[0] : (a == 1 ? g.bc[1] : g.bc[2]);
+        const int o = a == 0 ? org[0] : (a == 1 ? org[1] : org[2]);
+        int i = o - M + l;
+        if (bc == EMPIC_BC_PERIODIC) {
+            i %= n;
+            i = i < 0 ? i + n : i;
+        } else if (i < 0 || i >= (a == c ? n : ext)) {
+            i = -1;
+        }
+        if (a == 0) sX[l] = i;
+        else if (a == 1) sY[l] = i < 0 ? -1 : i * g.ext[0];
+        else sZ[l] = i < 0 ? -1 : i * (g.ext[0] * g.ext[1]);
+    }
+    __syncthreads();
+    const T *src = c == 0 ? P.src[0] : (c == 1 ? P.src[1] : P.src[2]);
+    const long long *fix = c == 0 ? P.fix[0] : (c == 1 ? P.fix[1] : P.fix[2]);
+    T *dst = c == 0 ? P.dst[0] : (c == 1 ? P.dst[1] : P.dst[2]);
+    // A thread keeps the same points e = tid + 256 i through every pass, and a
+    // pass covers the whole window: no index arithmetic but e +- stride (the
+    // outermost points go stale by one a pass and are not used), with the
+    // points that count as zero in a bit mask
+    constexpr int NE = (V + 255) / 256;
+    static_assert(NE <= 32, "one mask bit per point of a thread");
+    uint32_t zero = 0u;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int e = tid + 256 * i;
+        if (e >= V) break;
+        const int lx = e % WX, r = e / WX, ly = r % WY, lz = r / WY;
+        const int ox = sX[lx], oy = sY[ly], oz = sZ[lz];
+        T v = T(0);
+        if ((ox | oy | oz) >= 0) {
+            if constexpr (FIXED) v = j_from_fixed<T>(fix[ox + oy + oz], jinv);
+            else v = src[ox + oy + oz];
+        } else {
+            zero |= 1u << i;
+        }
+        buf[0][e] = v;
+    }
+    T *A = buf[0], *B = buf[1];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        constexpr int ST[3] = {1, WX, WX * WY};
+        const int st = ST[ax];
+#pragma unroll 1
+        for (int k = 0; k < M; ++k) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = tid + 256 * i;
+                if (e >= V) break;
+                const T lo = A[max(e - st, 0)], hi = A[min(e + st, V - 1)];
+                const T v = filter_point(lo, A[e], hi, k == passes);
+                B[e] = (zero >> i) & 1u ? T(0) : v;
+            }
+            T *t = A;
+            A = B;
+            B = t;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < FTX * FTY * FTZ; i += 256) {
+        const int lx = i % FTX, ly = (i / FTX) % FTY, lz = i / (FTX * FTY);
+        const int x = org[0] + lx, y = org[1] + ly, z = org[2] + lz;
+        if (x < g.ext[0] && y < g.ext[1] && z < g.ext[2])
+            dst[x + (long long)g.ext[0] * (y + (long long)g.ext[1] * z)] =
+                A[lx + M + WX * (ly + M + WY * (lz + M))];
     }
 }
 
@@ -520,21 +626,71 @@ void launch_mur_apply(const GridP &g, T *const E[3], const T *planes, long long 
     }
 }
 
+namespace {
+template <typename T, int M>
+void filter_tile(const GridP &g, const FilterPtr<T> &P, int passes, double jinv, hipStream_t s) {
+    const int nt = ((g.ext[0] + FTX - 1) / FTX) * ((g.ext[1] + FTY - 1) / FTY) *
+                   ((g.ext[2] + FTZ - 1) / FTZ);
+    if (P.fix[0])
+        hipLaunchKernelGGL((k_filter_tile<T, M, true>), dim3(nt, 3), dim3(256), 0, s, g, P, passes,
+                           jinv);
+    else
+        hipLaunchKernelGGL((k_filter_tile<T, M, false>), dim3(nt, 3), dim3(256), 0, s, g, P, passes,
+                           jinv);
+}
+}  // namespace
+
+// Up to FTILE_M passes per axis go through the patch kernel: both its buffers
+// fit the 64 KB of static LDS (M = 4 in FP32: 60 KB; M = 2 in FP64: 54 KB), and
+// the work on the halos, (1 + 2 M/32)(1 + 2 M/8)(1 + 2 M/4) times the patch,
+// stays below what 3 M launches cost.  Wider filters run pass by pass.
 template <typename T>
-void launch_filter(const GridP &g, T *const F[3], T *const tmp[3], int passes, int compensate,
-                   hipStream_t s) {
-    T *cur[3] = {F[0], F[1], F[2]}, *oth[3] = {tmp[0], tmp[1], tmp[2]};
+void launch_filter(const GridP &g, T *const S[3], const long long *const Jf[3], double jinv,
+                   T *const F[3], T *const tmp[3], int passes, int compensate, hipStream_t s) {
+    constexpr int FTILE_M = sizeof(T) == 4 ? 4 : 2;
+    const int M = passes + (compensate ? 1 : 0);
+    if (M <= FTILE_M) {
+        FilterPtr<T> P{};
+        const bool inplace = !Jf && S[0] == F[0];
+        for (int c = 0; c < 3; ++c) {
+            P.src[c] = S[c];
+            P.fix[c] = Jf ? Jf[c] : nullptr;
+            P.dst[c] = inplace ? tmp[c] : F[c];
+        }
+        if (M == 1) filter_tile<T, 1>(g, P, passes, jinv, s);
+        if (M == 2) filter_tile<T, 2>(g, P, passes, jinv, s);
+        if constexpr (sizeof(T) == 4) {
+            if (M == 3) filter_tile<T, 3>(g, P, passes, jinv, s);
+            if (M == 4) filter_tile<T, 4>(g, P, passes, jinv, s);
+        }
+        if (inplace)
+            for (int c = 0; c < 3; ++c)
+                (void)hipMemcpyAsync(F[c], tmp[c], (size_t)g.V * sizeof(T),
+                                     hipMemcpyDeviceToDevice, s);
+        return;
+    }
+    // pass by pass, alternating so that the last one writes F; an odd number of
+    // passes in place starts from a copy
+    const int N = 3 * M;
+    T *cur[3], *oth[3];
+    for (int c = 0; c < 3; ++c) {
+        cur[c] = N % 2 ? tmp[c] : F[c];
+        oth[c] = N % 2 ? F[c] : tmp[c];
+    }
+    if (Jf) {
+        if constexpr (sizeof(T) == 4) launch_j_from_fixed(g, cur, Jf, jinv, s);
+    } else if (cur[0] != S[0]) {
+        for (int c = 0; c < 3; ++c)
+            (void)hipMemcpyAsync(cur[c], S[c], (size_t)g.V * sizeof(T), hipMemcpyDeviceToDevice, s);
+    }
     for (int ax = 0; ax < 3; ++ax)
-        for (int k = 0; k < passes + (compensate ? 1 : 0); ++k) {
-            const bool comp = k == passes;
-            const T a = comp ? T(-0.25) : T(0.25), b = comp ? T(1.5) : T(0.5);
-            hipLaunchKernelGGL(k_filter_pass<T>, point_grid(g), dim3(PT_THREADS), 0, s, g, ax, cur[0],
-                               cur[1], cur[2], oth[0], oth[1], oth[2], a, b);
+        for (int k = 0; k < M; ++k) {
+            const auto kern = ax == 0 ? k_filter_pass<T, 0>
+                                      : (ax == 1 ? k_filter_pass<T, 1> : k_filter_pass<T, 2>);
+            hipLaunchKernelGGL(kern, point_grid(g), dim3(PT_THREADS), 0, s, g, cur[0], cur[1],
+                               cur[2], oth[0], oth[1], oth[2], k == passes);
             for (int c = 0; c < 3; ++c) std::swap(cur[c], oth[c]);
         }
-    if (cur[0] != F[0])
-        for (int c = 0; c < 3; ++c)
-            (void)hipMemcpyAsync(F[c], cur[c], (size_t)g.V * sizeof(T), hipMemcpyDeviceToDevice, s);
 }
 
 template <typename T>
@@ -584,8 +740,8 @@ void launch_field_energy(const GridP &g, T *const E[3], T *const B[3], double *p
                                   hipStream_t);                                                \
     template void launch_window_shift<T>(const GridP &, T *const[3], T *const[3], int, int,    \
                                          bool, hipStream_t);                                   \
-    template void launch_filter<T>(const GridP &, T *const[3], T *const[3], int, int,          \
-                                   hipStream_t);                                               \
+    template void launch_filter<T>(const GridP &, T *const[3], const long long *const[3],      \
+                                   double, T *const[3], T *const[3], int, int, hipStream_t);   \
     template void launch_port<T>(const GridP &, T *const[3], const empic_port_desc &, double,  \
                                  hipStream_t);                                                 \
     template void launch_field_energy<T>(const GridP &, T *const[3], T *const[3], double *,    \

@@ -233,11 +233,12 @@ void launch_window_shift(const GridP &g, T *const F[3], T *const tmp[3], int ax,
 void launch_window_particles(const SpeciesP &sp, int ax, int cells, hipStream_t s);
 void launch_inject(const SpeciesP &sp, const int lo[3], const int nc[3], const int per[3],
                    float w, int next_id, int32_t *reserve, uint32_t *fault, hipStream_t s);
-// current filter: `passes` binomial passes per axis, then the compensator;
-// tmp: three more arrays of the grid's size
+// current filter: `passes` binomial passes per axis, then the compensator,
+// from S (F itself: in place) or, with Jf, from the int64 current sums times
+// jinv (FP32), into F; tmp: three more arrays of the grid's size
 template <typename T>
-void launch_filter(const GridP &g, T *const F[3], T *const tmp[3], int passes, int compensate,
-                   hipStream_t s);
+void launch_filter(const GridP &g, T *const S[3], const long long *const Jf[3], double jinv,
+                   T *const F[3], T *const tmp[3], int passes, int compensate, hipStream_t s);
 template <typename T>
 void launch_port(const GridP &g, T *const E[3], const empic_port_desc &P, double t, hipStream_t s);
 template <typename T>
