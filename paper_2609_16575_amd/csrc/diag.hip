@@ -86,12 +86,14 @@ __global__ void k_continuity(GridP g, const T *Jx, const T *Jy, const T *Jz, con
     }
 }
 
-__global__ void k_final_reduce(const double *partials, double *result) {
+constexpr int RED_FINAL = 1024;
+__global__ __launch_bounds__(RED_FINAL) void k_final_reduce(const double *partials, double *result) {
     __shared__ double sm[16];
     const int q = blockIdx.x;
     const bool mx = slot_is_max(q);
     double v = 0.0;
-    for (int i = threadIdx.x; i < PSTRIDE; i += blockDim.x) {
+#pragma unroll
+    for (int i = threadIdx.x; i < PSTRIDE; i += RED_FINAL) {
         const double x = partials[(long long)q * PSTRIDE + i];
         v = mx ? fmax(v, x) : v + x;
     }
@@ -163,7 +165,7 @@ void launch_dot_f64(const float *a, const float *b, long long n, double *partial
 }
 
 void launch_final_reduce(const double *partials, double *result, hipStream_t s) {
-    hipLaunchKernelGGL(k_final_reduce, dim3(NQ), dim3(256), 0, s, partials, result);
+    hipLaunchKernelGGL(k_final_reduce, dim3(NQ), dim3(RED_FINAL), 0, s, partials, result);
 }
 
 template void launch_gauss<float>(const GridP &, float *const[3], const double *, double,

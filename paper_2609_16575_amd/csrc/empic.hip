@@ -958,6 +958,15 @@ empic_status empic_step(empic_sim *s, int32_t nsteps) {
     return check_launch(s, "step");
 }
 
+// Fixed-point scale of the charge windows: one contribution |q| w / dV <= 2^48
+static double rho_scale(const empic_sim *s, int i) {
+    const double dV = s->g.d[0] * s->g.d[1] * s->g.d[2];
+    const double B = std::fabs(s->sp[i].desc.q) * s->sp[i].wmax / dV;
+    const double e =
+        B > 0.0 && std::isfinite(B) ? std::floor(std::log2(std::ldexp(1.0, 48) / B)) : 0.0;
+    return std::ldexp(1.0, (int)std::fmax(-1000.0, std::fmin(1000.0, e)));
+}
+
 empic_status empic_deposit_rho(empic_sim *s, int32_t sp, double *rho_out) {
     EMPIC_GUARD(s);
     if (!rho_out || sp < -1 || sp >= s->nsp) return fail(s, EMPIC_E_ARG, "bad rho arguments");
@@ -965,17 +974,11 @@ empic_status empic_deposit_rho(empic_sim *s, int32_t sp, double *rho_out) {
     for (int i = 0; i < s->nsp; ++i) {
         if (sp >= 0 && i != sp) continue;
         const SpeciesP p = species_params(s, i, s->sp[i].cur);
-        if (fp64(s)) {
+        if (fp64(s))
             launch_rho_f64(s->g, p, s->sp[i].host_count, rho_out, s->stream);
-        } else {
-            // fixed-point scale of the tile windows: one contribution |q| w / dV <= 2^48
-            const double dV = s->g.d[0] * s->g.d[1] * s->g.d[2];
-            const double B = std::fabs(s->sp[i].desc.q) * s->sp[i].wmax / dV;
-            const double e =
-                B > 0.0 && std::isfinite(B) ? std::floor(std::log2(std::ldexp(1.0, 48) / B)) : 0.0;
-            const double scale = std::ldexp(1.0, (int)std::fmax(-1000.0, std::fmin(1000.0, e)));
-            launch_rho_f32(s->g, s->ti, s->sp[i].tiles_valid, scale, p, rho_out, s->stream);
-        }
+        else if (!launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, rho_scale(s, i), p, rho_out,
+                                    nullptr, nullptr, nullptr, nullptr, s->fault, s->stream))
+            launch_rho_f32(s->g, p, rho_out, s->stream);
     }
     return check_launch(s, "deposit_rho");
 }
@@ -986,10 +989,11 @@ empic_status empic_diagnostics(empic_sim *s, empic_diag *out) {
     if (!s->bound) return fail(s, EMPIC_E_ARG, "fields not bound");
     std::memset(out, 0, sizeof(*out));
     launch_zero_f64(s->partials, (long long)NQ * PSTRIDE, s->stream);
-    empic_status st = empic_deposit_rho(s, -1, s->rho_cur);
-    if (st != EMPIC_OK) return st;
+    empic_status st = EMPIC_OK;
     const bool cont = s->rho_prev_step >= 0 && s->rho_prev_step == s->nstep - 1;
     if (fp64(s)) {
+        st = empic_deposit_rho(s, -1, s->rho_cur);
+        if (st != EMPIC_OK) return st;
         double *E[3], *B[3], *J[3], *Bb[3];
         field_ptrs<double>(s, E, B, J, Bb);
         launch_gauss<double>(s->g, E, s->rho_cur, s->rho_bg, s->partials, s->stream);
@@ -1005,16 +1009,21 @@ empic_status empic_diagnostics(empic_sim *s, empic_diag *out) {
     } else {
         float *E[3], *B[3], *J[3], *Bb[3];
         field_ptrs<float>(s, E, B, J, Bb);
+        launch_faraday<float>(s->g, E, B, Bb, nullptr, nullptr, false, s->stream);
+        launch_zero_f64(s->rho_cur, s->g.V, s->stream);
+        for (int i = 0; i < s->nsp; ++i) {
+            const SpeciesP p = species_params(s, i, s->sp[i].cur);
+            double *km = s->partials + (Q_KM + i) * PSTRIDE, *kp = s->partials + (Q_KP + i) * PSTRIDE;
+            if (launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, rho_scale(s, i), p, s->rho_cur,
+                                  E, Bb, km, kp, s->fault, s->stream))
+                continue;
+            launch_rho_f32(s->g, p, s->rho_cur, s->stream);
+            launch_kinetic_f32(p, km, s->stream);
+            launch_dry_push_f32(s->g, E, Bb, p, kp, s->fault, s->stream);
+        }
         launch_gauss<float>(s->g, E, s->rho_cur, s->rho_bg, s->partials, s->stream);
         if (cont) launch_continuity<float>(s->g, J, s->rho_cur, s->rho_prev, s->partials, s->stream);
         launch_field_energy<float>(s->g, E, B, s->partials, s->stream);
-        launch_faraday<float>(s->g, E, B, Bb, nullptr, nullptr, false, s->stream);
-        for (int i = 0; i < s->nsp; ++i) {
-            const SpeciesP p = species_params(s, i, s->sp[i].cur);
-            launch_kinetic_f32(p, s->partials + (Q_KM + i) * PSTRIDE, s->stream);
-            launch_dry_push_f32(s->g, E, Bb, p, s->partials + (Q_KP + i) * PSTRIDE, s->fault,
-                                s->stream);
-        }
     }
     launch_final_reduce(s->partials, s->result, s->stream);
     st = check_launch(s, "diagnostics");

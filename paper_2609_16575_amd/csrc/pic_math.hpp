@@ -385,9 +385,12 @@ __device__ __forceinline__ float move_cells(float v, float dtd, float dtd_lo) {
 // Float -> int64 fixed point, round to nearest: the sum with 1.5 * 2^52 puts
 // the integer part of x * scale in the low mantissa bits (valid for
 // |x * scale| < 2^51, which the choice of the scale guarantees).
-__device__ __forceinline__ long long to_fixed(float x, double scale) {
-    const double t = fma((double)x, scale, 6755399441055744.0);
+__device__ __forceinline__ long long fixed_ll(double x, double scale) {
+    const double t = fma(x, scale, 6755399441055744.0);
     return __double_as_longlong(t) - 0x4338000000000000LL;
+}
+__device__ __forceinline__ long long to_fixed(float x, double scale) {
+    return fixed_ll((double)x, scale);
 }
 
 __device__ __forceinline__ int local_axis(const GridP &g, int a, int c, int wo) {

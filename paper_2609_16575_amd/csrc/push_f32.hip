@@ -29,6 +29,8 @@
 // Algorithmic bytes per particle: 28 read + 28 written.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "internal.hpp"
 #include "pic_math.hpp"
 
@@ -912,6 +914,59 @@ __global__ __launch_bounds__(256) void k_push_fallback(FusedArgs A) {
 // ---------------------------------------------------------------------------
 // Diagnostics and conversions (one thread per particle slot)
 // ---------------------------------------------------------------------------
+struct FieldPtrs {
+    const float *E[3];
+    const float *Bb[3];
+};
+
+// m (gamma - 1) of momentum u (times the weight, in mw)
+__device__ __forceinline__ double kinetic(float x, float y, float z, double mw) {
+    const double uu = (double)x * x + (double)y * y + (double)z * z;
+    return mw * uu / (sqrt(1.0 + uu) + 1.0);
+}
+
+// E and centred B of a particle in window cell l at offset o, from the LDS
+// field window
+template <class TL, int ORDER>
+__device__ __forceinline__ void gather_lds(const float *sF, const int l[3], const float o[3],
+                                           float Ep[3], float Bp[3]) {
+    constexpr int FW3 = TL::FW3, FWX = TL::FWX, FWY = TL::FWY;
+    if constexpr (ORDER == 2) {
+        int xn[3], xh[3];
+        float wn[3][3], wh[3][3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            int m;
+            float d;
+            b2_node(o[a], m, d);
+            xn[a] = l[a] + m - 1;
+            b2_w(d, wn[a]);
+            xh[a] = l[a] - 1;
+            b2_w(o[a] - 0.5f, wh[a]);
+        }
+        Ep[0] = tri2_lds<TL>(sF + 0 * FW3, xh[0], xn[1], xn[2], wh[0], wn[1], wn[2]);
+        Ep[1] = tri2_lds<TL>(sF + 1 * FW3, xn[0], xh[1], xn[2], wn[0], wh[1], wn[2]);
+        Ep[2] = tri2_lds<TL>(sF + 2 * FW3, xn[0], xn[1], xh[2], wn[0], wn[1], wh[2]);
+        Bp[0] = tri2_lds<TL>(sF + 3 * FW3, xn[0], xh[1], xh[2], wn[0], wh[1], wh[2]);
+        Bp[1] = tri2_lds<TL>(sF + 4 * FW3, xh[0], xn[1], xh[2], wh[0], wn[1], wh[2]);
+        Bp[2] = tri2_lds<TL>(sF + 5 * FW3, xh[0], xh[1], xn[2], wh[0], wh[1], wn[2]);
+    } else {
+        int h[3];
+        float f[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) half_axis(o[a], l[a], h[a], f[a]);
+        const auto at = [&](int c, int x, int y, int z) {
+            return (const char *)(sF + c * FW3 + x + FWX * (y + FWY * z));
+        };
+        Ep[0] = tri_lds_at<TL>(at(0, h[0], l[1], l[2]), f[0], o[1], o[2]);
+        Ep[1] = tri_lds_at<TL>(at(1, l[0], h[1], l[2]), o[0], f[1], o[2]);
+        Ep[2] = tri_lds_at<TL>(at(2, l[0], l[1], h[2]), o[0], o[1], f[2]);
+        Bp[0] = tri_lds_at<TL>(at(3, l[0], h[1], h[2]), o[0], f[1], f[2]);
+        Bp[1] = tri_lds_at<TL>(at(4, h[0], l[1], h[2]), f[0], o[1], f[2]);
+        Bp[2] = tri_lds_at<TL>(at(5, h[0], h[1], l[2]), f[0], f[1], o[2]);
+    }
+}
+
 __global__ void k_dry_push_f32(GridP g, const float *Ex, const float *Ey, const float *Ez,
                                const float *Bx, const float *By, const float *Bz, SpeciesP sp,
                                float r, float r_lo, double *partial, uint32_t *fault) {
@@ -937,9 +992,8 @@ __global__ void k_dry_push_f32(GridP g, const float *Ex, const float *Ey, const 
         float gam;
         boris_f32(ux, uy, uz, Ep, Bp, r, r_lo, gam);
         if (!isfinite(gam)) atomicOr(fault, (uint32_t)EMPIC_FAULT_NONFINITE);
-        const double uu = (double)ux * ux + (double)uy * uy + (double)uz * uz;
         const double wp = WP ? (double)WP[p] : sp.w_species;
-        ks += wp * sp.m * uu / (sqrt(1.0 + uu) + 1.0);
+        ks += kinetic(ux, uy, uz, wp * sp.m);
     }
     const double t = block_reduce<false>(ks, sm);
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
@@ -953,11 +1007,9 @@ __global__ void k_kinetic_f32(SpeciesP sp, double *partial) {
     for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < count;
          p += (long long)gridDim.x * blockDim.x) {
         if (sp.cell[p] == DEAD) continue;
-        const double ux = ((const float *)sp.u[0])[p], uy = ((const float *)sp.u[1])[p],
-                     uz = ((const float *)sp.u[2])[p];
-        const double uu = ux * ux + uy * uy + uz * uz;
         const double wp = WP ? (double)WP[p] : sp.w_species;
-        ks += wp * sp.m * uu / (sqrt(1.0 + uu) + 1.0);
+        ks += kinetic(((const float *)sp.u[0])[p], ((const float *)sp.u[1])[p],
+                      ((const float *)sp.u[2])[p], wp * sp.m);
     }
     const double t = block_reduce<false>(ks, sm);
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
@@ -1021,81 +1073,183 @@ __global__ void k_rho_f32(GridP g, SpeciesP sp, double *rho) {
     }
 }
 
-// CIC rho of particles still grouped by the tiles of the last sort: one
-// workgroup per tile accumulates its particles in an LDS window of nodes as
-// int64 fixed point (scale: one contribution <= 2^48), then adds the window
-// to the global FP64 array, one atomic per touched node instead of eight per
-// particle.  Particles that drifted out of the window add their eight
-// contributions directly.
-template <class TL>
-__global__ __launch_bounds__(256) void k_rho_tiles(GridP g, TileInfo ti, SpeciesP sp,
-                                                   double scale, double *rho) {
+// Diagnostics of particles still grouped by the tiles of the last sort, one
+// workgroup per tile (a workgroup strides over tiles when they outnumber the
+// partial slots): the charge density in LDS windows of nodes as int64 fixed
+// point (scale: one contribution <= 2^48), added to the global FP64 array with
+// one atomic per touched node, and (KIN) the kinetic energies before and after
+// a push that changes nothing, with E and the centred B gathered from an LDS
+// window as in the step.  Particles that drifted out of the window go through
+// global memory.
+// Bound by LDS atomics and FP64 issue: consecutive lanes hold particles of one
+// cell, so the charge has RHO_REP windows that the lanes take in turn.  The
+// benchmark plasma (2 x 16.8 M): a rho kernel, a kinetic kernel and a push
+// that gathered from global memory took 218 + 83 + 1151 us per species; this
+// one 332 us (0.47 GB of particles: 100 us at a copy's rate).
+constexpr int DIAG_T = 512;
+template <class TL, int ORDER, bool KIN>
+__global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, SpeciesP sp,
+                                                       double scale, double *rho, FieldPtrs F,
+                                                       float r, float r_lo, double *part_m,
+                                                       double *part_p, uint32_t *fault) {
     constexpr int TX = TL::TX, TY = TL::TY, TZ = TL::TZ;
     constexpr int FWX = TL::FWX, FWY = TL::FWY, FWZ = TL::FWZ, FW3 = TL::FW3, ROWS = TL::ROWS;
     constexpr int LHI_X = TL::LHI_X, LHI_Y = TL::LHI_Y, LHI_Z = TL::LHI_Z;
-    __shared__ unsigned long long acc[FW3];
+    constexpr int RHO_REP = ORDER == 1 ? 4 : 3;  // as many as leave two workgroups to a CU
+    constexpr int RS = FW3 + 9;                  // replicas start in different banks
+    __shared__ unsigned long long acc[RHO_REP * RS];
+    __shared__ float sF[KIN ? 6 * FW3 : 1];
     __shared__ int sG[3][ROWS];
-    const int nb8 = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
-    if (tile >= ti.ntiles) return;
-    const int beg = sp.tile_off[tile], end = sp.tile_off[tile + 1];
-    if (beg >= end) return;
-    const int tx = tile % ti.nt[0];
-    const int tyz = tile / ti.nt[0];
-    const int ty = tyz % ti.nt[1], tz = tyz / ti.nt[1];
-    const int wo[3] = {tx * TX - MARGIN - 1, ty * TY - MARGIN - 1, tz * TZ - MARGIN - 1};
+    __shared__ double sm[16];
     const int tid = threadIdx.x;
-    if (tid < 3 * ROWS) {
-        const int a = tid / ROWS, l = tid % ROWS;
-        const int wl = a == 0 ? FWX : (a == 1 ? FWY : FWZ);
-        if (l < wl) {
-            const int gi = gaxis(g, a, wo[a] + l);
-            const int mul = a == 0 ? 1 : (a == 1 ? g.ext[0] : g.ext[0] * g.ext[1]);
-            sG[a][l] = gi < 0 ? -1 : gi * mul;
-        }
-    }
-    for (int e = tid; e < FW3; e += 256) acc[e] = 0ull;
-    __syncthreads();
+    const int nb8 = gridDim.x >> 3;
+    const int nt8 = (ti.ntiles + 7) / 8;  // tiles of one XCD
     const float *WP = (sp.per_particle_w && sp.w) ? (const float *)sp.w : nullptr;
     const double dV = g.d[0] * g.d[1] * g.d[2];
-    for (int p = beg + tid; p < end; p += 256) {
-        const uint32_t c = sp.cell[p];
-        if (c == DEAD) continue;
-        const double amp = sp.q * (WP ? (double)WP[p] : sp.w_species) / dV;
-        const int ci[3] = {cell_i(c), cell_j(c), cell_k(c)};
-        const double f[3] = {((const float *)sp.pos[0])[p], ((const float *)sp.pos[1])[p],
-                             ((const float *)sp.pos[2])[p]};
-        const int lx = local_axis(g, 0, ci[0], wo[0]), ly = local_axis(g, 1, ci[1], wo[1]),
-                  lz = local_axis(g, 2, ci[2], wo[2]);
-        const bool inwin =
-            lx >= 1 && lx <= LHI_X && ly >= 1 && ly <= LHI_Y && lz >= 1 && lz <= LHI_Z;
-        for (int o = 0; o < 8; ++o) {
-            const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-            const double wt = (ox ? f[0] : 1.0 - f[0]) * (oy ? f[1] : 1.0 - f[1]) *
-                              (oz ? f[2] : 1.0 - f[2]);
-            if (inwin) {
-                const long long v = __double2ll_rn(amp * wt * scale);
-                atomicAdd(acc + (lx + ox) + FWX * ((ly + oy) + FWY * (lz + oz)),
-                          (unsigned long long)v);
-            } else {
-                const int gx = gaxis(g, 0, ci[0] + ox), gy = gaxis(g, 1, ci[1] + oy),
-                          gz = gaxis(g, 2, ci[2] + oz);
-                if (gx < 0 || gy < 0 || gz < 0) continue;
-                atomicAdd(rho + gx + (long long)g.ext[0] * (gy + (long long)g.ext[1] * gz), amp * wt);
+    double km = 0.0, kp = 0.0;
+    uint32_t bad = 0u;
+    for (int q = blockIdx.x >> 3; q < nt8; q += nb8) {
+        const int tile = (blockIdx.x & 7) * nt8 + q;  // XCD-contiguous tiles
+        if (tile >= ti.ntiles) break;
+        const int beg = sp.tile_off[tile], end = sp.tile_off[tile + 1];
+        if (beg >= end) continue;
+        const int tx = tile % ti.nt[0];
+        const int tyz = tile / ti.nt[0];
+        const int ty = tyz % ti.nt[1], tz = tyz / ti.nt[1];
+        const int wo[3] = {tx * TX - MARGIN - 1, ty * TY - MARGIN - 1, tz * TZ - MARGIN - 1};
+        if (tid < 3 * ROWS) {
+            const int a = tid / ROWS, l = tid % ROWS;
+            const int wl = a == 0 ? FWX : (a == 1 ? FWY : FWZ);
+            if (l < wl) {
+                const int gi = gaxis(g, a, (a == 0 ? wo[0] : (a == 1 ? wo[1] : wo[2])) + l);
+                const int mul = a == 0 ? 1 : (a == 1 ? g.ext[0] : g.ext[0] * g.ext[1]);
+                sG[a][l] = gi < 0 ? -1 : gi * mul;
             }
         }
+        for (int e = tid; e < RHO_REP * RS; e += DIAG_T) acc[e] = 0ull;
+        __syncthreads();
+        if constexpr (KIN) {
+            constexpr int NR = (FW3 + DIAG_T - 1) / DIAG_T;
+            float tmp[6][NR];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                const int e = tid + k * DIAG_T;
+                const int lz = e / (FWX * FWY), r2 = e - lz * (FWX * FWY);
+                const int ly = r2 / FWX, lx = r2 - ly * FWX;
+                int o = -1;
+                if (e < FW3 && (sG[0][lx] | sG[1][ly] | sG[2][lz]) >= 0)
+                    o = sG[0][lx] + sG[1][ly] + sG[2][lz];
+#pragma unroll
+                for (int c = 0; c < 6; ++c)
+                    tmp[c][k] = o >= 0 ? (c < 3 ? F.E[c] : F.Bb[c - 3])[o] : 0.f;
+            }
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+#pragma unroll
+                for (int c = 0; c < 6; ++c)
+                    if (tid + k * DIAG_T < FW3) sF[c * FW3 + tid + k * DIAG_T] = tmp[c][k];
+            __syncthreads();
+        }
+        unsigned long long *ac = acc + (tid % RHO_REP) * RS;
+        for (int p = beg + tid; p < end; p += DIAG_T) {
+            const uint32_t c = sp.cell[p];
+            if (c == DEAD) continue;
+            const double wp = WP ? (double)WP[p] : sp.w_species;
+            const double amp = sp.q * wp / dV;
+            const int ci[3] = {cell_i(c), cell_j(c), cell_k(c)};
+            const float o[3] = {((const float *)sp.pos[0])[p], ((const float *)sp.pos[1])[p],
+                                ((const float *)sp.pos[2])[p]};
+            const int l[3] = {local_axis(g, 0, ci[0], wo[0]), local_axis(g, 1, ci[1], wo[1]),
+                              local_axis(g, 2, ci[2], wo[2])};
+            const bool inwin = l[0] >= 1 && l[0] <= LHI_X && l[1] >= 1 && l[1] <= LHI_Y &&
+                               l[2] >= 1 && l[2] <= LHI_Z;
+            // node weights, from the first node of the stencil
+            constexpr int NP = ORDER + 1;
+            double w[3][NP];
+            int first[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double f = o[a];
+                if constexpr (ORDER == 1) {
+                    first[a] = 0;
+                    w[a][0] = 1.0 - f;
+                    w[a][1] = f;
+                } else {
+                    const double d = f - (f >= 0.5 ? 1.0 : 0.0);
+                    first[a] = f >= 0.5 ? 0 : -1;
+                    w[a][0] = 0.5 * (0.5 - d) * (0.5 - d);
+                    w[a][1] = 0.75 - d * d;
+                    w[a][2] = 0.5 * (0.5 + d) * (0.5 + d);
+                }
+            }
+            if (inwin) {
+                const int b = l[0] + first[0] + FWX * (l[1] + first[1] + FWY * (l[2] + first[2]));
+#pragma unroll
+                for (int k = 0; k < NP; ++k)
+#pragma unroll
+                    for (int j = 0; j < NP; ++j)
+#pragma unroll
+                        for (int i = 0; i < NP; ++i) {
+                            const double wt = w[0][i] * w[1][j] * w[2][k];
+                            atomicAdd(ac + b + i + FWX * (j + FWY * k),
+                                      (unsigned long long)fixed_ll(amp * wt, scale));
+                        }
+            } else {
+                for (int k = 0; k < NP; ++k) {
+                    const int gz = gaxis(g, 2, ci[2] + first[2] + k);
+                    if (gz < 0) continue;
+                    for (int j = 0; j < NP; ++j) {
+                        const int gy = gaxis(g, 1, ci[1] + first[1] + j);
+                        if (gy < 0) continue;
+                        for (int i = 0; i < NP; ++i) {
+                            const int gx = gaxis(g, 0, ci[0] + first[0] + i);
+                            if (gx < 0) continue;
+                            const double wx = i == 0 ? w[0][0] : (i == 1 ? w[0][1] : w[0][NP - 1]);
+                            const double wy = j == 0 ? w[1][0] : (j == 1 ? w[1][1] : w[1][NP - 1]);
+                            const double wz = k == 0 ? w[2][0] : (k == 1 ? w[2][1] : w[2][NP - 1]);
+                            atomicAdd(rho + gx + (long long)g.ext[0] * (gy + (long long)g.ext[1] * gz),
+                                      amp * (wx * wy * wz));
+                        }
+                    }
+                }
+            }
+            if constexpr (KIN) {
+                float ux = ((const float *)sp.u[0])[p], uy = ((const float *)sp.u[1])[p],
+                      uz = ((const float *)sp.u[2])[p];
+                km += kinetic(ux, uy, uz, wp * sp.m);
+                float Ep[3], Bp[3], gam;
+                if (inwin) gather_lds<TL, ORDER>(sF, l, o, Ep, Bp);
+                else if constexpr (ORDER == 2)
+                    gather2_global(g, F.E, F.Bb, ci[0], ci[1], ci[2], o[0], o[1], o[2], Ep, Bp);
+                else gather_global(g, F.E, F.Bb, ci[0], ci[1], ci[2], o[0], o[1], o[2], Ep, Bp);
+                boris_f32(ux, uy, uz, Ep, Bp, r, r_lo, gam);
+                if (!isfinite(gam)) bad |= EMPIC_FAULT_NONFINITE;
+                kp += kinetic(ux, uy, uz, wp * sp.m);
+            }
+        }
+        __syncthreads();
+        const double inv = 1.0 / scale;
+        for (int e = tid; e < FW3; e += DIAG_T) {
+            unsigned long long v = acc[e];
+#pragma unroll
+            for (int k = 1; k < RHO_REP; ++k) v += acc[k * RS + e];
+            if (v == 0) continue;
+            const int lz = e / (FWX * FWY);
+            const int r2 = e - lz * (FWX * FWY);
+            const int ly = r2 / FWX, lx = r2 - ly * FWX;
+            const int gx = sG[0][lx], gy = sG[1][ly], gz = sG[2][lz];
+            if (gx < 0 || gy < 0 || gz < 0) continue;
+            atomicAdd(rho + gx + gy + gz, (double)(long long)v * inv);
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    const double inv = 1.0 / scale;
-    for (int e = tid; e < FW3; e += 256) {
-        const long long v = (long long)acc[e];
-        if (v == 0) continue;
-        const int lz = e / (FWX * FWY);
-        const int r = e - lz * (FWX * FWY);
-        const int ly = r / FWX, lx = r - ly * FWX;
-        const int gx = sG[0][lx], gy = sG[1][ly], gz = sG[2][lz];
-        if (gx < 0 || gy < 0 || gz < 0) continue;
-        atomicAdd(rho + gx + gy + gz, (double)v * inv);
+    if constexpr (KIN) {
+        const double a = block_reduce<false>(km, sm), b = block_reduce<false>(kp, sm);
+        if (tid == 0) {
+            part_m[blockIdx.x] = a;
+            part_p[blockIdx.x] = b;
+        }
+        if (bad) atomicOr(fault, bad);
     }
 }
 
@@ -1616,20 +1770,46 @@ void launch_kinetic_f32(const SpeciesP &sp, double *partial_slot, hipStream_t s)
     hipLaunchKernelGGL(k_kinetic_f32, dim3(RED_BLOCKS), dim3(256), 0, s, sp, partial_slot);
 }
 
-void launch_rho_f32(const GridP &g, const TileInfo &ti, bool tiles_valid, double scale,
-                    const SpeciesP &sp, double *rho, hipStream_t s) {
-    if (sp.capacity <= 0) return;
-    if (g.shape_order == 2) {
-        hipLaunchKernelGGL(k_rho2_f32, dim3(nblk(sp.capacity, 256)), dim3(256), 0, s, g, sp, rho);
-        return;
-    }
-    const unsigned nb = 8 * ((ti.ntiles + 7) / 8);
-    if (tiles_valid && ti.slab)
-        hipLaunchKernelGGL(k_rho_tiles<TileSlab>, dim3(nb), dim3(256), 0, s, g, ti, sp, scale, rho);
-    else if (tiles_valid)
-        hipLaunchKernelGGL(k_rho_tiles<TileCube>, dim3(nb), dim3(256), 0, s, g, ti, sp, scale, rho);
+namespace {
+template <class TL, int ORDER>
+void diag_tiles(const GridP &g, const TileInfo &ti, double scale, const SpeciesP &sp, double *rho,
+                const FieldPtrs *F, double *part_m, double *part_p, uint32_t *fault,
+                hipStream_t s) {
+    // one partial slot per workgroup
+    const int nb = 8 * std::min((ti.ntiles + 7) / 8, PSTRIDE / 8);
+    float r, r_lo;
+    split_f32(sp.q * g.dt / (2.0 * sp.m), r, r_lo);
+    if (F)
+        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, true>), dim3(nb), dim3(DIAG_T), 0, s, g, ti, sp,
+                           scale, rho, *F, r, r_lo, part_m, part_p, fault);
     else
-        hipLaunchKernelGGL(k_rho_f32, dim3(nblk(sp.capacity, 256)), dim3(256), 0, s, g, sp, rho);
+        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, false>), dim3(nb), dim3(DIAG_T), 0, s, g, ti, sp,
+                           scale, rho, FieldPtrs{}, r, r_lo, part_m, part_p, fault);
+}
+}  // namespace
+
+bool launch_diag_tiles(const GridP &g, const TileInfo &ti, bool tiles_valid, double scale,
+                       const SpeciesP &sp, double *rho, float *const E[3], float *const Bbar[3],
+                       double *part_m, double *part_p, uint32_t *fault, hipStream_t s) {
+    if (!tiles_valid || sp.capacity <= 0) return false;
+    FieldPtrs F{};
+    if (E)
+        for (int a = 0; a < 3; ++a) {
+            F.E[a] = E[a];
+            F.Bb[a] = Bbar[a];
+        }
+    const FieldPtrs *f = E ? &F : nullptr;
+    if (ti.slab) diag_tiles<TileSlab, 1>(g, ti, scale, sp, rho, f, part_m, part_p, fault, s);
+    else if (g.shape_order == 2)
+        diag_tiles<TileCube2, 2>(g, ti, scale, sp, rho, f, part_m, part_p, fault, s);
+    else diag_tiles<TileCube, 1>(g, ti, scale, sp, rho, f, part_m, part_p, fault, s);
+    return true;
+}
+
+void launch_rho_f32(const GridP &g, const SpeciesP &sp, double *rho, hipStream_t s) {
+    if (sp.capacity <= 0) return;
+    hipLaunchKernelGGL(g.shape_order == 2 ? k_rho2_f32 : k_rho_f32, dim3(nblk(sp.capacity, 256)),
+                       dim3(256), 0, s, g, sp, rho);
 }
 
 void launch_load_f32(const GridP &g, const SpeciesP &sp, long long count, const double *pos,
