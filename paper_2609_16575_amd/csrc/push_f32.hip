@@ -207,6 +207,7 @@ __device__ __forceinline__ void load_batch(const SpeciesP &S, int base, Batch<P>
 #pragma unroll
     for (int k = 0; k < P; ++k) b.w[k] = 1.f;
     if (S.per_particle_w) b.w = __builtin_nontemporal_load((const VF *)((const gfloat *)S.w + base));
+
 }
 
 // Mid-point and displacement of the second ZigZag segment of a move from
@@ -268,6 +269,16 @@ struct TileCtx {
 // rare crossings do not make every lane of a wave wait for a second
 // segment.  A full queue makes the particle deposit its second segment at
 // once.
+//
+// On the benchmark plasma (540 us per launch) the kernel sits between three
+// bounds: its 1.96 GB take 413 us at a copy's rate (4.7 TB/s; 403 us measured
+// without the gathers and the LDS adds), its VALU instructions about 400 us
+// and its LDS accesses about 300 us, overlapped by 16 waves per CU.  The
+// cell steps as floats from one floor per axis, one test for all faults and
+// rare cases, corner addresses added up from each other and the split of the
+// first segment only in waves with a crossing took 30 VALU instructions off
+// each particle: 555 -> 540 us.  Compiling the weight away where a species has
+// none spilled in the sparse-tile code (wakefield box 1310 -> 1700 us).
 template <class TL, int P, bool INTERIOR>
 __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecies &D,
                                              const SpeciesP &S, const SpeciesP &Wr, int beg,
@@ -285,16 +296,14 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
     guint *CQ = (guint *)Wr.cell;
     gfloat *OXQ = (gfloat *)Wr.pos[0], *OYQ = (gfloat *)Wr.pos[1], *OZQ = (gfloat *)Wr.pos[2];
     gfloat *UXQ = (gfloat *)Wr.u[0], *UYQ = (gfloat *)Wr.u[1], *UZQ = (gfloat *)Wr.u[2];
-    // per-component window bases, opaque to the compiler so that it keeps one
-    // register base per component and puts the eight corner offsets of a
-    // gather into the ds_read2 offset fields
-    const char *sFc[6];
+    // offsets of the components' windows: E_c's, and Bbar_x's from E_y's,
+    // Bbar_y's and Bbar_z's from E_x's (a corner's address is one add3 from
+    // another's); opaque to the compiler so that it keeps one register base
+    // per component and puts the eight corner offsets of a gather into the
+    // ds_read2 offset fields
+    uint32_t sFo[6] = {0, FW3 * 4, 2 * FW3 * 4, 2 * FW3 * 4, 4 * FW3 * 4, 5 * FW3 * 4};
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        uint32_t o = c * FW3 * 4;
-        asm volatile("" : "+s"(o));
-        sFc[c] = (const char *)sF + o;
-    }
+    for (int c = 0; c < 6; ++c) asm volatile("" : "+s"(sFo[c]));
     const int lane = (int)(threadIdx.x & 63);
     const int base0 = batch_base0<P>(beg) + (int)threadIdx.x * P;
     // one (non-temporal) access of P consecutive particles per array; with
@@ -333,59 +342,88 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
                                    (unsigned)(lz - 1) < (unsigned)LHI_Z);
             if (list_fallback(A, outside, s, p, nfb)) continue;
             const float ox = b.ox[k], oy = b.oy[k], oz = b.oz[k];
-            // a NaN offset is caught below as a non-finite momentum
-            if (!(fminf(fminf(ox, oy), oz) >= 0.f && fmaxf(fmaxf(ox, oy), oz) < 1.f))
-                fbits |= EMPIC_FAULT_OFFSET;
-            int hx, hy, hz;
-            float fx, fy, fz;
-            half_axis(ox, lx, hx, fx);
-            half_axis(oy, ly, hy, fy);
-            half_axis(oz, lz, hz, fz);
-            // byte offsets of the node (l) and half (h) positions per axis
-            const uint32_t xl = (uint32_t)lx * 4u, xh = (uint32_t)hx * 4u;
-            const uint32_t yl = __umul24((uint32_t)ly, FWX * 4), yh = __umul24((uint32_t)hy, FWX * 4);
-            const uint32_t zl = __umul24((uint32_t)lz, FWX * FWY * 4),
-                           zh = __umul24((uint32_t)hz, FWX * FWY * 4);
+            // per axis: whether the half-cell point below the particle is the one
+            // under its cell's node, and the fraction from it
+            const bool sx = ox < 0.5f, sy = oy < 0.5f, sz = oz < 0.5f;
+            const float fx = ox + (sx ? 0.5f : -0.5f), fy = oy + (sy ? 0.5f : -0.5f),
+                        fz = oz + (sz ? 0.5f : -0.5f);
+            // byte addresses of the six corners: the node's, less a row, plane or
+            // point where the component is half-staggered
+            const uint32_t nb = (uint32_t)lx * 4u + (uint32_t)ly * (FWX * 4u) +
+                                (uint32_t)lz * (FWX * FWY * 4u);
+            const uint32_t hx = sx ? -4u : 0u, hy = sy ? -(FWX * 4u) : 0u,
+                           hz = sz ? -(FWX * FWY * 4u) : 0u;
+            const uint32_t a0 = nb + hx + sFo[0], a1 = nb + hy + sFo[1], a2 = nb + hz + sFo[2];
+            const uint32_t a3 = a1 + hz + sFo[3], a4 = a0 + hz + sFo[4], a5 = a0 + hy + sFo[5];
+            const char *sFb = (const char *)sF;
             float Ep[3], Bp[3];
-            Ep[0] = tri_lds_at<TL>(sFc[0] + (xh + yl + zl), fx, oy, oz);
-            Ep[1] = tri_lds_at<TL>(sFc[1] + (xl + yh + zl), ox, fy, oz);
-            Ep[2] = tri_lds_at<TL>(sFc[2] + (xl + yl + zh), ox, oy, fz);
-            Bp[0] = tri_lds_at<TL>(sFc[3] + (xl + yh + zh), ox, fy, fz);
-            Bp[1] = tri_lds_at<TL>(sFc[4] + (xh + yl + zh), fx, oy, fz);
-            Bp[2] = tri_lds_at<TL>(sFc[5] + (xh + yh + zl), fx, fy, oz);
+            Ep[0] = tri_lds_at<TL>(sFb + a0, fx, oy, oz);
+            Ep[1] = tri_lds_at<TL>(sFb + a1, ox, fy, oz);
+            Ep[2] = tri_lds_at<TL>(sFb + a2, ox, oy, fz);
+            Bp[0] = tri_lds_at<TL>(sFb + a3, ox, fy, fz);
+            Bp[1] = tri_lds_at<TL>(sFb + a4, fx, oy, fz);
+            Bp[2] = tri_lds_at<TL>(sFb + a5, fx, fy, oz);
             float ux = b.ux[k], uy = b.uy[k], uz = b.uz[k], gam;
             const float ig = boris_f32(ux, uy, uz, Ep, Bp, r, r_lo, gam);
-            if (!isfinite(gam)) fbits |= EMPIC_FAULT_NONFINITE;
             const float o[3] = {ox, oy, oz};
             const float dx[3] = {move_cells(ux * ig, A.dtd[0], A.dtd_lo[0]),
                                  move_cells(uy * ig, A.dtd[1], A.dtd_lo[1]),
                                  move_cells(uz * ig, A.dtd[2], A.dtd_lo[2])};
-            if (!(fmaxf(fmaxf(fabsf(dx[0]), fabsf(dx[1])), fabsf(dx[2])) < 1.f))
-                fbits |= EMPIC_FAULT_FAST;
-            float e[3], no[3];
-            int dc[3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a) move_axis_sel(o[a], dx[a], e[a], dc[a], no[a]);
-            const float wq = b.w[k];
-
-            const int jb = lx + JWX * (ly + JWY * lz);
-            const bool cross = (dc[0] | dc[1] | dc[2]) != 0;
-            // first segment: the whole move inside the cell, or from the start
-            // to the relay point (Sec. 2.5, ZigZag)
-            const float half = cross ? 0.5f : 1.f;
-            float WA[3], DA[3];
+            // new offsets and cell steps fl (-1, 0, 1 as floats)
+            float no[3], fl[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const float xr = dc[a] > 0 ? 1.f : 0.f;
-                DA[a] = dc[a] != 0 ? xr - o[a] : half * dx[a];
-                WA[a] = fmaf(0.5f, DA[a], o[a]);
+                const float e = o[a] + dx[a];
+                fl[a] = floorf(e);
+                no[a] = e - fl[a];
             }
+            // one test for everything out of the ordinary: an end point whose
+            // e + 1 rounds to 1 (stays at offset 0 of its cell, see move_axis), a
+            // move of a cell or more, a non-finite momentum (its 1/gamma and so
+            // every move is then NaN), a stored offset outside [0, 1)
+            const float big = fmaxf(fmaxf(fmaxf(fabsf(dx[0]), fabsf(dx[1])), fabsf(dx[2])),
+                                    fmaxf(fmaxf(no[0], no[1]), no[2]));
+            const uint32_t obits = max(max(__float_as_uint(ox), __float_as_uint(oy)),
+                                       __float_as_uint(oz));
+            if (__builtin_expect(!(big < 1.f) || obits >= 0x3f800000u, 0)) {
+                // a NaN offset is a non-finite momentum
+                if (!(fminf(fminf(ox, oy), oz) >= 0.f && fmaxf(fmaxf(ox, oy), oz) < 1.f))
+                    fbits |= EMPIC_FAULT_OFFSET;
+                if (!isfinite(gam)) fbits |= EMPIC_FAULT_NONFINITE;
+                if (!(fmaxf(fmaxf(fabsf(dx[0]), fabsf(dx[1])), fabsf(dx[2])) < 1.f))
+                    fbits |= EMPIC_FAULT_FAST;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    float e;
+                    int dc;
+                    move_axis_sel(o[a], dx[a], e, dc, no[a]);
+                    fl[a] = (float)dc;
+                }
+            }
+            const float wq = b.w[k];
+
+            // the cell step packed like a cell index; exact in FP32
+            const float pk = fmaf(fl[2], 4194304.f, fmaf(fl[1], 2048.f, fl[0]));
+            const bool cross = pk != 0.f;
+            const unsigned long long m = __ballot(cross);
+            const int jb = lx + JWX * (ly + JWY * lz);
+            // first segment: the whole move inside the cell, or from the start
+            // to the relay point (Sec. 2.5, ZigZag)
+            float WA[3], DA[3] = {dx[0], dx[1], dx[2]};
+            if (m) {
+                const float half = cross ? 0.5f : 1.f;
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    DA[a] = fl[a] != 0.f ? fmaxf(fl[a], 0.f) - o[a] : half * dx[a];
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) WA[a] = fmaf(0.5f, DA[a], o[a]);
             lds_add_segment<TL>(sJ, jb, WA, DA, wq, mult);
             // second segment of the crossing particles: from the relay point
             // to the end, in the cell + dc; queued as the move itself (the
             // segment is worked out when the queue is deposited)
-            const unsigned long long m = __ballot(cross);
             if (m) {
+                const int dc[3] = {(int)fl[0], (int)fl[1], (int)fl[2]};
                 bool now = cross;
                 if constexpr (TL::QCAP > 0) {
                     unsigned qb = 0;
@@ -413,12 +451,12 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
             }
             if constexpr (INTERIOR) {
                 // inside the grid on every axis: a step of the packed index
-                b.c[k] = c + (uint32_t)(dc[0] + (dc[1] << 11) + (dc[2] << 22));
+                b.c[k] = c + (uint32_t)(int)pk;
             } else {
                 int ni, nj, nk;
-                const int in = (int)new_cell(g, 0, cell_i(c), dc[0], ni) &
-                               (int)new_cell(g, 1, cell_j(c), dc[1], nj) &
-                               (int)new_cell(g, 2, cell_k(c), dc[2], nk);
+                const int in = (int)new_cell(g, 0, cell_i(c), (int)fl[0], ni) &
+                               (int)new_cell(g, 1, cell_j(c), (int)fl[1], nj) &
+                               (int)new_cell(g, 2, cell_k(c), (int)fl[2], nk);
                 b.c[k] = in ? pack_cell(ni, nj, nk) : DEAD;
             }
             b.ox[k] = no[0];
@@ -650,19 +688,15 @@ __device__ __forceinline__ void push_tile(const FusedArgs &A, const TileCtx &T, 
                                           bool sparse0, int beg0, int end0, const Batch<1> &pre1,
                                           const float *sF, unsigned long long *sJ,
                                           const SegQueue &Q, uint32_t &fbits, unsigned &nfb) {
-    if (sparse0)
-        push_species<TL, 1, INTERIOR>(A, A.tbl[0], A.tbl[0].p[A.cur_mask & 1u],
-                                      A.tbl[0].p[A.wr_mask & 1u], beg0, end0, T, sF, sJ, Q, 0,
-                                      fbits, nfb, pre1, true);
-    for (int s = sparse0 ? 1 : 0; s < A.nsp; ++s) {
+    for (int s = 0; s < A.nsp; ++s) {
         const DevSpecies &D = A.tbl[s];
         const SpeciesP &S = D.p[(A.cur_mask >> s) & 1u];
         const SpeciesP &Wr = D.p[(A.wr_mask >> s) & 1u];
-        const int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
+        const int beg = s == 0 ? beg0 : S.tile_off[tile], end = s == 0 ? end0 : S.tile_off[tile + 1];
         if (beg >= end) continue;
         if (end - beg <= 2 * PUSH_THREADS)
-            push_species<TL, 1, INTERIOR>(A, D, S, Wr, beg, end, T, sF, sJ, Q, s, fbits, nfb,
-                                          pre1, false);
+            push_species<TL, 1, INTERIOR>(A, D, S, Wr, beg, end, T, sF, sJ, Q, s, fbits, nfb, pre1,
+                                          s == 0 && sparse0);
         else
             push_species<TL, PPT, INTERIOR>(A, D, S, Wr, beg, end, T, sF, sJ, Q, s, fbits, nfb,
                                             Batch<PPT>(), false);
