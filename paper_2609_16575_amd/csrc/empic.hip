@@ -48,6 +48,7 @@ void tile_shape_of(const empic_grid_desc *d, int t[3], int &slab) {
 void grid_info(const empic_grid_desc *d, GridP &g, TileInfo &ti) {
     int t[3];
     tile_shape_of(d, t, ti.slab);
+    ti.fold = ti.slab && d->bc[1] == EMPIC_BC_PERIODIC && d->n[1] <= 2 ? 1 : 0;
     for (int a = 0; a < 3; ++a) {
         g.n[a] = d->n[a];
         g.bc[a] = d->bc[a];

@@ -70,6 +70,9 @@ struct TileT {
     static constexpr int FW3 = FWX * FWY * FWZ, JW3 = JWX * JWY * JWZ;
     static constexpr int LHI_X = X + 2 * MARGIN, LHI_Y = Y + 2 * MARGIN, LHI_Z = Z + 2 * MARGIN;
     static constexpr int ROWS = 24;  // rows of the window index tables
+    static constexpr bool FOLD = false;
+    static constexpr int MGX = MARGIN, MGZ = MARGIN;  // drift margins of the windows
+    static constexpr int REP = 1, JREP = 3 * JW3;  // copies of the current window, their stride
     static_assert(X * Y * Z == TC, "every tile shape holds TC cells");
     static_assert(JWX <= ROWS && JWY <= ROWS && JWZ <= ROWS, "window index tables");
     static_assert((X & (X - 1)) == 0 && (Y & (Y - 1)) == 0 && (Z & (Z - 1)) == 0,
@@ -84,6 +87,31 @@ using TileCube = TileT<8, 8, 4, 512>;
 // 34.6 KB + 45.9 KB, still two workgroups in a CU's 160 KB of LDS, which
 // leaves no room for a crossing queue.
 using TileSlab = TileT<16, 2, 8, 0>;
+// The push on grids one or two cells thick along a periodic y (the
+// two-dimensional runs): the same 16 x 2 x 8 tile with windows folded onto the
+// two rows that exist, [z][x][row], where TileSlab's hold 6 and 7 rows of
+// them.  What that frees goes into a margin of MGX, MGZ cells (relativistic
+// particles cross half a cell per step, and the moving window sorts every 16)
+// and into REP copies of the current window that neighbouring lanes take in
+// turn (with 32 particles per cell eight of them hold one cell).  77 KB, two
+// workgroups per CU.  The wakefield run with 32 particles per cell (26.9 M; its
+// 1.5 GB take 320 us at a copy's rate): 801 us per launch with TileSlab; folded
+// with 1, 2, 3 copies and margins of 3: 758, 510, 442 us; 4 copies and margins
+// (3, 1): 421 us (4 copies leave no more).  Pass of 32 steps: 44.5 ms; margins
+// (3, 1) 23.1, (2, 1) 29.1, (5, 1) with 3 copies 23.4, (4, 2) 23.6, (3, 3) 23.4.  A
+// crossing queue in place of a copy made no difference.
+struct TileFold {
+    static constexpr int TX = 16, TY = 2, TZ = 8, QCAP = 0, MGX = 3, MGZ = 1;
+    static constexpr bool FOLD = true;
+    static constexpr int FWX = TX + 2 * MGX + 2, FWY = 2, FWZ = TZ + 2 * MGZ + 2;
+    static constexpr int JWX = TX + 2 * MGX + 3, JWY = 2, JWZ = TZ + 2 * MGZ + 3;
+    static constexpr int FW3 = FWX * FWY * FWZ, JW3 = JWX * JWY * JWZ;
+    static constexpr int LHI_X = TX + 2 * MGX, LHI_Y = 2, LHI_Z = TZ + 2 * MGZ;
+    static constexpr int ROWS = 32;
+    static constexpr int REP = 4, JREP = 3 * JW3 + 6;
+    static_assert(JWX <= ROWS && JWZ <= ROWS, "window index tables");
+    static_assert(FWX * FWZ <= PUSH_THREADS && JWX * JWZ <= PUSH_THREADS, "one column per thread");
+};
 // Second-order shapes (three-dimensional grids): the 8 x 8 x 4 tile with a
 // 13 x 13 x 9 field window (36.5 KB) and the same current window, no queue:
 // 73 KB, two workgroups per CU.
@@ -115,6 +143,7 @@ struct TileInfo {
     int lg[3];      // log2 of the tile sides
     int ntiles;
     int slab;       // 1: TileSlab, 0: TileCube
+    int fold;       // 1: slab with a periodic y of one or two cells (the push takes TileFold)
     long long NK;   // ntiles * TC sort keys
 };
 

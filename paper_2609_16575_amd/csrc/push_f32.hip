@@ -175,6 +175,40 @@ __device__ __forceinline__ void lds_add_segment(unsigned long long *sJ, int base
         atomicAdd(sJ + base + edge_off<TL>(q), (unsigned long long)to_fixed(v[q], mult[q >> 2]));
 }
 
+// The same into a folded window (TileFold): jb, the index of the particle's
+// cell, holds the row in bit 0; j1 is the cell's next node row along y.
+template <class TL>
+__device__ __forceinline__ void lds_add_segment_fold(unsigned long long *sJ, int jb, int j1,
+                                                     const float W[3], const float D[3], float wq,
+                                                     const double mult[3]) {
+    const float amp[3] = {wq, wq, wq};
+    float v[12];
+    segment_weights(W, D, amp, v);
+#pragma unroll
+    for (int q = 0; q < 12; ++q) {
+        const int c = q >> 2, o1 = q & 1, o2 = (q >> 1) & 1;
+        // J_x (oy,oz); J_y (oz,ox); J_z (ox,oy)
+        const int oy = c == 0 ? o1 : (c == 2 ? o2 : 0);
+        const int ox = c == 1 ? o2 : (c == 2 ? o1 : 0), oz = c == 0 ? o2 : (c == 1 ? o1 : 0);
+        atomicAdd(sJ + (oy ? j1 : jb) + c * TL::JW3 + 2 * ox + 2 * TL::JWX * oz,
+                  (unsigned long long)to_fixed(v[q], mult[c]));
+    }
+}
+
+// Trilinear value from a folded field window of (row 0, row 1) pairs at pb,
+// the corner of lowest x and z: sel, whether the lower y corner is row 1; fys,
+// the y fraction, negated when it is (lerp(a, b, f) with a and b exchanged).
+// The operations are those of tri_lds_at.
+template <class TL>
+__device__ __forceinline__ float tri_fold_at(const char *pb, float fx, bool sel, float fys,
+                                             float fz) {
+    const float2 *p = (const float2 *)pb;
+    const float2 a = p[0], b = p[1], c = p[TL::FWX], d = p[TL::FWX + 1];
+    const float p0 = lerpf(a.x, b.x, fx), p1 = lerpf(a.y, b.y, fx);
+    const float q0 = lerpf(c.x, d.x, fx), q1 = lerpf(c.y, d.y, fx);
+    return lerpf(fmaf(fys, p1 - p0, sel ? p1 : p0), fmaf(fys, q1 - q0, sel ? q1 : q0), fz);
+}
+
 typedef float __attribute__((address_space(1))) gfloat;
 typedef uint32_t __attribute__((address_space(1))) guint;
 
@@ -225,6 +259,20 @@ __device__ __forceinline__ void second_segment(const float o[3], const float dx[
     }
 }
 
+// Second segment of a crossing particle of window cell jb into the cell + dc
+template <class TL>
+__device__ __forceinline__ void add_second(unsigned long long *sJ, int jb, const int dc[3],
+                                           int yflip, const float WB[3], const float DB[3],
+                                           float wq, const double mult[3]) {
+    if constexpr (TL::FOLD) {
+        const int j2 = (jb + 2 * (dc[0] + TL::JWX * dc[2])) ^ (dc[1] != 0 ? yflip : 0);
+        lds_add_segment_fold<TL>(sJ, j2, j2 ^ yflip, WB, DB, wq, mult);
+    } else {
+        lds_add_segment<TL>(sJ, jb + dc[0] + TL::JWX * (dc[1] + TL::JWY * dc[2]), WB, DB, wq,
+                            mult);
+    }
+}
+
 // Marks particle (s, p) for k_push_fallback when `outside`: a bit in the
 // out-of-window mask, set by an atomic whose result is not waited for (a
 // list slot claimed with a returning atomic made every wave with such a
@@ -248,8 +296,9 @@ struct SegQueue {
 
 // Per-tile constants of the particle loop.
 struct TileCtx {
-    int wo[3];          // global cell of window point 0 per axis
+    int wo[3];          // global cell of window point 0 per axis (a folded y: 0)
     uint32_t wo_pack;   // the same, packed (interior tiles only)
+    int yflip;          // folded y: 1 with two rows, 0 with one
 };
 
 // One species of one tile: P consecutive particles per thread (one access
@@ -332,13 +381,13 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
                 lz = (int)(cl >> 22);
             } else {
                 lx = local_axis(g, 0, cell_i(c), T.wo[0]);
-                ly = local_axis(g, 1, cell_j(c), T.wo[1]);
+                ly = TL::FOLD ? cell_j(c) : local_axis(g, 1, cell_j(c), T.wo[1]);
                 lz = local_axis(g, 2, cell_k(c), T.wo[2]);
             }
             // drifted out of the tile window since the last sort: listed for
             // k_push_fallback
             const bool outside = !((unsigned)(lx - 1) < (unsigned)LHI_X &&
-                                   (unsigned)(ly - 1) < (unsigned)LHI_Y &&
+                                   (TL::FOLD || (unsigned)(ly - 1) < (unsigned)LHI_Y) &&
                                    (unsigned)(lz - 1) < (unsigned)LHI_Z);
             if (list_fallback(A, outside, s, p, nfb)) continue;
             const float ox = b.ox[k], oy = b.oy[k], oz = b.oz[k];
@@ -349,20 +398,32 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
                         fz = oz + (sz ? 0.5f : -0.5f);
             // byte addresses of the six corners: the node's, less a row, plane or
             // point where the component is half-staggered
-            const uint32_t nb = (uint32_t)lx * 4u + (uint32_t)ly * (FWX * 4u) +
-                                (uint32_t)lz * (FWX * FWY * 4u);
-            const uint32_t hx = sx ? -4u : 0u, hy = sy ? -(FWX * 4u) : 0u,
-                           hz = sz ? -(FWX * FWY * 4u) : 0u;
+            constexpr uint32_t SX = TL::FOLD ? 8u : 4u, SY = TL::FOLD ? 0u : FWX * 4u,
+                               SZ = TL::FOLD ? FWX * 8u : FWX * FWY * 4u;
+            const uint32_t nb = (uint32_t)lx * SX + (uint32_t)ly * SY + (uint32_t)lz * SZ;
+            const uint32_t hx = sx ? -SX : 0u, hy = sy ? -SY : 0u, hz = sz ? -SZ : 0u;
             const uint32_t a0 = nb + hx + sFo[0], a1 = nb + hy + sFo[1], a2 = nb + hz + sFo[2];
             const uint32_t a3 = a1 + hz + sFo[3], a4 = a0 + hz + sFo[4], a5 = a0 + hy + sFo[5];
             const char *sFb = (const char *)sF;
             float Ep[3], Bp[3];
-            Ep[0] = tri_lds_at<TL>(sFb + a0, fx, oy, oz);
-            Ep[1] = tri_lds_at<TL>(sFb + a1, ox, fy, oz);
-            Ep[2] = tri_lds_at<TL>(sFb + a2, ox, oy, fz);
-            Bp[0] = tri_lds_at<TL>(sFb + a3, ox, fy, fz);
-            Bp[1] = tri_lds_at<TL>(sFb + a4, fx, oy, fz);
-            Bp[2] = tri_lds_at<TL>(sFb + a5, fx, fy, oz);
+            if constexpr (TL::FOLD) {
+                // the lower row of the node and of the half-cell points
+                const bool rn = ly != 0, rh = (ly ^ (sy ? T.yflip : 0)) != 0;
+                const float yn = rn ? -oy : oy, yh = rh ? -fy : fy;
+                Ep[0] = tri_fold_at<TL>(sFb + a0, fx, rn, yn, oz);
+                Ep[1] = tri_fold_at<TL>(sFb + a1, ox, rh, yh, oz);
+                Ep[2] = tri_fold_at<TL>(sFb + a2, ox, rn, yn, fz);
+                Bp[0] = tri_fold_at<TL>(sFb + a3, ox, rh, yh, fz);
+                Bp[1] = tri_fold_at<TL>(sFb + a4, fx, rn, yn, fz);
+                Bp[2] = tri_fold_at<TL>(sFb + a5, fx, rh, yh, oz);
+            } else {
+                Ep[0] = tri_lds_at<TL>(sFb + a0, fx, oy, oz);
+                Ep[1] = tri_lds_at<TL>(sFb + a1, ox, fy, oz);
+                Ep[2] = tri_lds_at<TL>(sFb + a2, ox, oy, fz);
+                Bp[0] = tri_lds_at<TL>(sFb + a3, ox, fy, fz);
+                Bp[1] = tri_lds_at<TL>(sFb + a4, fx, oy, fz);
+                Bp[2] = tri_lds_at<TL>(sFb + a5, fx, fy, oz);
+            }
             float ux = b.ux[k], uy = b.uy[k], uz = b.uz[k], gam;
             const float ig = boris_f32(ux, uy, uz, Ep, Bp, r, r_lo, gam);
             const float o[3] = {ox, oy, oz};
@@ -406,7 +467,7 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
             const float pk = fmaf(fl[2], 4194304.f, fmaf(fl[1], 2048.f, fl[0]));
             const bool cross = pk != 0.f;
             const unsigned long long m = __ballot(cross);
-            const int jb = lx + JWX * (ly + JWY * lz);
+            const int jb = TL::FOLD ? 2 * (lx + JWX * lz) + ly : lx + JWX * (ly + JWY * lz);
             // first segment: the whole move inside the cell, or from the start
             // to the relay point (Sec. 2.5, ZigZag)
             float WA[3], DA[3] = {dx[0], dx[1], dx[2]};
@@ -418,7 +479,9 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a) WA[a] = fmaf(0.5f, DA[a], o[a]);
-            lds_add_segment<TL>(sJ, jb, WA, DA, wq, mult);
+            if constexpr (TL::FOLD)
+                lds_add_segment_fold<TL>(sJ, jb, jb ^ T.yflip, WA, DA, wq, mult);
+            else lds_add_segment<TL>(sJ, jb, WA, DA, wq, mult);
             // second segment of the crossing particles: from the relay point
             // to the end, in the cell + dc; queued as the move itself (the
             // segment is worked out when the queue is deposited)
@@ -445,13 +508,16 @@ __device__ __forceinline__ void push_species(const FusedArgs &A, const DevSpecie
                 if (now) {
                     float WB[3], DB[3];
                     second_segment(o, dx, dc, WB, DB);
-                    lds_add_segment<TL>(sJ, jb + dc[0] + JWX * (dc[1] + JWY * dc[2]), WB, DB, wq,
-                                        mult);
+                    add_second<TL>(sJ, jb, dc, T.yflip, WB, DB, wq, mult);
                 }
             }
             if constexpr (INTERIOR) {
-                // inside the grid on every axis: a step of the packed index
-                b.c[k] = c + (uint32_t)(int)pk;
+                // inside the grid on every axis: a step of the packed index (a
+                // folded y wraps instead)
+                if constexpr (TL::FOLD)
+                    b.c[k] = (c + (uint32_t)(int)fmaf(fl[2], 4194304.f, fl[0])) ^
+                             (fl[1] != 0.f ? (uint32_t)T.yflip << 11 : 0u);
+                else b.c[k] = c + (uint32_t)(int)pk;
             } else {
                 int ni, nj, nk;
                 const int in = (int)new_cell(g, 0, cell_i(c), (int)fl[0], ni) &
@@ -710,8 +776,9 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     constexpr int JWX = TL::JWX, JWY = TL::JWY, JWZ = TL::JWZ, JW3 = TL::JW3;
     constexpr int ROWS = TL::ROWS;
     constexpr int QN = TL::QCAP > 0 ? 2 * TL::QCAP : 1;
-    __shared__ float sF[6 * FW3];
-    __shared__ __align__(16) unsigned long long sJ[3 * JW3 + 1];
+    __shared__ __align__(8) float sF[6 * FW3];
+    constexpr int JALL = TL::REP * TL::JREP;
+    __shared__ __align__(16) unsigned long long sJ[(JALL + 1) / 2 * 2];
     __shared__ float4 sQ[QN];
     __shared__ unsigned sQn;
     __shared__ unsigned sNfb;  // particles of this tile marked for k_push_fallback
@@ -740,10 +807,11 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     const int tyz = tile / A.ti.nt[0];
     const int ty = tyz % A.ti.nt[1], tz = tyz / A.ti.nt[1];
     TileCtx T;
-    T.wo[0] = tx * TX - MARGIN - 1;
-    T.wo[1] = ty * TY - MARGIN - 1;
-    T.wo[2] = tz * TZ - MARGIN - 1;
-    const int JW[3] = {JWX, JWY, JWZ};
+    T.wo[0] = tx * TX - TL::MGX - 1;
+    T.wo[1] = TL::FOLD ? 0 : ty * TY - MARGIN - 1;
+    T.wo[2] = tz * TZ - TL::MGZ - 1;
+    T.yflip = TL::FOLD ? g.n[1] - 1 : 0;
+    const int JW[3] = {JWX, TL::FOLD ? 0 : JWY, JWZ};
     bool interior = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) interior = interior && T.wo[a] >= 0 && T.wo[a] + JW[a] <= g.n[a];
@@ -768,7 +836,23 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
         }
     }
     __syncthreads();
-    {
+    if constexpr (TL::FOLD) {
+        // one (x, z) column of both rows per thread
+        const int lz = tid / FWX, lx = tid - lz * FWX;
+        if (tid < FWX * FWZ) {
+            const int gx = sG[0][lx], gz = sG[2][lz];
+            const int r1 = T.yflip ? g.ext[0] : 0;
+            float2 tmp[6];
+#pragma unroll
+            for (int c = 0; c < 6; ++c) {
+                const float *src = c < 3 ? A.E[c] : A.Bb[c - 3];
+                tmp[c] = (gx | gz) >= 0 ? make_float2(src[gx + gz], src[gx + gz + r1])
+                                        : make_float2(0.f, 0.f);
+            }
+#pragma unroll
+            for (int c = 0; c < 6; ++c) *(float2 *)(sF + c * FW3 + 2 * tid) = tmp[c];
+        }
+    } else {
         // a thread owns one (x, y) column of the window at every ZG-th z and
         // the same points of all six components: their global offsets are
         // worked out once, and every load is issued before any is waited on
@@ -802,19 +886,20 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     {
         // 16-byte stores (the window has an even number of words with its pad)
         uint4 *z4 = (uint4 *)sJ;
-        for (int e = tid; e < (3 * JW3 + 1) / 2; e += PUSH_THREADS) z4[e] = make_uint4(0u, 0u, 0u, 0u);
+        for (int e = tid; e < (JALL + 1) / 2; e += PUSH_THREADS) z4[e] = make_uint4(0u, 0u, 0u, 0u);
     }
     __syncthreads();
 
     uint32_t fbits = 0;
     unsigned nfb = 0;
     const SegQueue Q = {sQ, &sQn};
+    unsigned long long *sJw = sJ + (tid % TL::REP) * TL::JREP;  // this lane's copy
     if constexpr (ORDER == 2)
-        push_tile2<TL>(A, T, tile, sF, sJ, fbits, nfb);
+        push_tile2<TL>(A, T, tile, sF, sJw, fbits, nfb);
     else if (interior)
-        push_tile<TL, true>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJ, Q, fbits, nfb);
+        push_tile<TL, true>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
     else
-        push_tile<TL, false>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJ, Q, fbits, nfb);
+        push_tile<TL, false>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
     // counts and fault bits gathered per workgroup in LDS: a global atomic per
     // thread on these single words serialised the whole step once many
     // particles were out of their windows
@@ -835,8 +920,7 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
             const float o[3] = {a.x, a.y, a.z}, dx[3] = {bq.x, bq.y, bq.z};
             float WB[3], DB[3];
             second_segment(o, dx, dc, WB, DB);
-            lds_add_segment<TL>(sJ, (int)(code & 0x7FFu) + dc[0] + JWX * (dc[1] + JWY * dc[2]),
-                                WB, DB, bq.w, mult);
+            add_second<TL>(sJw, (int)(code & 0x7FFu), dc, T.yflip, WB, DB, bq.w, mult);
         }
         __syncthreads();
     }
@@ -844,7 +928,23 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     // only: integer adds, so the sums do not depend on their order); a thread
     // owns one (x, y) column of the window at every ZG-th z, the same points
     // of the three components
-    {
+    if constexpr (TL::FOLD) {
+        const int lz = tid / JWX, lx = tid - lz * JWX;
+        if (tid < JWX * JWZ && (sG[0][lx] | sG[2][lz]) >= 0) {
+            const int gxz = sG[0][lx] + sG[2][lz];
+            const bool skip[3] = {sPad[0][lx] != 0, false, sPad[2][lz] != 0};
+            for (int row = 0; row < g.n[1]; ++row)
+#pragma unroll
+                for (int comp = 0; comp < 3; ++comp) {
+                    unsigned long long fx = 0;
+#pragma unroll
+                    for (int k = 0; k < TL::REP; ++k)
+                        fx += sJ[k * TL::JREP + comp * JW3 + 2 * tid + row];
+                    if (fx == 0 || skip[comp]) continue;
+                    atomicAdd(A.Jf[comp] + gxz + row * g.ext[0], fx);
+                }
+        }
+    } else {
         constexpr int NCOL = JWX * JWY, ZG = PUSH_THREADS / NCOL, NZ = (JWZ + ZG - 1) / ZG;
         const int col = tid % NCOL, zg = tid / NCOL;
         if (zg < ZG) {
@@ -1783,8 +1883,11 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
         // list can hold most tiles
         hipLaunchKernelGGL(g.shape_order == 2 ? k_push_fallback<2> : k_push_fallback<1>,
                            dim3(2048), dim3(256), 0, s, A);
+    else if (ti.fold)
+        launch_fused<TileFold, 1>(A, nb, s, ev_start, ev_stop);
     else if (ti.slab)
         launch_fused<TileSlab, 1>(A, nb, s, ev_start, ev_stop);  // order 2 is refused on slab grids
+
     else if (g.shape_order == 2)
         launch_fused<TileCube2, 2>(A, nb, s, ev_start, ev_stop);
     else
