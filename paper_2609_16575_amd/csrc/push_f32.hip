@@ -982,15 +982,33 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     }
 }
 
+// Index of the k-th (from 0) set bit of w, which has more than k
+__device__ __forceinline__ int nth_bit(uint32_t w, int k) {
+    int pos = 0;
+#pragma unroll
+    for (int h = 16; h > 0; h >>= 1) {
+        const int c = __popc((w >> pos) & ((1u << h) - 1u));
+        if (k >= c) {
+            k -= c;
+            pos += h;
+        }
+    }
+    return pos;
+}
+
 // Out-of-window particles of this step, whole particle through global memory
-// (gather from E and Bbar, global atomic deposit).  A thread takes one mask
+// (gather from E and Bbar, global atomic deposit).  A lane takes one mask
 // word of a listed tile's slot range (flat over the listed tiles, so that
 // all of them are scanned at once rather than one after another per
 // workgroup), keeps the bits inside the range (a word can straddle two
-// tiles), clears them and pushes their particles.  The counts and the tile
-// list are cleared by the next step's Faraday kernel (a ticket for the last
-// workgroup, a returning atomic of every workgroup on one word, cost more
-// than the pass itself in most steps).
+// tiles) and clears them; the wave then spreads the particles of its 64 words
+// over its lanes, one particle each.  Bound by the latency of a particle's
+// chain of gathers, so what counts is how many are in flight: with each lane
+// walking its own word's bits, the wakefield run's pass (particles half a
+// cell per step, whole words marked in a few tiles) had two waves per CU at
+// work: 210 us per step on average, 57 us now.  The counts and the tile list are cleared by the next step's
+// Faraday kernel (a ticket for the last workgroup, a returning atomic of every
+// workgroup on one word, cost more than the pass itself in most steps).
 constexpr int FB_WPT = 160;  // words per item stride: the 129 of a 4096-particle tile
 template <int ORDER>
 __global__ __launch_bounds__(256) void k_push_fallback(FusedArgs A) {
@@ -1000,48 +1018,74 @@ __global__ __launch_bounds__(256) void k_push_fallback(FusedArgs A) {
         __threadfence_system();
     }
     const unsigned ntl = *(volatile unsigned *)(A.fb_count + 2);
+    const int lane = (int)(threadIdx.x & 63);
     uint32_t fbits = 0;
     // items (listed tile, word j < FB_WPT); a tile with more words takes
-    // them FB_WPT apart
+    // them FB_WPT apart.  A wave's items are consecutive and every lane stays
+    // in the loop until the last of them is done.
     const long long items = (long long)ntl * FB_WPT;
-    for (long long it = blockIdx.x * (long long)blockDim.x + threadIdx.x; it < items;
-         it += (long long)gridDim.x * blockDim.x)
-    for (int s = 0; s < A.nsp; ++s) {
-        const int j = (int)(it % FB_WPT);
-        const int tile = A.fb_tiles[it / FB_WPT];
-        const DevSpecies &D = A.tbl[s];
-        const SpeciesP &S = D.p[(A.cur_mask >> s) & 1u];
-        const SpeciesP &Wr = D.p[(A.wr_mask >> s) & 1u];
-        const int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
-        if (beg >= end) continue;
-        const int w0 = beg >> 5, w1 = (end - 1) >> 5;
-        for (int w = w0 + j; w <= w1; w += FB_WPT) {
-        const int lo = w == w0 ? (beg & 31) : 0, hi = w == w1 ? ((end - 1) & 31) : 31;
-        const uint32_t range = (0xffffffffu >> (31 - hi)) & (0xffffffffu << lo);
-        uint32_t *mw = A.fb_mask + (long long)s * A.mask_words + w;
-        uint32_t bits = *mw & range;
-        if (!bits) continue;
-        atomicAnd(mw, ~bits);
-        const int p0 = w * 32;
-        while (bits) {
-            const int p = p0 + __builtin_ctz(bits);
-            bits &= bits - 1u;
-            uint32_t c = S.cell[p];
-            float ox = ((float *)S.pos[0])[p], oy = ((float *)S.pos[1])[p],
-                  oz = ((float *)S.pos[2])[p];
-            float ux = ((float *)S.u[0])[p], uy = ((float *)S.u[1])[p], uz = ((float *)S.u[2])[p];
-            const float wq = (S.per_particle_w && S.w) ? ((const float *)S.w)[p] : 1.f;
-            particle_global<ORDER>(A, D, c, ox, oy, oz, ux, uy, uz, wq, fbits);
-            Wr.cell[p] = c;
-            ((float *)Wr.pos[0])[p] = ox;
-            ((float *)Wr.pos[1])[p] = oy;
-            ((float *)Wr.pos[2])[p] = oz;
-            ((float *)Wr.u[0])[p] = ux;
-            ((float *)Wr.u[1])[p] = uy;
-            ((float *)Wr.u[2])[p] = uz;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long it0 = blockIdx.x * (long long)blockDim.x + (threadIdx.x & ~63u); it0 < items;
+         it0 += stride)
+        for (int s = 0; s < A.nsp; ++s) {
+            const long long it = it0 + lane;
+            const DevSpecies &D = A.tbl[s];
+            const SpeciesP &S = D.p[(A.cur_mask >> s) & 1u];
+            const SpeciesP &Wr = D.p[(A.wr_mask >> s) & 1u];
+            int beg = 0, end = 0;
+            if (it < items) {
+                const int tile = A.fb_tiles[it / FB_WPT];
+                beg = S.tile_off[tile];
+                end = S.tile_off[tile + 1];
+            }
+            const int w0 = beg >> 5, w1 = beg < end ? (end - 1) >> 5 : -1;
+            for (int w = w0 + (int)(it % FB_WPT); __ballot(w <= w1) != 0ull; w += FB_WPT) {
+                uint32_t bits = 0;
+                if (w <= w1) {
+                    const int lo = w == w0 ? (beg & 31) : 0, hi = w == w1 ? ((end - 1) & 31) : 31;
+                    const uint32_t range = (0xffffffffu >> (31 - hi)) & (0xffffffffu << lo);
+                    uint32_t *mw = A.fb_mask + (long long)s * A.mask_words + w;
+                    bits = *mw & range;
+                    if (bits) atomicAnd(mw, ~bits);
+                }
+                if (__ballot(bits != 0u) == 0ull) continue;
+                // inclusive prefix of the words' particle counts over the wave
+                int sum = __popc(bits);
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int y = __shfl_up(sum, o, 64);
+                    if (lane >= o) sum += y;
+                }
+                const int total = __shfl(sum, 63, 64);
+                for (int base = 0; base < total; base += 64) {
+                    // this lane's particle: the first word whose prefix exceeds q
+                    const int q = base + lane;
+                    int src = 0;
+#pragma unroll
+                    for (int h = 32; h > 0; h >>= 1)
+                        if (__shfl(sum, src + h - 1, 64) <= q) src += h;
+                    src = min(src, 63);
+                    const uint32_t wb = (uint32_t)__shfl((int)bits, src, 64);
+                    const int ws = __shfl(w, src, 64);
+                    const int before = __shfl(sum, src, 64) - __popc(wb);
+                    if (q >= total) continue;
+                    const int p = ws * 32 + nth_bit(wb, q - before);
+                    uint32_t c = S.cell[p];
+                    float ox = ((float *)S.pos[0])[p], oy = ((float *)S.pos[1])[p],
+                          oz = ((float *)S.pos[2])[p];
+                    float ux = ((float *)S.u[0])[p], uy = ((float *)S.u[1])[p],
+                          uz = ((float *)S.u[2])[p];
+                    const float wq = (S.per_particle_w && S.w) ? ((const float *)S.w)[p] : 1.f;
+                    particle_global<ORDER>(A, D, c, ox, oy, oz, ux, uy, uz, wq, fbits);
+                    Wr.cell[p] = c;
+                    ((float *)Wr.pos[0])[p] = ox;
+                    ((float *)Wr.pos[1])[p] = oy;
+                    ((float *)Wr.pos[2])[p] = oz;
+                    ((float *)Wr.u[0])[p] = ux;
+                    ((float *)Wr.u[1])[p] = uy;
+                    ((float *)Wr.u[2])[p] = uz;
+                }
+            }
         }
-        }
-    }
     if (fbits) atomicOr(A.fault, fbits);
 }
 
