@@ -30,6 +30,8 @@
 // Derivatives are taken inside the current piece of each piecewise map (the
 // relay-point branch and the interpolation corners are frozen).  Position
 // adjoints are per unit length (global coordinates).
+#include <algorithm>
+
 #include "internal.hpp"
 #include "pic_math.hpp"
 
@@ -47,6 +49,8 @@ typedef uint32_t vuA __attribute__((ext_vector_type(APPT)));
 typedef float vfS __attribute__((ext_vector_type(SPPT)));
 typedef uint32_t vuS __attribute__((ext_vector_type(SPPT)));
 constexpr int NO_EXP = -100000;
+constexpr int ADJ_SLOTS = 768;     // workgroups of pass 1 that fill the chip (3 per CU)
+constexpr int SCAT_SLOTS = 256;    // and of pass 2, whose windows are flushed once each
 
 __device__ __forceinline__ int pwrap(int x, int n) {
     int m = x % n;
@@ -176,7 +180,9 @@ struct AdjArgs {
     uint32_t *fb_mask;   // bit p: slot p of this species is outside its tile window
     unsigned *fb_count;  // marked particles
     float *l6[6];        // per slot: lam_Ep, lam_Bp from pass 1 (scratch)
-    int *tile_exp;       // per tile: exponent bound of its lam_Ep, lam_Bp
+    int *tile_exp;       // per workgroup of pass 1: exponent bound of its lam_Ep, lam_Bp
+    TileSplit split;     // workgroups per tile of the pass
+    int exps;            // exponents per tile (the split of pass 1)
 };
 
 struct AdjSpecies {
@@ -381,11 +387,14 @@ __device__ __forceinline__ void window_rows(const GridP &g, const int wo[3],
     }
 }
 
+// the workgroup's tile and its slice of it (split workgroups per tile)
 template <class TL>
-__device__ __forceinline__ int tile_of_block(const TileInfo &ti, int wo[3]) {
+__device__ __forceinline__ int tile_of_block(const TileInfo &ti, int split, int wo[3], int &part) {
     constexpr int TX = TL::TX, TY = TL::TY, TZ = TL::TZ;
     const int nb8 = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
+    const int id = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
+    const int tile = id / split;
+    part = id - tile * split;
     const int tx = tile % ti.nt[0];
     const int tyz = tile / ti.nt[0];
     const int ty = tyz % ti.nt[1], tz = tyz / ti.nt[1];
@@ -411,11 +420,15 @@ __global__ __launch_bounds__(ADJ_THREADS, 3) void k_adj_particles(AdjArgs A, Adj
     __shared__ unsigned sNfb;
 
     const GridP &g = A.g;
-    int wo[3];
-    const int tile = tile_of_block<TL>(A.ti, wo);
+    int wo[3], part;
+    const int tile = tile_of_block<TL>(A.ti, A.split.n, wo, part);
     if (tile >= A.ti.ntiles) return;
-    const int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
-    if (beg >= end) return;
+    int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
+    A.split.slice(part, beg, end);
+    if (beg >= end) {  // an empty slice of a tile that has particles
+        if (threadIdx.x == 0) A.tile_exp[tile * A.split.n + part] = NO_EXP;
+        return;
+    }
     const int tid = threadIdx.x;
     window_rows<TL>(g, wo, sG);
     if (tid == 0) {
@@ -569,7 +582,7 @@ __global__ __launch_bounds__(ADJ_THREADS, 3) void k_adj_particles(AdjArgs A, Adj
     if (nfb) atomicAdd(&sNfb, nfb);
     __syncthreads();
     if (tid == 0) {
-        A.tile_exp[tile] = sE;
+        A.tile_exp[tile * A.split.n + part] = sE;
         if (sNfb) atomicAdd(A.fb_count, sNfb);
     }
 }
@@ -590,12 +603,14 @@ __global__ __launch_bounds__(SCAT_THREADS) void k_adj_scatter(AdjArgs A, AdjSpec
     __shared__ int sG[3][TL::ROWS];
 
     const GridP &g = A.g;
-    int wo[3];
-    const int tile = tile_of_block<TL>(A.ti, wo);
+    int wo[3], part;
+    const int tile = tile_of_block<TL>(A.ti, A.split.n, wo, part);
     if (tile >= A.ti.ntiles) return;
-    const int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
+    int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
+    A.split.slice(part, beg, end);
     if (beg >= end) return;
-    const int et = A.tile_exp[tile];
+    int et = A.tile_exp[tile * A.exps];
+    for (int k = 1; k < A.exps; ++k) et = max(et, A.tile_exp[tile * A.exps + k]);
     if (et == NO_EXP) return;
     const int ee = max(et, -96);  // keeps the scale a finite float
     const int tid = threadIdx.x;
@@ -770,10 +785,12 @@ __global__ void k_sort_vjp_scatter(Lam6 lam, Lam6 tmp, const int32_t *perm, long
 }
 
 // Six arrays of n floats cleared in one launch: 16-byte stores when every
-// array is 16-byte aligned (vec), single floats otherwise
-__global__ void k_zero6(Lam6 z, long long n, int vec) {
+// array is 16-byte aligned (vec), single floats otherwise; and the first
+// species' count of marked particles
+__global__ void k_zero6(Lam6 z, long long n, int vec, unsigned *count) {
     const long long stride = (long long)gridDim.x * blockDim.x;
     const long long t0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (t0 == 0) *count = 0u;
     if (!vec) {
         for (long long i = t0; i < n; i += stride)
 #pragma unroll
@@ -806,7 +823,8 @@ void launch_step_vjp(const GridP &g, const TileInfo &ti, float *const E[3], floa
             z.p[3 + a] = lBb[a];
         }
         for (int a = 0; a < 6; ++a) vec &= ((uintptr_t)z.p[a] & 15u) == 0 ? 1 : 0;
-        hipLaunchKernelGGL(k_zero6, dim3(2048), dim3(256), 0, s, z, g.V, vec);
+        const long long nb = std::min(2048LL, (g.V + 1023) / 1024);
+        hipLaunchKernelGGL(k_zero6, dim3((unsigned)nb), dim3(256), 0, s, z, g.V, vec, fb_count);
     }
     AdjArgs A;
     A.g = g;
@@ -825,10 +843,14 @@ void launch_step_vjp(const GridP &g, const TileInfo &ti, float *const E[3], floa
     A.fb_count = fb_count;
     A.tile_exp = tile_exp;
     const double dV = g.d[0] * g.d[1] * g.d[2];
-    // one workgroup per tile; a multiple of 8 for the XCD-contiguous tile map
-    const unsigned nblocks = (unsigned)(8 * ((ti.ntiles + 7) / 8));
     for (int i = 0; i < nsp; ++i) {
         if (sp[i].capacity <= 0) continue;
+        // a multiple of 8 for the XCD-contiguous tile map
+        const auto blocks = [&](int split) { return dim3(8 * ((ti.ntiles * split + 7) / 8)); };
+        const long long avg = sp[i].capacity / ti.ntiles;
+        const int split1 = tile_split(ti.ntiles, avg, ADJ_SLOTS, 256);
+        const int split2 = tile_split(ti.ntiles, avg, SCAT_SLOTS, 512);
+        A.split.n = A.exps = split1;
         AdjSpecies S;
         S.cell = sp[i].cell;
         for (int a = 0; a < 3; ++a) {
@@ -843,20 +865,22 @@ void launch_step_vjp(const GridP &g, const TileInfo &ti, float *const E[3], floa
         const double w = sp[i].per_particle_w ? 1.0 : sp[i].w_species;
         for (int a = 0; a < 3; ++a) split_f32(sp[i].q * w * g.d[a] / (g.dt * dV), S.qc[a], S.qc_lo[a]);
         for (int q = 0; q < 6; ++q) A.l6[q] = l6[i][q];
-        launch_fill_i32((int32_t *)fb_count, 1, 0, s);
+        if (i > 0) launch_fill_i32((int32_t *)fb_count, 1, 0, s);
         if (ti.slab)
-            hipLaunchKernelGGL(k_adj_particles<TileSlab>, dim3(nblocks), dim3(ADJ_THREADS), 0, s,
+            hipLaunchKernelGGL(k_adj_particles<TileSlab>, blocks(split1), dim3(ADJ_THREADS), 0, s,
                                A, S);
         else
-            hipLaunchKernelGGL(k_adj_particles<TileCube>, dim3(nblocks), dim3(ADJ_THREADS), 0, s,
+            hipLaunchKernelGGL(k_adj_particles<TileCube>, blocks(split1), dim3(ADJ_THREADS), 0, s,
                                A, S);
-        hipLaunchKernelGGL(k_adj_fallback, dim3(1024), dim3(256), 0, s, A, S,
-                           (long long)((sp[i].capacity + 31) / 32));
+        const long long words = (sp[i].capacity + 31) / 32;
+        hipLaunchKernelGGL(k_adj_fallback, dim3((unsigned)std::min(1024LL, (words + 255) / 256)),
+                           dim3(256), 0, s, A, S, words);
+        A.split.n = split2;
         if (ti.slab)
-            hipLaunchKernelGGL(k_adj_scatter<TileSlab>, dim3(nblocks), dim3(SCAT_THREADS), 0, s,
+            hipLaunchKernelGGL(k_adj_scatter<TileSlab>, blocks(split2), dim3(SCAT_THREADS), 0, s,
                                A, S);
         else
-            hipLaunchKernelGGL(k_adj_scatter<TileCube>, dim3(nblocks), dim3(SCAT_THREADS), 0, s,
+            hipLaunchKernelGGL(k_adj_scatter<TileCube>, blocks(split2), dim3(SCAT_THREADS), 0, s,
                                A, S);
     }
     const dim3 grid((g.n[0] + 63) / 64, (g.n[1] + 3) / 4, g.n[2]);

@@ -385,12 +385,21 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
                 (void)hipEventCreate(&tp.a);
                 (void)hipEventCreate(&tp.b);
             }
+            // A workgroup per CU: more only add flushes of the same windows.  32^3
+            // with 16 per cell (128 tiles): 30 us per launch unsplit, 22 with two
+            // workgroups per tile, 31 with four; 16^3 with 8 per cell (16 tiles): 16
+            // us unsplit, 14 with four.  The list of marked tiles of a split grid
+            // takes the sort's counters (256 words per tile, free between sorts).
+            long long slots = 0;
+            for (int i = 0; i < s->nsp; ++i) slots += s->sp[i].host_count;
+            const int split = tile_split(s->ti.ntiles, slots / s->ti.ntiles, 256, 512);
             for (int pass = 0; pass < 2; ++pass)
                 launch_push_fused(s->g, s->ti, (float *const *)E, (float *const *)Bb,
                                   s->jfix, tbl, s->nsp, rmask, wmask, s->fault,
-                                  s->fallback, s->fb_mask, s->mask_words, s->fb_tiles,
+                                  s->fallback, s->fb_mask, s->mask_words,
+                                  split > 1 ? s->counts : s->fb_tiles,
                                   s->fb_count, s->jscale,
-                                  pass == 1, s->stream, pass == 0 ? tp.a : nullptr,
+                                  pass == 1, split, s->stream, pass == 0 ? tp.a : nullptr,
                                   pass == 0 ? tp.b : nullptr, pass == 1 ? publish : nullptr);
             if (s->timing) s->events.push_back(tp);
         }

@@ -147,6 +147,31 @@ struct TileInfo {
     long long NK;   // ntiles * TC sort keys
 };
 
+// Small grids: `split` workgroups share a tile, each with its own windows and a
+// slice of every species' particles (the windows' sums are integers or have
+// exponents of their own, so nothing depends on the split).  Slice `part` of
+// particles [beg, end), cut at multiples of four slots.
+struct TileSplit {
+    int n = 1;
+    __device__ void slice(int part, int &beg, int &end) const {
+        if (n == 1) return;
+        const int b = beg, len = end - beg;
+        const auto cut = [&](int k) {
+            return k == 0 ? b : (k == n ? b + len : max(b, (b + (int)((long long)len * k / n)) & ~3));
+        };
+        beg = cut(part);
+        end = cut(part + 1);
+    }
+};
+// Workgroups per tile for tiles holding `avg` particles on average, when
+// `slots` workgroups fill the chip: enough to fill it, none with fewer than
+// `least` particles, at most 8.
+inline int tile_split(int ntiles, long long avg, int slots, int least) {
+    long long n = slots / (ntiles > 0 ? ntiles : 1);
+    if (n > avg / least) n = avg / least;
+    return (int)(n < 1 ? 1 : (n > 8 ? 8 : n));
+}
+
 __host__ __device__ inline long long sort_key(const TileInfo &t, int i, int j, int k) {
     const int tx = i >> t.lg[0], ty = j >> t.lg[1], tz = k >> t.lg[2];
     const int lx = i - (tx << t.lg[0]), ly = j - (ty << t.lg[1]), lz = k - (tz << t.lg[2]);
@@ -278,15 +303,17 @@ void launch_field_energy(const GridP &g, T *const E[3], T *const B[3], double *p
 // 1/jscale.  fallback_pass = false launches the fused tile
 // kernel, true the follow-up pass over particles that left their tile window;
 // that pass also writes the cumulative out-of-window count to `publish`
-// (device-accessible pinned host memory) when it is not null.
+// (device-accessible pinned host memory) when it is not null.  split:
+// workgroups per tile (tile_split); fb_tiles holds split entries per tile.
 void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
                        float *const Bbar[3], unsigned long long *const Jf[3],
                        const DevSpecies *tbl, int nsp,
                        unsigned cur_mask, unsigned wr_mask, uint32_t *fault, unsigned long long *fallback,
                        uint32_t *fb_mask, long long mask_words, int *fb_tiles,
                        unsigned *fb_count, double jscale,
-                       bool fallback_pass, hipStream_t s, hipEvent_t ev_start = nullptr,
-                       hipEvent_t ev_stop = nullptr, unsigned long long *publish = nullptr);
+                       bool fallback_pass, int split, hipStream_t s,
+                       hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
+                       unsigned long long *publish = nullptr);
 void launch_dry_push_f32(const GridP &g, float *const E[3], float *const Bbar[3],
                          const SpeciesP &sp, double *partial_slot, uint32_t *fault,
                          hipStream_t s);

@@ -58,6 +58,7 @@ struct FusedArgs {
     unsigned *fb_count;            // [0] particles marked this step, [1] unused, [2]
                                    // entries in fb_tiles (cleared by k_faraday)
     unsigned long long *publish;   // host-visible copy of *fallback (k_push_fallback), or null
+    TileSplit split;               // workgroups per tile
 };
 
 // global atomic deposit of one segment's 12 values at cell (ci,cj,ck), in
@@ -299,6 +300,7 @@ struct TileCtx {
     int wo[3];          // global cell of window point 0 per axis (a folded y: 0)
     uint32_t wo_pack;   // the same, packed (interior tiles only)
     int yflip;          // folded y: 1 with two rows, 0 with one
+    int part;           // this workgroup's slice of the tile's particles
 };
 
 // One species of one tile: P consecutive particles per thread (one access
@@ -728,7 +730,7 @@ __device__ __forceinline__ void push_species2(const FusedArgs &A, const DevSpeci
     }
 }
 
-template <class TL>
+template <class TL, bool SPLIT>
 __device__ __forceinline__ void push_tile2(const FusedArgs &A, const TileCtx &T, int tile,
                                            const float *sF, unsigned long long *sJ,
                                            uint32_t &fbits, unsigned &nfb) {
@@ -736,7 +738,8 @@ __device__ __forceinline__ void push_tile2(const FusedArgs &A, const TileCtx &T,
         const DevSpecies &D = A.tbl[s];
         const SpeciesP &S = D.p[(A.cur_mask >> s) & 1u];
         const SpeciesP &Wr = D.p[(A.wr_mask >> s) & 1u];
-        const int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
+        int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
+        if constexpr (SPLIT) A.split.slice(T.part, beg, end);
         if (beg >= end) continue;
         // two particles per thread in dense tiles: four made the 27-point
         // gathers and the EZ deposit spill registers
@@ -749,7 +752,7 @@ __device__ __forceinline__ void push_tile2(const FusedArgs &A, const TileCtx &T,
 
 // Every species of one tile (sparse ones one particle per thread, so that all
 // the workgroup's waves work; dense ones four per thread).
-template <class TL, bool INTERIOR>
+template <class TL, bool INTERIOR, bool SPLIT>
 __device__ __forceinline__ void push_tile(const FusedArgs &A, const TileCtx &T, int tile,
                                           bool sparse0, int beg0, int end0, const Batch<1> &pre1,
                                           const float *sF, unsigned long long *sJ,
@@ -758,7 +761,12 @@ __device__ __forceinline__ void push_tile(const FusedArgs &A, const TileCtx &T, 
         const DevSpecies &D = A.tbl[s];
         const SpeciesP &S = D.p[(A.cur_mask >> s) & 1u];
         const SpeciesP &Wr = D.p[(A.wr_mask >> s) & 1u];
-        const int beg = s == 0 ? beg0 : S.tile_off[tile], end = s == 0 ? end0 : S.tile_off[tile + 1];
+        int beg = beg0, end = end0;
+        if (s > 0) {
+            beg = S.tile_off[tile];
+            end = S.tile_off[tile + 1];
+            if constexpr (SPLIT) A.split.slice(T.part, beg, end);
+        }
         if (beg >= end) continue;
         if (end - beg <= 2 * PUSH_THREADS)
             push_species<TL, 1, INTERIOR>(A, D, S, Wr, beg, end, T, sF, sJ, Q, s, fbits, nfb, pre1,
@@ -769,7 +777,10 @@ __device__ __forceinline__ void push_tile(const FusedArgs &A, const TileCtx &T, 
     }
 }
 
-template <class TL, int ORDER>
+// SPLIT: several workgroups share a tile (small grids); a template argument
+// because the slicing's registers made the unsplit kernel spill (wakefield box
+// 3 % slower).
+template <class TL, int ORDER, bool SPLIT>
 __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     constexpr int TX = TL::TX, TY = TL::TY, TZ = TL::TZ;
     constexpr int FWX = TL::FWX, FWY = TL::FWY, FWZ = TL::FWZ, FW3 = TL::FW3;
@@ -788,8 +799,11 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
 
     const GridP &g = A.g;
     const int nb8 = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
+    const int id = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
+    const int tile = SPLIT ? id / A.split.n : id;
     if (tile >= A.ti.ntiles) return;
+    TileCtx T;
+    T.part = SPLIT ? id - tile * A.split.n : 0;
     int total = 0;
     for (int s = 0; s < A.nsp; ++s)
         total += A.tbl[s].p[0].tile_off[tile + 1] - A.tbl[s].p[0].tile_off[tile];
@@ -798,7 +812,8 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     // a sparse tile of species 0 (one particle per thread) loads its particles
     // together with the field window: one memory latency for both
     const SpeciesP &S0 = A.tbl[0].p[A.cur_mask & 1u];
-    const int beg0 = S0.tile_off[tile], end0 = S0.tile_off[tile + 1];
+    int beg0 = S0.tile_off[tile], end0 = S0.tile_off[tile + 1];
+    if constexpr (SPLIT) A.split.slice(T.part, beg0, end0);
     const bool sparse0 = ORDER == 1 && end0 > beg0 && end0 - beg0 <= 2 * PUSH_THREADS;
     Batch<1> pre1;
     if (sparse0 && beg0 + (int)threadIdx.x < end0) load_batch<1>(S0, beg0 + (int)threadIdx.x, pre1);
@@ -806,7 +821,6 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     const int tx = tile % A.ti.nt[0];
     const int tyz = tile / A.ti.nt[0];
     const int ty = tyz % A.ti.nt[1], tz = tyz / A.ti.nt[1];
-    TileCtx T;
     T.wo[0] = tx * TX - TL::MGX - 1;
     T.wo[1] = TL::FOLD ? 0 : ty * TY - MARGIN - 1;
     T.wo[2] = tz * TZ - TL::MGZ - 1;
@@ -895,11 +909,11 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     const SegQueue Q = {sQ, &sQn};
     unsigned long long *sJw = sJ + (tid % TL::REP) * TL::JREP;  // this lane's copy
     if constexpr (ORDER == 2)
-        push_tile2<TL>(A, T, tile, sF, sJw, fbits, nfb);
+        push_tile2<TL, SPLIT>(A, T, tile, sF, sJw, fbits, nfb);
     else if (interior)
-        push_tile<TL, true>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
+        push_tile<TL, true, SPLIT>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
     else
-        push_tile<TL, false>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
+        push_tile<TL, false, SPLIT>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
     // counts and fault bits gathered per workgroup in LDS: a global atomic per
     // thread on these single words serialised the whole step once many
     // particles were out of their windows
@@ -1046,7 +1060,9 @@ __global__ __launch_bounds__(256) void k_push_fallback(FusedArgs A) {
                     const uint32_t range = (0xffffffffu >> (31 - hi)) & (0xffffffffu << lo);
                     uint32_t *mw = A.fb_mask + (long long)s * A.mask_words + w;
                     bits = *mw & range;
-                    if (bits) atomicAnd(mw, ~bits);
+                    // a tile that several workgroups share can be listed more
+                    // than once: the bits go to whoever cleared them
+                    if (bits) bits &= atomicAnd(mw, ~bits);
                 }
                 if (__ballot(bits != 0u) == 0ull) continue;
                 // inclusive prefix of the words' particle counts over the wave
@@ -1883,11 +1899,11 @@ namespace {
 template <class TL, int ORDER>
 void launch_fused(const FusedArgs &A, int nb, hipStream_t s, hipEvent_t ev_start,
                   hipEvent_t ev_stop) {
+    const auto k = A.split.n > 1 ? k_push_fused<TL, ORDER, true> : k_push_fused<TL, ORDER, false>;
     if (ev_start)  // timestamps taken by the dispatch itself
-        hipExtLaunchKernelGGL((k_push_fused<TL, ORDER>), dim3(nb), dim3(PUSH_THREADS), 0, s,
-                              ev_start, ev_stop, 0, A);
+        hipExtLaunchKernelGGL(k, dim3(nb), dim3(PUSH_THREADS), 0, s, ev_start, ev_stop, 0, A);
     else
-        hipLaunchKernelGGL((k_push_fused<TL, ORDER>), dim3(nb), dim3(PUSH_THREADS), 0, s, A);
+        hipLaunchKernelGGL(k, dim3(nb), dim3(PUSH_THREADS), 0, s, A);
 }
 }  // namespace
 
@@ -1897,7 +1913,7 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
                        unsigned cur_mask, unsigned wr_mask, uint32_t *fault, unsigned long long *fallback,
                        uint32_t *fb_mask, long long mask_words, int *fb_tiles,
                        unsigned *fb_count, double jscale,
-                       bool fallback_pass, hipStream_t s, hipEvent_t ev_start,
+                       bool fallback_pass, int split, hipStream_t s, hipEvent_t ev_start,
                        hipEvent_t ev_stop, unsigned long long *publish) {
     FusedArgs A;
     A.g = g;
@@ -1921,12 +1937,15 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
     A.fb_tiles = fb_tiles;
     A.fb_count = fb_count;
     A.publish = publish;
-    const int nb = 8 * ((ti.ntiles + 7) / 8);
-    if (fallback_pass)
+    A.split.n = split;
+    const int nb = 8 * ((ti.ntiles * split + 7) / 8);
+    if (fallback_pass) {
         // a grid that fills the chip: after many steps without a sort the
-        // list can hold most tiles
+        // list can hold most tiles; on small grids no more than their items
+        const long long items = (long long)ti.ntiles * split * FB_WPT;
         hipLaunchKernelGGL(g.shape_order == 2 ? k_push_fallback<2> : k_push_fallback<1>,
-                           dim3(2048), dim3(256), 0, s, A);
+                           dim3(std::min(2048u, nblk(items, 256))), dim3(256), 0, s, A);
+    }
     else if (ti.fold)
         launch_fused<TileFold, 1>(A, nb, s, ev_start, ev_stop);
     else if (ti.slab)
