@@ -113,9 +113,9 @@ struct TileFold {
     static_assert(FWX * FWZ <= PUSH_THREADS && JWX * JWZ <= PUSH_THREADS, "one column per thread");
 };
 // Second-order shapes (three-dimensional grids): the 8 x 8 x 4 tile with a
-// 13 x 13 x 9 field window (36.5 KB) and the same current window, no queue:
-// 73 KB, two workgroups per CU.
-using TileCube2 = TileT<8, 8, 4, 0, 1>;
+// 13 x 13 x 9 field window (36.5 KB) and the same current window, and what two
+// workgroups per CU leave for the queue of two-part moves (8 KB): 81.8 KB.
+using TileCube2 = TileT<8, 8, 4, 256, 1>;
 
 // A constant c of the FP32 path as the pair (hi, lo) of FP32 numbers with
 // hi = c rounded and lo = c - hi rounded.  Products c x are formed as

@@ -610,12 +610,18 @@ struct LdsSink2 {
 // window is left as loaded and marked for k_push_fallback, which pushes it
 // through global memory (a second, inlined global deposit here made the
 // kernel spill registers).
+// Bound by VALU issue (59 % of the cycles) and LDS (66 %, half of it lanes of
+// one cell adding to one word) together.  The moves of two parts (707 VALU
+// instructions against 337 for one part; 3 % of the electrons' moves here, so
+// nearly every wave had one) go through the workgroup's queue: benchmark plasma
+// 1678 -> 1537 us per launch.  One or four particles per thread: 1654, 1600 us;
+// lanes two batches apart: 1546.
 template <class TL, int P>
 __device__ __forceinline__ void push_species2(const FusedArgs &A, const DevSpecies &D,
                                               const SpeciesP &S, const SpeciesP &Wr, int beg,
                                               int end, const TileCtx &T, const float *sF,
-                                              unsigned long long *sJ, int s, uint32_t &fbits,
-                                              unsigned &nfb) {
+                                              unsigned long long *sJ, const SegQueue &Q, int s,
+                                              uint32_t &fbits, unsigned &nfb) {
     typedef float VF __attribute__((ext_vector_type(P)));
     typedef uint32_t VU __attribute__((ext_vector_type(P)));
     constexpr int FW3 = TL::FW3, JWX = TL::JWX, JWY = TL::JWY;
@@ -675,20 +681,45 @@ __device__ __forceinline__ void push_species2(const FusedArgs &A, const DevSpeci
             // the window indices the current's stencils span (first node
             // m - 1 of the lower cell to m + 1 of the upper, per axis)
             const int JW[3] = {JWX, JWY, TL::JWZ};
-            bool fits = true;
+            bool fits = true, cross = false;
+            float s1[3];
+            int m0[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const int m0 = o[a] >= 0.5f ? 1 : 0;
-                const int m1 = (int)floorf(o[a] + dx[a] + 0.5f);
-                fits = fits && l[a] + min(m0, m1) - 1 >= 0 && l[a] + max(m0, m1) + 1 < JW[a];
+                s1[a] = o[a] + dx[a];
+                m0[a] = o[a] >= 0.5f ? 1 : 0;
+                const int m1 = (int)floorf(s1[a] + 0.5f);
+                cross = cross || m0[a] != m1;
+                fits = fits && l[a] + min(m0[a], m1) - 1 >= 0 && l[a] + max(m0[a], m1) + 1 < JW[a];
             }
             // a particle whose current leaves the window is pushed again by
             // k_push_fallback from its loaded state (kept here)
             if (list_fallback(A, !fits, s, p, nfb)) continue;
-            {
-                LdsSink2<TL> sink{sJ, lx + JWX * (ly + JWY * lz), mult};
-                ez2_move(o, dx, b.w[k], sink);
+            // a move inside one cell of the stencil is one part; the moves of
+            // two parts go to the workgroup's queue, deposited once the tile's
+            // particles are done (a full queue: at once)
+            const int jb = lx + JWX * (ly + JWY * lz);
+            LdsSink2<TL> sink{sJ, jb, mult};
+            const unsigned long long m = __ballot(cross);
+            bool now = cross;
+            if (m) {
+                const int lane = (int)(threadIdx.x & 63);
+                unsigned qb = 0;
+                if (lane == __builtin_ctzll(__ballot(1)))
+                    qb = atomicAdd(Q.n, (unsigned)__popcll(m));
+                const unsigned slot =
+                    __builtin_amdgcn_readfirstlane(qb) +
+                    __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (cross && slot < (unsigned)TL::QCAP) {
+                    const uint32_t code = (uint32_t)jb | ((uint32_t)s << 17);
+                    Q.q[2 * slot] = make_float4(o[0], o[1], o[2], __uint_as_float(code));
+                    Q.q[2 * slot + 1] = make_float4(dx[0], dx[1], dx[2], b.w[k]);
+                    now = false;
+                }
             }
+            if (!cross) ez2_part(o, s1, m0, b.w[k], sink);
+            else if (now) ez2_move(o, dx, b.w[k], sink);
             float e[3], no[3];
             int dc[3];
 #pragma unroll
@@ -733,7 +764,7 @@ __device__ __forceinline__ void push_species2(const FusedArgs &A, const DevSpeci
 template <class TL, bool SPLIT>
 __device__ __forceinline__ void push_tile2(const FusedArgs &A, const TileCtx &T, int tile,
                                            const float *sF, unsigned long long *sJ,
-                                           uint32_t &fbits, unsigned &nfb) {
+                                           const SegQueue &Q, uint32_t &fbits, unsigned &nfb) {
     for (int s = 0; s < A.nsp; ++s) {
         const DevSpecies &D = A.tbl[s];
         const SpeciesP &S = D.p[(A.cur_mask >> s) & 1u];
@@ -744,9 +775,9 @@ __device__ __forceinline__ void push_tile2(const FusedArgs &A, const TileCtx &T,
         // two particles per thread in dense tiles: four made the 27-point
         // gathers and the EZ deposit spill registers
         if (end - beg <= 2 * PUSH_THREADS)
-            push_species2<TL, 1>(A, D, S, Wr, beg, end, T, sF, sJ, s, fbits, nfb);
+            push_species2<TL, 1>(A, D, S, Wr, beg, end, T, sF, sJ, Q, s, fbits, nfb);
         else
-            push_species2<TL, 2>(A, D, S, Wr, beg, end, T, sF, sJ, s, fbits, nfb);
+            push_species2<TL, 2>(A, D, S, Wr, beg, end, T, sF, sJ, Q, s, fbits, nfb);
     }
 }
 
@@ -909,7 +940,7 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     const SegQueue Q = {sQ, &sQn};
     unsigned long long *sJw = sJ + (tid % TL::REP) * TL::JREP;  // this lane's copy
     if constexpr (ORDER == 2)
-        push_tile2<TL, SPLIT>(A, T, tile, sF, sJw, fbits, nfb);
+        push_tile2<TL, SPLIT>(A, T, tile, sF, sJw, Q, fbits, nfb);
     else if (interior)
         push_tile<TL, true, SPLIT>(A, T, tile, sparse0, beg0, end0, pre1, sF, sJw, Q, fbits, nfb);
     else
@@ -920,8 +951,8 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     if (fbits) atomicOr(&sFbits, fbits);
     if (nfb) atomicAdd(&sNfb, nfb);
     __syncthreads();
-    if constexpr (TL::QCAP > 0 && ORDER == 1) {
-        // the queued second segments
+    if constexpr (TL::QCAP > 0) {
+        // the queued second segments, or two-part moves at second order
         static_assert(TL::JW3 <= 2048, "window index in the 11 bits of a queue entry's code");
         const int nq = (int)min(sQn, (unsigned)TL::QCAP);
         for (int q = tid; q < nq; q += PUSH_THREADS) {
@@ -932,9 +963,14 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
             const double *qcd = A.tbl[code >> 17].qcd;
             const double mult[3] = {A.jscale * qcd[0], A.jscale * qcd[1], A.jscale * qcd[2]};
             const float o[3] = {a.x, a.y, a.z}, dx[3] = {bq.x, bq.y, bq.z};
-            float WB[3], DB[3];
-            second_segment(o, dx, dc, WB, DB);
-            add_second<TL>(sJw, (int)(code & 0x7FFu), dc, T.yflip, WB, DB, bq.w, mult);
+            if constexpr (ORDER == 2) {
+                LdsSink2<TL> sink{sJw, (int)(code & 0x7FFu), mult};
+                ez2_move(o, dx, bq.w, sink);
+            } else {
+                float WB[3], DB[3];
+                second_segment(o, dx, dc, WB, DB);
+                add_second<TL>(sJw, (int)(code & 0x7FFu), dc, T.yflip, WB, DB, bq.w, mult);
+            }
         }
         __syncthreads();
     }
