@@ -350,11 +350,11 @@ void adaptive_record(empic_sim *s) {
 }
 
 // One PIC cycle.  FP32 path: particles are read from buffer set bit s of
-// rd_mask and written to bit s of wr_mask of table `tbl` (the species' own
-// sets by default).
+// rd_mask and written to bit s of wr_mask of table `tbl`, whose state's tile
+// offsets are toff (the species' own sets by default).
 template <typename T>
 void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, int wr_mask = -1,
-              unsigned long long *publish = nullptr) {
+              unsigned long long *publish = nullptr, const int32_t *const *toff = nullptr) {
     T *E[3], *B[3], *J[3], *Bb[3];
     field_ptrs<T>(s, E, B, J, Bb);
     const bool absorbing = s->g.bc[0] == EMPIC_BC_ABSORBING || s->g.bc[1] == EMPIC_BC_ABSORBING ||
@@ -377,6 +377,9 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
             unsigned mask = 0;
             for (int i = 0; i < s->nsp; ++i) mask |= (unsigned)s->sp[i].cur << i;
             if (!tbl) tbl = s->table;
+            const int32_t *own[EMPIC_MAX_SPECIES] = {};
+            for (int i = 0; i < s->nsp; ++i) own[i] = s->sp[i].tile_off;
+            if (!toff) toff = own;
             const unsigned rmask = rd_mask < 0 ? mask : (unsigned)rd_mask;
             const unsigned wmask = wr_mask < 0 ? mask : (unsigned)wr_mask;
             // the fused kernel is timed by events attached to its own dispatch
@@ -395,7 +398,7 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
             const int split = tile_split(s->ti.ntiles, slots / s->ti.ntiles, 256, 512);
             for (int pass = 0; pass < 2; ++pass)
                 launch_push_fused(s->g, s->ti, (float *const *)E, (float *const *)Bb,
-                                  s->jfix, tbl, s->nsp, rmask, wmask, s->fault,
+                                  s->jfix, tbl, toff, s->nsp, rmask, wmask, s->fault,
                                   s->fallback, s->fb_mask, s->mask_words,
                                   split > 1 ? s->counts : s->fb_tiles,
                                   s->fb_count, s->jscale,
@@ -1385,7 +1388,11 @@ empic_status empic_step_state(empic_sim *s, const empic_state *src, const empic_
         s->E[a] = dst->E[a];
         s->B[a] = dst->B[a];
     }
-    one_step<float>(s, s->xtable, 0, (int)((1u << s->nsp) - 1u));
+    // a species without slots has no arrays in a state: its own (empty) offsets
+    const int32_t *toff[EMPIC_MAX_SPECIES] = {};
+    for (int i = 0; i < s->nsp; ++i)
+        toff[i] = src->tiles[i] ? src->tiles[i] : s->sp[i].tile_off;
+    one_step<float>(s, s->xtable, 0, (int)((1u << s->nsp) - 1u), nullptr, toff);
     for (int a = 0; a < 3; ++a) {
         s->E[a] = E0[a];
         s->B[a] = B0[a];

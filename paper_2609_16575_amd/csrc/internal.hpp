@@ -305,9 +305,10 @@ void launch_field_energy(const GridP &g, T *const E[3], T *const B[3], double *p
 // that pass also writes the cumulative out-of-window count to `publish`
 // (device-accessible pinned host memory) when it is not null.  split:
 // workgroups per tile (tile_split); fb_tiles holds split entries per tile.
+// toff: per species, the tile offsets of the state that is read.
 void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
                        float *const Bbar[3], unsigned long long *const Jf[3],
-                       const DevSpecies *tbl, int nsp,
+                       const DevSpecies *tbl, const int32_t *const *toff, int nsp,
                        unsigned cur_mask, unsigned wr_mask, uint32_t *fault, unsigned long long *fallback,
                        uint32_t *fb_mask, long long mask_words, int *fb_tiles,
                        unsigned *fb_count, double jscale,

@@ -59,6 +59,8 @@ struct FusedArgs {
                                    // entries in fb_tiles (cleared by k_faraday)
     unsigned long long *publish;   // host-visible copy of *fallback (k_push_fallback), or null
     TileSplit split;               // workgroups per tile
+    const int32_t *toff[EMPIC_MAX_SPECIES];  // tile offsets of the state read
+    FastDiv dnt[2];                // by the tiles along x, y
 };
 
 // global atomic deposit of one segment's 12 values at cell (ci,cj,ck), in
@@ -321,7 +323,7 @@ struct TileCtx {
 // segment.  A full queue makes the particle deposit its second segment at
 // once.
 //
-// On the benchmark plasma (540 us per launch) the kernel sits between three
+// On the benchmark plasma (528 us per launch) the kernel sits between three
 // bounds: its 1.96 GB take 413 us at a copy's rate (4.7 TB/s; 403 us measured
 // without the gathers and the LDS adds), its VALU instructions about 400 us
 // and its LDS accesses about 300 us, overlapped by 16 waves per CU.  The
@@ -835,23 +837,34 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     if (tile >= A.ti.ntiles) return;
     TileCtx T;
     T.part = SPLIT ? id - tile * A.split.n : 0;
+    // The chain of dependent loads in front of the particle loop is what a
+    // workgroup of a sparse tile or a small grid spends much of its time on:
+    // the tile offsets come straight from pointers in the arguments, and the
+    // window's loads take their addresses from arithmetic, not from the
+    // index tables below (which only the flush reads), so that the window's
+    // and the first particles' loads go out together, one latency after the
+    // start; the current window is cleared while they are under way.  Wakefield
+    // box (57 k tiles of about 512 particles, one per thread) 1323 -> 1195 us per
+    // launch, benchmark plasma 541 -> 528, 75 x 49 x 53 with 2 x 4 per cell 57 -> 54.
+    // Loading a second sparse batch ahead: box 1220; two particles per thread from
+    // 513 on: 54 -> 51 on the last, but 523 -> 532 on the second.
     int total = 0;
-    for (int s = 0; s < A.nsp; ++s)
-        total += A.tbl[s].p[0].tile_off[tile + 1] - A.tbl[s].p[0].tile_off[tile];
+#pragma unroll
+    for (int s = 0; s < EMPIC_MAX_SPECIES; ++s)
+        if (s < A.nsp) total += A.toff[s][tile + 1] - A.toff[s][tile];
     if (total == 0) return;
 
     // a sparse tile of species 0 (one particle per thread) loads its particles
     // together with the field window: one memory latency for both
     const SpeciesP &S0 = A.tbl[0].p[A.cur_mask & 1u];
-    int beg0 = S0.tile_off[tile], end0 = S0.tile_off[tile + 1];
+    int beg0 = A.toff[0][tile], end0 = A.toff[0][tile + 1];
     if constexpr (SPLIT) A.split.slice(T.part, beg0, end0);
     const bool sparse0 = ORDER == 1 && end0 > beg0 && end0 - beg0 <= 2 * PUSH_THREADS;
     Batch<1> pre1;
     if (sparse0 && beg0 + (int)threadIdx.x < end0) load_batch<1>(S0, beg0 + (int)threadIdx.x, pre1);
 
-    const int tx = tile % A.ti.nt[0];
-    const int tyz = tile / A.ti.nt[0];
-    const int ty = tyz % A.ti.nt[1], tz = tyz / A.ti.nt[1];
+    const int tyz = (int)fastdiv((uint32_t)tile, A.dnt[0]), tx = tile - tyz * A.ti.nt[0];
+    const int tz = (int)fastdiv((uint32_t)tyz, A.dnt[1]), ty = tyz - tz * A.ti.nt[1];
     T.wo[0] = tx * TX - TL::MGX - 1;
     T.wo[1] = TL::FOLD ? 0 : ty * TY - MARGIN - 1;
     T.wo[2] = tz * TZ - TL::MGZ - 1;
@@ -862,6 +875,46 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
     for (int a = 0; a < 3; ++a) interior = interior && T.wo[a] >= 0 && T.wo[a] + JW[a] <= g.n[a];
     T.wo_pack = interior ? pack_cell(T.wo[0], T.wo[1], T.wo[2]) : 0u;
     const int tid = threadIdx.x;
+
+    // A thread owns one column of the window, (x, z) of both rows of a folded
+    // one, else (x, y) at every ZG-th z, and the same points of all six
+    // components: their global offsets are worked out once, and every load is
+    // issued before any is waited on
+    constexpr int NCOL = TL::FOLD ? FWX * FWZ : FWX * FWY;
+    constexpr int ZG = TL::FOLD ? 1 : PUSH_THREADS / NCOL;
+    constexpr int NZ = TL::FOLD ? 2 : (FWZ + ZG - 1) / ZG;
+    const int col = tid % NCOL, zg = tid / NCOL;
+    const int wc = col / FWX, lx = col - wc * FWX;
+    const int sxy = g.ext[0] * g.ext[1];
+    int off[NZ];
+    if (interior) {
+        const int o0 = T.wo[0] + lx + (TL::FOLD ? 0 : (T.wo[1] + wc) * g.ext[0]);
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) {
+            const int lz = TL::FOLD ? wc : zg + q * ZG;
+            off[q] = TL::FOLD ? o0 + (T.wo[2] + lz) * sxy + q * T.yflip * g.ext[0]
+                              : (lz < FWZ ? o0 + (T.wo[2] + lz) * sxy : -1);
+        }
+    } else {
+        const int gx = gaxis(g, 0, T.wo[0] + lx), gy = TL::FOLD ? 0 : gaxis(g, 1, T.wo[1] + wc);
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) {
+            const int lz = TL::FOLD ? wc : zg + q * ZG;
+            const int gz = lz < FWZ ? gaxis(g, 2, T.wo[2] + lz) : -1;
+            const int y = TL::FOLD ? q * T.yflip : gy;
+            off[q] = (gx | gy | gz) >= 0 ? gx + y * g.ext[0] + gz * sxy : -1;
+        }
+    }
+    if (zg >= ZG)
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) off[q] = -1;
+    float tmp[6][NZ];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        const float *src = c < 3 ? A.E[c] : A.Bb[c - 3];
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) tmp[c][q] = off[q] >= 0 ? src[off[q]] : 0.f;
+    }
 
     // global index tables of the window rows: x index, y*ext0, z*ext0*ext1
     if (tid == 0) {
@@ -875,63 +928,29 @@ __global__ __launch_bounds__(PUSH_THREADS, 4) void k_push_fused(FusedArgs A) {
         if (l < wl) {
             const int woa = a == 0 ? T.wo[0] : (a == 1 ? T.wo[1] : T.wo[2]);
             const int gi = gaxis(g, a, woa + l);
-            const int mul = a == 0 ? 1 : (a == 1 ? g.ext[0] : g.ext[0] * g.ext[1]);
+            const int mul = a == 0 ? 1 : (a == 1 ? g.ext[0] : sxy);
             sG[a][l] = gi < 0 ? -1 : gi * mul;
             sPad[a][l] = (gi >= 0 && g.bc[a] != EMPIC_BC_PERIODIC && gi >= g.n[a]) ? 1 : 0;
-        }
-    }
-    __syncthreads();
-    if constexpr (TL::FOLD) {
-        // one (x, z) column of both rows per thread
-        const int lz = tid / FWX, lx = tid - lz * FWX;
-        if (tid < FWX * FWZ) {
-            const int gx = sG[0][lx], gz = sG[2][lz];
-            const int r1 = T.yflip ? g.ext[0] : 0;
-            float2 tmp[6];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) {
-                const float *src = c < 3 ? A.E[c] : A.Bb[c - 3];
-                tmp[c] = (gx | gz) >= 0 ? make_float2(src[gx + gz], src[gx + gz + r1])
-                                        : make_float2(0.f, 0.f);
-            }
-#pragma unroll
-            for (int c = 0; c < 6; ++c) *(float2 *)(sF + c * FW3 + 2 * tid) = tmp[c];
-        }
-    } else {
-        // a thread owns one (x, y) column of the window at every ZG-th z and
-        // the same points of all six components: their global offsets are
-        // worked out once, and every load is issued before any is waited on
-        constexpr int NCOL = FWX * FWY, ZG = PUSH_THREADS / NCOL, NZ = (FWZ + ZG - 1) / ZG;
-        const int col = tid % NCOL, zg = tid / NCOL;
-        if (zg < ZG) {
-            const int ly = col / FWX, lx = col - ly * FWX;
-            const int gxy = (sG[0][lx] >= 0 && sG[1][ly] >= 0) ? sG[0][lx] + sG[1][ly] : -1;
-            int off[NZ];
-#pragma unroll
-            for (int q = 0; q < NZ; ++q) {
-                const int lz = zg + q * ZG;
-                off[q] = (lz < FWZ && gxy >= 0 && sG[2][lz] >= 0) ? gxy + sG[2][lz] : -1;
-            }
-            float tmp[6][NZ];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) {
-                const float *src = c < 3 ? A.E[c] : A.Bb[c - 3];
-#pragma unroll
-                for (int q = 0; q < NZ; ++q) tmp[c][q] = off[q] >= 0 ? src[off[q]] : 0.f;
-            }
-#pragma unroll
-            for (int c = 0; c < 6; ++c)
-#pragma unroll
-                for (int q = 0; q < NZ; ++q) {
-                    const int lz = zg + q * ZG;
-                    if (lz < FWZ) sF[c * FW3 + col + lz * NCOL] = tmp[c][q];
-                }
         }
     }
     {
         // 16-byte stores (the window has an even number of words with its pad)
         uint4 *z4 = (uint4 *)sJ;
         for (int e = tid; e < (JALL + 1) / 2; e += PUSH_THREADS) z4[e] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (zg < ZG) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            if constexpr (TL::FOLD) {
+                *(float2 *)(sF + c * FW3 + 2 * col) = make_float2(tmp[c][0], tmp[c][1]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < NZ; ++q) {
+                    const int lz = zg + q * ZG;
+                    if (lz < FWZ) sF[c * FW3 + col + lz * NCOL] = tmp[c][q];
+                }
+            }
+        }
     }
     __syncthreads();
 
@@ -1945,7 +1964,7 @@ void launch_fused(const FusedArgs &A, int nb, hipStream_t s, hipEvent_t ev_start
 
 void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
                        float *const Bbar[3], unsigned long long *const Jf[3],
-                       const DevSpecies *tbl, int nsp,
+                       const DevSpecies *tbl, const int32_t *const *toff, int nsp,
                        unsigned cur_mask, unsigned wr_mask, uint32_t *fault, unsigned long long *fallback,
                        uint32_t *fb_mask, long long mask_words, int *fb_tiles,
                        unsigned *fb_count, double jscale,
@@ -1974,6 +1993,8 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
     A.fb_count = fb_count;
     A.publish = publish;
     A.split.n = split;
+    for (int i = 0; i < EMPIC_MAX_SPECIES; ++i) A.toff[i] = i < nsp ? toff[i] : nullptr;
+    for (int a = 0; a < 2; ++a) A.dnt[a] = make_fastdiv((uint32_t)ti.nt[a]);
     const int nb = 8 * ((ti.ntiles * split + 7) / 8);
     if (fallback_pass) {
         // a grid that fills the chip: after many steps without a sort the
