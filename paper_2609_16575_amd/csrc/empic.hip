@@ -351,10 +351,13 @@ void adaptive_record(empic_sim *s) {
 
 // One PIC cycle.  FP32 path: particles are read from buffer set bit s of
 // rd_mask and written to bit s of wr_mask of table `tbl`, whose state's tile
-// offsets are toff (the species' own sets by default).
+// offsets are toff (the species' own sets by default).  write_J = false: the
+// caller runs another step before anyone can read J, which Ampere forms itself
+// and then need not store.
 template <typename T>
 void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, int wr_mask = -1,
-              unsigned long long *publish = nullptr, const int32_t *const *toff = nullptr) {
+              unsigned long long *publish = nullptr, const int32_t *const *toff = nullptr,
+              bool write_J = true) {
     T *E[3], *B[3], *J[3], *Bb[3];
     field_ptrs<T>(s, E, B, J, Bb);
     const bool absorbing = s->g.bc[0] == EMPIC_BC_ABSORBING || s->g.bc[1] == EMPIC_BC_ABSORBING ||
@@ -428,7 +431,7 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
         launch_filter<T>(s->g, J, f32 ? jf : nullptr, jinv, J, tmp, s->filter_passes,
                          s->filter_comp, s->stream);
     }
-    launch_ampere<T>(s->g, E, B, J, jmode, jf, jinv, s->stream);  // sets the PEC faces too
+    launch_ampere<T>(s->g, E, B, J, jmode, write_J, jf, jinv, s->stream);  // sets the PEC faces too
     if (s->laser.enabled) launch_laser<T>(s->g, E, s->laser, (s->nstep + 0.5) * s->g.dt, s->stream);
     if (absorbing) launch_mur_apply<T>(s->g, E, planes, s->L.mur_stride, s->stream);
     if (s->port.enabled) launch_port<T>(s->g, E, s->port, (s->nstep + 1) * s->g.dt, s->stream);
@@ -954,17 +957,23 @@ empic_status empic_step(empic_sim *s, int32_t nsteps) {
     if (!s->bound) return fail(s, EMPIC_E_ARG, "fields not bound");
     if (nsteps < 0) return fail(s, EMPIC_E_ARG, "negative step count");
     for (int k = 0; k < nsteps; ++k) {
+        const bool last = k == nsteps - 1;
         if (fp64(s)) {
-            one_step<double>(s);
+            one_step<double>(s, nullptr, -1, -1, nullptr, nullptr, last);
         } else {
-            if (s->window.enabled && !window_step(s))
+            if (s->window.enabled && !window_step(s)) {
+                if (k > 0 && !s->filter_passes && !s->filter_comp)  // J of the last step run
+                    launch_j_from_fixed(s->g, (float *const *)s->J,
+                                        (const long long *const *)s->jfix, 1.0 / s->jscale,
+                                        s->stream);
                 return fail(s, EMPIC_E_CAPACITY,
                             "the injected plasma would take particle ids past 2^31 - 1");
+            }
             if (s->adaptive) adaptive_poll(s);
             const int S = s->desc.sort_every;
             if (s->nsp > 0 && (s->need_sort || (S > 0 && s->nstep % S == 0))) do_sort(s);
             const bool publish = s->adaptive && s->nsp > 0;
-            one_step<float>(s, nullptr, -1, -1, publish ? adaptive_slot(s) : nullptr);
+            one_step<float>(s, nullptr, -1, -1, publish ? adaptive_slot(s) : nullptr, nullptr, last);
             if (publish) adaptive_record(s);
         }
     }

@@ -262,11 +262,12 @@ void launch_faraday(const GridP &g, T *const E[3], T *const B[3], T *const Bbar[
                     unsigned *fb_reset = nullptr, T *mur_planes = nullptr,
                     long long plane_stride = 0);
 // Ampere-Maxwell and the PEC faces; J_FIXED: J is first set to Jf * jinv
-// (FP32 path), J_NONE: to zero (no particles), J_READ: taken as it is
+// (FP32 path), J_NONE: to zero (no particles), J_READ: taken as it is; the J so
+// formed is stored with write_J
 enum JMode { J_READ, J_FIXED, J_NONE };
 template <typename T>
 void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], JMode mode,
-                   const long long *const Jf[3], double jinv, hipStream_t s);
+                   bool write_J, const long long *const Jf[3], double jinv, hipStream_t s);
 void launch_j_from_fixed(const GridP &g, float *const J[3], const long long *const Jf[3],
                          double jinv, hipStream_t s);
 // dst[a][i] = src[a][i], six arrays of n floats, one launch
