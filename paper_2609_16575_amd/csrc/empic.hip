@@ -439,6 +439,38 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
     s->nstep += 1;
 }
 
+// Steps of a grid without particles, in pairs: E, B into scratch and back
+// (Bbar and the filter's buffer, which such a step does not use otherwise), so
+// that Faraday and Ampere are one pass over memory.  Returns the steps done; a
+// single step is left to one_step.
+template <typename T>
+int vacuum_steps(empic_sim *s, int nsteps) {
+    if (s->nsp > 0 || s->window.enabled || !vacuum_fits(s->g)) return 0;
+    const bool absorbing = s->g.bc[0] == EMPIC_BC_ABSORBING || s->g.bc[1] == EMPIC_BC_ABSORBING ||
+                           s->g.bc[2] == EMPIC_BC_ABSORBING;
+    T *E[3], *B[3], *J[3], *E2[3], *B2[3];
+    field_ptrs<T>(s, E, B, J, E2);
+    for (int c = 0; c < 3; ++c) B2[c] = (T *)s->filt + (size_t)c * s->g.V;
+    T *planes = absorbing ? (T *)s->mur : nullptr;
+    const int pairs = nsteps / 2;
+    for (int k = 0; k < 2 * pairs; ++k) {
+        TimedEvent t;
+        ev_begin(s, t, 1);
+        T *const *Eo = k % 2 == 0 ? E2 : E;
+        launch_vacuum<T>(s->g, k % 2 == 0 ? E : E2, k % 2 == 0 ? B : B2, Eo,
+                         k % 2 == 0 ? B2 : B, k == nsteps - 1 ? J : nullptr, planes,
+                         s->L.mur_stride, s->stream);
+        if (s->laser.enabled)
+            launch_laser<T>(s->g, Eo, s->laser, (s->nstep + 0.5) * s->g.dt, s->stream);
+        if (absorbing) launch_mur_apply<T>(s->g, Eo, planes, s->L.mur_stride, s->stream);
+        if (s->port.enabled)
+            launch_port<T>(s->g, Eo, s->port, (s->nstep + 1) * s->g.dt, s->stream);
+        ev_end(s, t);
+        s->nstep += 1;
+    }
+    return 2 * pairs;
+}
+
 // Moving window (FP32 path): at the start of a step, once the window has
 // travelled (t - t_start) v >= (shifts + 1) cells d, fields and particles
 // move `cells` cells back along the window axis, particles behind it are
@@ -956,7 +988,8 @@ empic_status empic_step(empic_sim *s, int32_t nsteps) {
     EMPIC_GUARD(s);
     if (!s->bound) return fail(s, EMPIC_E_ARG, "fields not bound");
     if (nsteps < 0) return fail(s, EMPIC_E_ARG, "negative step count");
-    for (int k = 0; k < nsteps; ++k) {
+    const int done = fp64(s) ? vacuum_steps<double>(s, nsteps) : vacuum_steps<float>(s, nsteps);
+    for (int k = done; k < nsteps; ++k) {
         const bool last = k == nsteps - 1;
         if (fp64(s)) {
             one_step<double>(s, nullptr, -1, -1, nullptr, nullptr, last);

@@ -241,6 +241,167 @@ __global__ __launch_bounds__(PT_THREADS) void k_ampere(
     }
 }
 
+// Faraday and Ampere of a step without particles in one pass, from E, B to
+// Eo, Bo (neighbouring workgroups still read the old values).  A workgroup
+// marches along z over zc planes of a 31 x 15 patch: its 32 x 16 threads form
+// B' at the patch and at the row and column below it, hand it to their +x and
+// +y neighbours through LDS and to the plane above in registers, and E' follows
+// without a trip to memory.  Loads run one plane ahead of the arithmetic.
+// Bound by memory: 48 bytes per point and step, where the two point kernels
+// move 72 (the halos come from the XCD's L2, whose workgroups share a range of
+// z).  Out of place the arrays take twice the room in the memory-side cache,
+// which the point kernels live on: 91 x 46 x 3001, 224 -> 202 us per step, and not
+// by the ratio of the bytes; nontemporal accesses lose what is left of it (249).
+// The same expressions as k_faraday and k_ampere, so the same bits.
+constexpr int VX = 32, VY = 16, VT = VX * VY;
+
+template <typename T>
+struct VacIO {
+    const T *E[3], *B[3];
+    T *Eo[3], *Bo[3];
+    T *J[3];  // zeroed when given (the last step of a call)
+    T *planes;
+    long long pstride;
+};
+
+// what a thread reads of one plane: E beside its point and old B
+template <typename T>
+struct VacPlane {
+    T ez, eyx, ezx, exy, ezy, exz, eyz, b[3];
+};
+
+template <typename T>
+__global__ __launch_bounds__(VT, 4) void k_vacuum(GridP g, VacIO<T> F, int nbx, int nby, int nbz,
+                                                  int zc) {
+    __shared__ T sB[2][3][VT];
+    const int nb8 = gridDim.x >> 3;
+    const int id = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous
+    if (id >= nbx * nby * nbz) return;
+    const int bz = id / (nbx * nby), bxy = id - bz * (nbx * nby);
+    const int by = bxy / nbx, bx = bxy - by * nbx;
+    const int tid = threadIdx.x, tx = tid & (VX - 1), ty = tid / VX;
+
+    Pt q;
+    q.st[0] = 1;
+    q.st[1] = g.ext[0];
+    q.st[2] = (long long)g.ext[0] * g.ext[1];
+    q.idx[0] = bx * (VX - 1) + tx - 1;
+    q.idx[1] = by * (VY - 1) + ty - 1;
+    bool in = true;  // the thread's column lies on the grid
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        if (q.idx[a] >= g.ext[a]) in = false;
+        if (q.idx[a] < 0) {
+            q.idx[a] = g.n[a] - 1;  // below a periodic axis' first point
+            in = in && g.bc[a] == EMPIC_BC_PERIODIC;
+        }
+    }
+    const bool own = in && tx > 0 && ty > 0;
+    const int zs = bz * zc, ze = min(zs + zc, g.ext[2]);
+    // the plane below: of a walled axis' first point nothing reads it
+    const bool below = zs > 0 || g.bc[2] == EMPIC_BC_PERIODIC;
+    int z = below ? (zs > 0 ? zs - 1 : g.n[2] - 1) : zs;
+
+    // +1 neighbours; past a wall the component is padding and nothing reads them
+    const auto upc = [&](int a) {
+        return g.bc[a] != EMPIC_BC_PERIODIC && q.idx[a] == g.n[a] ? 0ll : up(g, q, a);
+    };
+    const long long ux = in ? upc(0) : 0, uy = in ? upc(1) : 0;
+    const long long col = q.idx[0] + (long long)g.ext[0] * q.idx[1];
+    const auto load = [&](int zz, VacPlane<T> &v) {
+        q.idx[2] = zz;
+        const long long p = col + zz * q.st[2], uz = upc(2);
+        v.ez = F.E[2][p];
+        v.eyx = F.E[1][p + ux];
+        v.ezx = F.E[2][p + ux];
+        v.exy = F.E[0][p + uy];
+        v.ezy = F.E[2][p + uy];
+        v.exz = F.E[0][p + uz];
+        v.eyz = F.E[1][p + uz];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v.b[c] = F.B[c][p];
+    };
+    VacPlane<T> v{}, w{};
+    T ex = T(0), ey = T(0);  // E_x, E_y at the thread's point
+    if (in) {
+        ex = F.E[0][col + z * q.st[2]];
+        ey = F.E[1][col + z * q.st[2]];
+        load(z, v);
+    }
+    const double dt = g.dt;
+    const double ix = g.inv_d[0], iy = g.inv_d[1], iz = g.inv_d[2];
+    T bxd = T(0), byd = T(0);  // B'_x, B'_y one plane below
+    int buf = 0;
+    for (int k = below ? -1 : 0; zs + k < ze; ++k) {
+        const int zn = zs + k + 1;  // the next plane
+        if (in && zn < ze) load(zn, w);
+        q.idx[2] = z;
+        q.p = col + z * q.st[2];
+        T b[3] = {v.b[0], v.b[1], v.b[2]};
+        if (in) {
+            if (valid_B(g, q, 0)) {
+                const double curl = ((double)v.ezy - (double)v.ez) * iy -
+                                    ((double)v.eyz - (double)ey) * iz;
+                b[0] = (T)((double)b[0] - dt * curl);
+            }
+            if (valid_B(g, q, 1)) {
+                const double curl = ((double)v.exz - (double)ex) * iz -
+                                    ((double)v.ezx - (double)v.ez) * ix;
+                b[1] = (T)((double)b[1] - dt * curl);
+            }
+            if (valid_B(g, q, 2)) {
+                const double curl = ((double)v.eyx - (double)ey) * ix -
+                                    ((double)v.exy - (double)ex) * iy;
+                b[2] = (T)((double)b[2] - dt * curl);
+            }
+        }
+        if (k >= 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sB[buf][c][tid] = b[c];
+            __syncthreads();  // (the other buffer is read before this barrier only)
+            if (own) {
+                const long long p = q.p;
+                if (F.planes) mur_save(g, q, F.E, F.planes, F.pstride);
+                T e[3] = {ex, ey, v.ez};
+                if (ampere_E(g, q, 0)) {
+                    const double curl = ((double)b[2] - (double)sB[buf][2][tid - VX]) * iy -
+                                        ((double)b[1] - (double)byd) * iz;
+                    e[0] = (T)((double)e[0] + dt * (curl - 0.0));
+                } else if (pec_zero(g, q.idx, 0)) {
+                    e[0] = T(0);
+                }
+                if (ampere_E(g, q, 1)) {
+                    const double curl = ((double)b[0] - (double)bxd) * iz -
+                                        ((double)b[2] - (double)sB[buf][2][tid - 1]) * ix;
+                    e[1] = (T)((double)e[1] + dt * (curl - 0.0));
+                } else if (pec_zero(g, q.idx, 1)) {
+                    e[1] = T(0);
+                }
+                if (ampere_E(g, q, 2)) {
+                    const double curl = ((double)b[1] - (double)sB[buf][1][tid - 1]) * ix -
+                                        ((double)b[0] - (double)sB[buf][0][tid - VX]) * iy;
+                    e[2] = (T)((double)e[2] + dt * (curl - 0.0));
+                } else if (pec_zero(g, q.idx, 2)) {
+                    e[2] = T(0);
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    F.Eo[c][p] = e[c];
+                    F.Bo[c][p] = b[c];
+                    if (F.J[0]) F.J[c][p] = T(0);
+                }
+            }
+            buf ^= 1;
+        }
+        bxd = b[0];
+        byd = b[1];
+        ex = v.exz;
+        ey = v.eyz;
+        v = w;
+        z = zn;
+    }
+}
+
 // Six arrays of n floats copied in one launch (the fields of a state)
 struct Copy6 {
     const float *src[6];
@@ -601,6 +762,42 @@ void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], 
                        Jf ? Jf[2] : nullptr, jinv);
 }
 
+// Two million points and a patch's extent along y and z: below, the march along
+// z is latency (31 x 16 x 1001: 22 us per step against 18 for the two point
+// kernels; 1024 x 64 x 16: 20 against 17; 46 x 23 x 1501: 31 against 32; 128^3: 24
+// against 29; 61 x 31 x 2001: 47 against 60; 91 x 46 x 3001: 202 against 224;
+// 256^3: 248 against 317, in FP64 486 against 576), and a thin axis leaves
+// threads idle or doubles the planes worked.
+bool vacuum_fits(const GridP &g) {
+    return g.V >= (1ll << 21) && g.ext[1] >= VY - 1 && g.ext[2] >= 16;
+}
+
+// A step without particles of E, B into Eo, Bo (J zeroed when given).
+template <typename T>
+void launch_vacuum(const GridP &g, T *const E[3], T *const B[3], T *const Eo[3], T *const Bo[3],
+                   T *const J[3], T *mur_planes, long long plane_stride, hipStream_t s) {
+    VacIO<T> F;
+    for (int c = 0; c < 3; ++c) {
+        F.E[c] = E[c];
+        F.B[c] = B[c];
+        F.Eo[c] = Eo[c];
+        F.Bo[c] = Bo[c];
+        F.J[c] = J ? J[c] : nullptr;
+    }
+    F.planes = mur_planes;
+    F.pstride = plane_stride;
+    const int nbx = (g.ext[0] + VX - 2) / (VX - 1), nby = (g.ext[1] + VY - 2) / (VY - 1);
+    // 16 planes per workgroup where that leaves two workgroups per CU, else 8: 61 x
+    // 31 x 2001 (756 of 16) 47 us per step with 16 and 54 with 8, 46 x 23 x 1501
+    // (376 of 16) 41 and 31, 91 x 46 x 3001 (2256) 202 and 197; with 4 and with
+    // 32 slower than the better of these everywhere.
+    const int zc = (long long)nbx * nby * ((g.ext[2] + 15) / 16) >= 512 ? 16 : 8;
+    const int nbz = (g.ext[2] + zc - 1) / zc;
+    const long long nb = (long long)nbx * nby * nbz;
+    hipLaunchKernelGGL(k_vacuum<T>, dim3((unsigned)((nb + 7) / 8 * 8)), dim3(VT), 0, s, g, F, nbx,
+                       nby, nbz, zc);
+}
+
 void launch_copy6(const float *const src[6], float *const dst[6], long long n, hipStream_t s) {
     Copy6 c;
     for (int a = 0; a < 6; ++a) {
@@ -740,6 +937,8 @@ void launch_field_energy(const GridP &g, T *const E[3], T *const B[3], double *p
     template void launch_ampere<T>(const GridP &, T *const[3], T *const[3], T *const[3],       \
                                    JMode, bool, const long long *const[3], double,             \
                                    hipStream_t);                                               \
+    template void launch_vacuum<T>(const GridP &, T *const[3], T *const[3], T *const[3],       \
+                                   T *const[3], T *const[3], T *, long long, hipStream_t);     \
     template void launch_mur_apply<T>(const GridP &, T *const[3], const T *, long long,        \
                                       hipStream_t);                                            \
     template void launch_laser<T>(const GridP &, T *const[3], const empic_laser_desc &, double, \

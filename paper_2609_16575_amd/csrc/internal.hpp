@@ -268,6 +268,11 @@ enum JMode { J_READ, J_FIXED, J_NONE };
 template <typename T>
 void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], JMode mode,
                    bool write_J, const long long *const Jf[3], double jinv, hipStream_t s);
+// a whole step without particles, out of place, on grids where one pass pays
+bool vacuum_fits(const GridP &g);
+template <typename T>
+void launch_vacuum(const GridP &g, T *const E[3], T *const B[3], T *const Eo[3], T *const Bo[3],
+                   T *const J[3], T *mur_planes, long long plane_stride, hipStream_t s);
 void launch_j_from_fixed(const GridP &g, float *const J[3], const long long *const Jf[3],
                          double jinv, hipStream_t s);
 // dst[a][i] = src[a][i], six arrays of n floats, one launch
