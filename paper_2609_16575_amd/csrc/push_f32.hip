@@ -61,7 +61,8 @@ struct FusedArgs {
     TileSplit split;               // workgroups per tile
     const int32_t *toff[EMPIC_MAX_SPECIES];  // tile offsets of the state read
     FastDiv dnt[2];                // by the tiles along x, y
-    FastDiv dgrp;                  // by the tiles of ZGROUP layers
+    FastDiv dgrp;                  // by the tiles of zgroup layers
+    int zgroup;                    // 1, or ZGROUP (tile_in_groups)
 };
 
 // global atomic deposit of one segment's 12 values at cell (ci,cj,ck), in
@@ -811,15 +812,20 @@ __device__ __forceinline__ void push_tile(const FusedArgs &A, const TileCtx &T, 
     }
 }
 
-// The seq-th tile in groups of ZGROUP layers along z, each taken x fastest, then
+// The seq-th tile in groups of zgroup layers along z, each taken x fastest, then
 // z, then y.  A cubic tile's field window is twice its extent along z: with the
 // neighbours along z an x row apart, instead of a whole layer, the overlap is
 // still in the XCD's L2 (loading the windows is 385 of the 1194 us below).
 // Wakefield box, 128 x 16 x 32 tiles: 1194 us per launch in layers, 1197 in
 // groups of two, 1170 of four, 1165 of eight; 128^3 with 8 per cell 526, 526,
-// 523, 540; second order with 8 per cell 1534, 1534, 1528, 1543.
+// 523, 540; second order with 8 per cell 1534, 1534, 1528, 1543.  Layers whose
+// windows (28 KB each) fit the 4 MB of L2 gain nothing and stay ungrouped: with
+// 4 x 4 x 35 tiles, just more than the chip takes at once, groups of four put full
+// tiles instead of the grid's cut ones last (25 x 25 x 139: 50 us against 45).
 constexpr int ZGROUP = 4;
+constexpr int ZGROUP_MIN = 150;  // tiles per layer: 4 MB of windows
 __device__ __forceinline__ int tile_in_groups(const FusedArgs &A, int seq) {
+    if (A.zgroup == 1) return seq;
     const int grp = (int)fastdiv((uint32_t)seq, A.dgrp), r = seq - grp * (int)A.dgrp.d;
     const int nz = min(ZGROUP, A.ti.nt[2] - grp * ZGROUP);
     const int row = (int)fastdiv((uint32_t)r, A.dnt[0]), x = r - row * A.ti.nt[0];
@@ -2035,7 +2041,8 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
     A.split.n = split;
     for (int i = 0; i < EMPIC_MAX_SPECIES; ++i) A.toff[i] = i < nsp ? toff[i] : nullptr;
     for (int a = 0; a < 2; ++a) A.dnt[a] = make_fastdiv((uint32_t)ti.nt[a]);
-    A.dgrp = make_fastdiv((uint32_t)(ti.nt[0] * ti.nt[1] * ZGROUP));
+    A.zgroup = ti.nt[0] * ti.nt[1] >= ZGROUP_MIN ? ZGROUP : 1;
+    A.dgrp = make_fastdiv((uint32_t)(ti.nt[0] * ti.nt[1] * A.zgroup));
     const int nb = 8 * ((ti.ntiles * split + 7) / 8);
     if (fallback_pass) {
         // a grid that fills the chip: after many steps without a sort the

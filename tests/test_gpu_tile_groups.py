@@ -1,7 +1,7 @@
-"""The order in which the push takes the tiles - groups of four layers along z,
-the last one with fewer - reaches every tile once: grids of 3, 5, 6 and 10
-layers, unequal in x and y, with one and several workgroups per tile, against
-the oracle, at both shape orders.  One step from a common state at 2e-5, as
+"""The order in which the push takes the tiles - on grids of 150 and more tiles
+per layer in groups of four layers along z, the last one with fewer, else layer
+by layer - reaches every tile once: 1 to 10 layers, unequal in x and y, with one
+and several workgroups per tile, against the oracle, at both shape orders.  One step from a common state at 2e-5, as
 elsewhere."""
 import pytest
 
@@ -12,6 +12,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,count,order", [
+    ((120, 80, 12), 6000, 1),
+    ((81, 117, 17), 6000, 1),
+    ((400, 17, 32), 6000, 2),
+    ((1200, 2, 40), 6000, 1),
     ((24, 16, 12), 40000, 1),
     ((24, 16, 12), 9000, 1),
     ((8, 24, 20), 30001, 1),
