@@ -15,9 +15,9 @@ FP64 step on the same workload is reported beside it.  The dominant kernel is
 the fused FP32 particle kernel; its roofline entry uses the algorithmic bytes
 56 per particle (28 read + 28 written) + 36 per cell (E and centred B read,
 J written) per launch over its HIP-event-timed average duration.  It reaches
-about 41 % of the 8 TB/s peak, short of a 50 % target: the kernel is
-co-limited by VALU issue (~411 instructions per particle) and its LDS
-atomics rather than by HBM (its traffic is within 9 % of the algorithmic
+about 43 % of the 8 TB/s peak, short of a 50 % target: the kernel is
+co-limited by VALU issue (~394 instructions per particle) and its LDS
+atomics rather than by HBM (its traffic is within 7 % of the algorithmic
 bytes).  The "adjoint" entry times a 50-step forward + adjoint on a 128^3 anisotropic
 plasma (see adjoint_leg); "shape_order_2" the same plasma stepped with
 second-order shapes (b_2 weighting, EZ current).  cpu_baseline: the FP64
@@ -164,9 +164,8 @@ def adjoint_leg(torch, n=128, steps=50, K=10):
 def field_only_leg(torch, n=256, steps=50):
     """The Yee update alone (Faraday + centring of B, Ampere-Maxwell) on a
     periodic vacuum grid of n^3 cells: field cell-updates/s and the HBM
-    rate of the two curl kernels (60 + 48 algorithmic bytes per cell in
-    FP32: Faraday reads E, B and writes B, B-bar and the zeroed J; Ampere
-    reads E, B, J and writes E)."""
+    rate of the kernel that does both in one pass (48 algorithmic bytes per
+    cell in FP32: E and B read once and written once)."""
     from paper_2609_16575_amd import workloads as W
     from paper_2609_16575_amd.sim import Sim
     w = W.Workload("vacuum", (n,) * 3, (1.0,) * 3, W.courant_dt((1.0,) * 3), (0, 0, 0), [])
@@ -178,11 +177,11 @@ def field_only_leg(torch, n=256, steps=50):
     torch.cuda.empty_cache()
     cells = w.n_cells
     field_ms = kt["field_ms"] / steps
-    gbs = 108.0 * cells / (field_ms * 1e-3) / 1e9
+    gbs = 48.0 * cells / (field_ms * 1e-3) / 1e9
     return {"workload": "vacuum, periodic %d^3, FP32" % n, "cell_updates_per_s": cells * steps / wall,
             "ms_per_step": 1e3 * wall / steps, "curl_kernels_ms_per_step": field_ms,
             "achieved_GBps": gbs, "frac_of_hbm": gbs / HBM_PEAK_GBS,
-            "algorithmic_bytes_per_cell": 108}
+            "algorithmic_bytes_per_cell": 48}
 
 
 def copy_calibration(torch, nbytes=1 << 30):
