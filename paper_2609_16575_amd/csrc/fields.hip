@@ -430,34 +430,38 @@ __global__ void k_j_from_fixed(GridP g, float *__restrict__ Jx, float *__restric
 }
 
 // The Mur faces of one axis from the saved planes of E^n (mur_save); points
-// that a PEC face holds at zero stay zero.
+// that a PEC face holds at zero stay zero.  One thread per point, component
+// (blockIdx.y) and face (blockIdx.z): a few thousand points with one chain of
+// loads each, those of an x face a cache line apart, so latency is what it
+// costs (box 1024 x 128 x 128: 5.4 us per launch, 15.7 with a
+// point's four updates in one thread).
+constexpr int MUR_T = 64;
 template <typename T>
-__global__ void k_mur_apply(GridP g, int a, T *Ex, T *Ey, T *Ez, const T *planes,
-                            long long pstride) {
+__global__ __launch_bounds__(MUR_T) void k_mur_apply(GridP g, int a, T *Ex, T *Ey, T *Ez,
+                                                     const T *planes, long long pstride) {
     const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
     const long long npt = (long long)g.ext[b1] * g.ext[b2];
-    const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    const long long t = blockIdx.x * (long long)MUR_T + threadIdx.x;
     if (t >= npt) return;
     const int i1 = (int)(t % g.ext[b1]), i2 = (int)(t / g.ext[b1]);
-    T *E[3] = {Ex, Ey, Ez};
-    long long st[3] = {1, g.ext[0], (long long)g.ext[0] * g.ext[1]};
+    const int ci = blockIdx.y, c = ci == 0 ? b1 : b2;
+    T *const E = c == 0 ? Ex : (c == 1 ? Ey : Ez);
+    const long long st[3] = {1, g.ext[0], (long long)g.ext[0] * g.ext[1]};
     const T coef = (T)((g.dt - g.d[a]) / (g.dt + g.d[a]));
     int idx[3];
     idx[a] = 0;
     idx[b1] = i1;
     idx[b2] = i2;
-    int ci = 0;
-    for (int c = 0; c < 3; ++c) {
-        if (c == a) continue;
-        const T *pl = planes + ((long long)a * 2 + ci) * 4 * pstride;
-        ++ci;
-        if (pec_zero(g, idx, c)) continue;
-        const long long base = st[b1] * i1 + st[b2] * i2;
+    if (pec_zero(g, idx, c)) return;
+    const T *pl = planes + ((long long)a * 2 + ci) * 4 * pstride;
+    const long long base = st[b1] * i1 + st[b2] * i2;
+    if (blockIdx.z == 0) {
         // face at index 0: E_0^{n+1} = E_1^n + coef (E_1^{n+1} - E_0^n)
-        E[c][base] = pl[1 * pstride + t] + coef * (E[c][base + st[a]] - pl[0 * pstride + t]);
+        E[base] = pl[1 * pstride + t] + coef * (E[base + st[a]] - pl[0 * pstride + t]);
+    } else {
         // face at index n: E_n^{n+1} = E_{n-1}^n + coef (E_{n-1}^{n+1} - E_n^n)
         const long long pn = base + st[a] * g.n[a];
-        E[c][pn] = pl[2 * pstride + t] + coef * (E[c][pn - st[a]] - pl[3 * pstride + t]);
+        E[pn] = pl[2 * pstride + t] + coef * (E[pn - st[a]] - pl[3 * pstride + t]);
     }
 }
 
@@ -823,8 +827,8 @@ void launch_mur_apply(const GridP &g, T *const E[3], const T *planes, long long 
         if (g.bc[a] != EMPIC_BC_ABSORBING) continue;
         const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
         const long long npt = (long long)g.ext[b1] * g.ext[b2];
-        hipLaunchKernelGGL(k_mur_apply<T>, dim3((unsigned)((npt + 255) / 256)), dim3(256), 0, s,
-                           g, a, E[0], E[1], E[2], planes, pstride);
+        hipLaunchKernelGGL(k_mur_apply<T>, dim3((unsigned)((npt + MUR_T - 1) / MUR_T), 2, 2),
+                           dim3(MUR_T), 0, s, g, a, E[0], E[1], E[2], planes, pstride);
     }
 }
 
