@@ -1348,12 +1348,15 @@ __global__ void k_rho_f32(GridP g, SpeciesP sp, double *rho) {
 
 // Diagnostics of particles still grouped by the tiles of the last sort, one
 // workgroup per tile (a workgroup strides over tiles when they outnumber the
-// partial slots): the charge density in LDS windows of nodes as int64 fixed
-// point (scale: one contribution <= 2^48), added to the global FP64 array with
-// one atomic per touched node, and (KIN) the kinetic energies before and after
-// a push that changes nothing, with E and the centred B gathered from an LDS
-// window as in the step.  Particles that drifted out of the window go through
-// global memory.
+// partial slots): the charge density in LDS windows of nodes, added to the
+// global FP64 array with one atomic per touched node, and (KIN) the kinetic
+// energies before and after a push that changes nothing, with E and the centred
+// B gathered from an LDS window as in the step.  Particles that drifted out of
+// the window go through global memory.
+// The windows hold int64 fixed point at first order (scale: one contribution
+// <= 2^48; a window is flushed every DIAG_SLICE = 2^14 particles, so that no
+// density overflows it) and FP64 at second order, whose 27 weights reach below
+// a fixed-point step where light particles lie beside heavy ones.
 // Bound by LDS atomics and FP64 issue: consecutive lanes hold particles of one
 // cell, so the charge has RHO_REP windows that the lanes take in turn.  The
 // benchmark plasma (2 x 16.8 M): a rho kernel, a kinetic kernel and a push
@@ -1361,6 +1364,23 @@ __global__ void k_rho_f32(GridP g, SpeciesP sp, double *rho) {
 // one 332 us, 305 with each thread's next particle loaded ahead (0.47 GB of
 // particles: 100 us at a copy's rate; 470 instructions per particle: 230 us).
 constexpr int DIAG_T = 512;
+constexpr int DIAG_SLICE = 1 << 14;
+template <int ORDER>
+struct RhoAcc {
+    typedef unsigned long long T;
+    static __device__ __forceinline__ T of(double v, double scale) {
+        return (T)fixed_ll(v, scale);
+    }
+    static __device__ __forceinline__ double value(T v, double inv) {
+        return (double)(long long)v * inv;
+    }
+};
+template <>
+struct RhoAcc<2> {
+    typedef double T;
+    static __device__ __forceinline__ T of(double v, double) { return v; }
+    static __device__ __forceinline__ double value(T v, double) { return v; }
+};
 struct DiagSlot {
     uint32_t c;
     float o[3], u[3], w;
@@ -1377,6 +1397,25 @@ __device__ __forceinline__ DiagSlot diag_load(const SpeciesP &sp, const float *W
     }
     return d;
 }
+// The replicas of a charge window summed and added to the global array
+template <class TL, int ORDER, int REP, int RS>
+__device__ __forceinline__ void diag_flush(const typename RhoAcc<ORDER>::T *acc,
+                                           const int (*sG)[TL::ROWS], double scale, double *rho) {
+    constexpr int FWX = TL::FWX, FWY = TL::FWY, FW3 = TL::FW3;
+    const double inv = 1.0 / scale;
+    for (int e = threadIdx.x; e < FW3; e += DIAG_T) {
+        typename RhoAcc<ORDER>::T v = acc[e];
+#pragma unroll
+        for (int k = 1; k < REP; ++k) v += acc[k * RS + e];
+        if (v == 0) continue;
+        const int lz = e / (FWX * FWY);
+        const int r2 = e - lz * (FWX * FWY);
+        const int ly = r2 / FWX, lx = r2 - ly * FWX;
+        const int gx = sG[0][lx], gy = sG[1][ly], gz = sG[2][lz];
+        if (gx < 0 || gy < 0 || gz < 0) continue;
+        atomicAdd(rho + gx + gy + gz, RhoAcc<ORDER>::value(v, inv));
+    }
+}
 template <class TL, int ORDER, bool KIN>
 __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, SpeciesP sp,
                                                        double scale, double *rho, FieldPtrs F,
@@ -1387,7 +1426,9 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
     constexpr int LHI_X = TL::LHI_X, LHI_Y = TL::LHI_Y, LHI_Z = TL::LHI_Z;
     constexpr int RHO_REP = ORDER == 1 ? 4 : 3;  // as many as leave two workgroups to a CU
     constexpr int RS = FW3 + 9;                  // replicas start in different banks
-    __shared__ unsigned long long acc[RHO_REP * RS];
+    typedef RhoAcc<ORDER> Acc;
+    typedef typename Acc::T RhoT;
+    __shared__ RhoT acc[RHO_REP * RS];
     __shared__ float sF[KIN ? 6 * FW3 : 1];
     __shared__ int sG[3][ROWS];
     __shared__ double sm[16];
@@ -1421,7 +1462,7 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
                 sG[a][l] = gi < 0 ? -1 : gi * mul;
             }
         }
-        for (int e = tid; e < RHO_REP * RS; e += DIAG_T) acc[e] = 0ull;
+        for (int e = tid; e < RHO_REP * RS; e += DIAG_T) acc[e] = RhoT(0);
         __syncthreads();
         if constexpr (KIN) {
             constexpr int NR = (FW3 + DIAG_T - 1) / DIAG_T;
@@ -1445,8 +1486,17 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
                     if (tid + k * DIAG_T < FW3) sF[c * FW3 + tid + k * DIAG_T] = tmp[c][k];
             __syncthreads();
         }
-        unsigned long long *ac = acc + (tid % RHO_REP) * RS;
-        for (int p = beg + tid; p < end; p += DIAG_T) {
+        RhoT *ac = acc + (tid % RHO_REP) * RS;
+        for (int p0 = beg; p0 < end; p0 += DIAG_T) {
+            if (ORDER == 1 && p0 != beg && ((p0 - beg) & (DIAG_SLICE - 1)) == 0) {
+                __syncthreads();
+                diag_flush<TL, ORDER, RHO_REP, RS>(acc, sG, scale, rho);
+                __syncthreads();
+                for (int e = tid; e < RHO_REP * RS; e += DIAG_T) acc[e] = RhoT(0);
+                __syncthreads();
+            }
+            const int p = p0 + tid;
+            if (p >= end) continue;
             const DiagSlot cur = nx;
             if (p + DIAG_T < end) nx = diag_load<KIN>(sp, WP, p + DIAG_T);
             const uint32_t c = cur.c;
@@ -1487,8 +1537,7 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
 #pragma unroll
                         for (int i = 0; i < NP; ++i) {
                             const double wt = w[0][i] * w[1][j] * w[2][k];
-                            atomicAdd(ac + b + i + FWX * (j + FWY * k),
-                                      (unsigned long long)fixed_ll(amp * wt, scale));
+                            atomicAdd(ac + b + i + FWX * (j + FWY * k), Acc::of(amp * wt, scale));
                         }
             } else {
                 for (int k = 0; k < NP; ++k) {
@@ -1523,19 +1572,7 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
             }
         }
         __syncthreads();
-        const double inv = 1.0 / scale;
-        for (int e = tid; e < FW3; e += DIAG_T) {
-            unsigned long long v = acc[e];
-#pragma unroll
-            for (int k = 1; k < RHO_REP; ++k) v += acc[k * RS + e];
-            if (v == 0) continue;
-            const int lz = e / (FWX * FWY);
-            const int r2 = e - lz * (FWX * FWY);
-            const int ly = r2 / FWX, lx = r2 - ly * FWX;
-            const int gx = sG[0][lx], gy = sG[1][ly], gz = sG[2][lz];
-            if (gx < 0 || gy < 0 || gz < 0) continue;
-            atomicAdd(rho + gx + gy + gz, (double)(long long)v * inv);
-        }
+        diag_flush<TL, ORDER, RHO_REP, RS>(acc, sG, scale, rho);
         __syncthreads();
     }
     if constexpr (KIN) {
