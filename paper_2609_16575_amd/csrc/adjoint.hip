@@ -102,15 +102,19 @@ __device__ __forceinline__ void tri_vg(const Acc &a, int q, int i, int j, int k,
     gr[0] = lerpf(lerpf(v1 - v0, v3 - v2, fy), lerpf(v5 - v4, v7 - v6, fy), fz);
 }
 
-// corner and fractions of component q (E0..2, Bbar0..2) on its staggered
-// sub-grid for a particle at offset o in cell l (any coordinates): E_a is
-// half-staggered along a, Bbar_a along the two other axes
+// component q (E0..2, Bbar0..2) lies at half-cell points along axis a: E_a along
+// a, Bbar_a along the two other axes
+__device__ __forceinline__ bool half_staggered(int q, int a) {
+    return q < 3 ? a == q : a != q - 3;
+}
+
+// corner and fractions of component q on its staggered sub-grid for a particle
+// at offset o in cell l (any coordinates)
 __device__ __forceinline__ void stagger(int q, const int l[3], const float o[3], int c[3],
                                         float f[3]) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const bool half = q < 3 ? (a == q) : (a != q - 3);
-        if (half) {
+        if (half_staggered(q, a)) {
             half_axis(o[a], l[a], c[a], f[a]);
         } else {
             c[a] = l[a];
@@ -387,7 +391,7 @@ __device__ __forceinline__ void window_rows(const GridP &g, const int wo[3],
     }
 }
 
-// the workgroup's tile and its slice of it (split workgroups per tile)
+// the workgroup's tile and its part of it (split workgroups per tile)
 template <class TL>
 __device__ __forceinline__ int tile_of_block(const TileInfo &ti, int split, int wo[3], int &part) {
     constexpr int TX = TL::TX, TY = TL::TY, TZ = TL::TZ;
@@ -587,27 +591,30 @@ __global__ __launch_bounds__(ADJ_THREADS, 3) void k_adj_particles(AdjArgs A, Adj
     }
 }
 
-// Pass 2, one workgroup per tile: the gather scatter of pass 1's lam_Ep,
-// lam_Bp onto the six Yee sub-grids, accumulated in an int64 LDS window in
-// units of 2^(tile_exp - 31): every contribution is below 2^31 there and is
-// rounded to an int32 (error <= 2^-32 of the tile's largest |lam|); one
-// entry takes at most one contribution per particle, so the sum cannot
-// overflow.  A lane takes SPPT consecutive particles and the lanes of a wave
-// are SPPT x 8 = 32 particles apart, in different cells.
-template <class TL>
+// Pass 2: the gather scatter of pass 1's lam_Ep, lam_Bp onto the six Yee
+// sub-grids, accumulated in an int64 LDS window in units of 2^(tile_exp - 31):
+// every contribution is below 2^31 there and is rounded to an int32 (error <=
+// 2^-32 of the tile's largest |lam|); one entry takes at most one contribution
+// per particle, so the sum cannot overflow.  A lane takes SPPT consecutive
+// particles and the lanes of a wave are SPPT x 8 = 32 particles apart, in
+// different cells.  On small grids a tile's six components are shared out to
+// 6 / NC workgroups of NC each: a component's window is summed by one of them
+// and rounded to FP32 once, whatever NC (slices of the particles, each rounded
+// by itself, gave up to eight FP32 partial sums in any order).
+template <class TL, int NC>
 __global__ __launch_bounds__(SCAT_THREADS) void k_adj_scatter(AdjArgs A, AdjSpecies S) {
     constexpr int FWX = TL::FWX, FWY = TL::FWY, FW3 = TL::FW3;
     // LDS layout of the window: row, plane and component strides (words)
     constexpr int RX = FWX, PS = FWX * FWY, CS = FW3;
-    __shared__ unsigned long long sA[6 * CS];
+    __shared__ unsigned long long sA[NC * CS];
     __shared__ int sG[3][TL::ROWS];
 
     const GridP &g = A.g;
     int wo[3], part;
-    const int tile = tile_of_block<TL>(A.ti, A.split.n, wo, part);
+    const int tile = tile_of_block<TL>(A.ti, 6 / NC, wo, part);
     if (tile >= A.ti.ntiles) return;
-    int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
-    A.split.slice(part, beg, end);
+    const int q0 = NC == 6 ? 0 : part * NC;  // the workgroup's first component
+    const int beg = S.tile_off[tile], end = S.tile_off[tile + 1];
     if (beg >= end) return;
     int et = A.tile_exp[tile * A.exps];
     for (int k = 1; k < A.exps; ++k) et = max(et, A.tile_exp[tile * A.exps + k]);
@@ -615,18 +622,18 @@ __global__ __launch_bounds__(SCAT_THREADS) void k_adj_scatter(AdjArgs A, AdjSpec
     const int ee = max(et, -96);  // keeps the scale a finite float
     const int tid = threadIdx.x;
     window_rows<TL>(g, wo, sG);
-    for (int e = tid; e < 6 * CS; e += SCAT_THREADS) sA[e] = 0ull;
+    for (int e = tid; e < NC * CS; e += SCAT_THREADS) sA[e] = 0ull;
     __syncthreads();
     constexpr int LHI_X = TL::LHI_X, LHI_Y = TL::LHI_Y, LHI_Z = TL::LHI_Z;
     const float scale = ldexpf(1.f, EB - ee);  // at most 2^127
-    const int q0 = (tid & 63) * (SPPT * (SCAT_THREADS / 64)) + (tid >> 6) * SPPT;
-    for (int base = (beg & ~(SPPT - 1)) + q0; base < end; base += SCAT_THREADS * SPPT) {
+    const int s0 = (tid & 63) * (SPPT * (SCAT_THREADS / 64)) + (tid >> 6) * SPPT;
+    for (int base = (beg & ~(SPPT - 1)) + s0; base < end; base += SCAT_THREADS * SPPT) {
         const vuS c4 = *(const vuS *)(S.cell + base);
         const vfS ox4 = *(const vfS *)(S.pos[0] + base), oy4 = *(const vfS *)(S.pos[1] + base),
                   oz4 = *(const vfS *)(S.pos[2] + base);
-        vfS l64[6];
+        vfS l64[NC];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) l64[q] = *(const vfS *)(A.l6[q] + base);
+        for (int q = 0; q < NC; ++q) l64[q] = *(const vfS *)(A.l6[q0 + q] + base);
 #pragma unroll
         for (int k = 0; k < SPPT; ++k) {
             const int p = base + k;
@@ -639,12 +646,12 @@ __global__ __launch_bounds__(SCAT_THREADS) void k_adj_scatter(AdjArgs A, AdjSpec
                 continue;  // handled by k_adj_fallback
             const float o[3] = {ox4[k], oy4[k], oz4[k]};
 #pragma unroll
-            for (int q = 0; q < 6; ++q) {
+            for (int q = 0; q < NC; ++q) {
                 const float v = l64[q][k];
                 if (v == 0.f) continue;
                 int cq[3];
                 float f[3], w[8];
-                stagger(q, wl, o, cq, f);
+                stagger(q0 + q, wl, o, cq, f);
                 tri_weights(f, v * scale, w);  // exact power-of-two scaling
                 unsigned long long *dst = sA + q * CS + cq[0] + RX * cq[1] + PS * cq[2];
 #pragma unroll
@@ -663,9 +670,10 @@ __global__ __launch_bounds__(SCAT_THREADS) void k_adj_scatter(AdjArgs A, AdjSpec
         const int ly = r2 / FWX, lx = r2 - ly * FWX;
         const int o = sG[0][lx] + sG[1][ly] + sG[2][lz];
 #pragma unroll
-        for (int comp = 0; comp < 6; ++comp) {
-            const long long fx = (long long)sA[comp * CS + lx + RX * ly + PS * lz];
+        for (int q = 0; q < NC; ++q) {
+            const long long fx = (long long)sA[q * CS + lx + RX * ly + PS * lz];
             if (fx == 0) continue;
+            const int comp = q0 + q;
             float *dst = comp < 3 ? A.lEg[comp] : A.lBb[comp - 3];
             atomicAdd(dst + o, (float)((double)fx * inv));
         }
@@ -808,6 +816,15 @@ __global__ void k_zero6(Lam6 z, long long n, int vec, unsigned *count) {
 
 }  // namespace
 
+namespace {
+template <class TL>
+void (*scatter_kernel(int groups))(AdjArgs, AdjSpecies) {
+    return groups == 1 ? k_adj_scatter<TL, 6>
+                       : (groups == 2 ? k_adj_scatter<TL, 3>
+                                      : (groups == 3 ? k_adj_scatter<TL, 2> : k_adj_scatter<TL, 1>));
+}
+}  // namespace
+
 void launch_step_vjp(const GridP &g, const TileInfo &ti, float *const E[3], float *const Bbar[3],
                      float *const lE[3], float *const lJdep[3], float *const lB[3],
                      float *const lEg[3],
@@ -850,6 +867,7 @@ void launch_step_vjp(const GridP &g, const TileInfo &ti, float *const E[3], floa
         const long long avg = sp[i].capacity / ti.ntiles;
         const int split1 = tile_split(ti.ntiles, avg, ADJ_SLOTS, 256);
         const int split2 = tile_split(ti.ntiles, avg, SCAT_SLOTS, 512);
+        const int groups = split2 >= 6 ? 6 : (split2 >= 3 ? 3 : split2);
         A.split.n = A.exps = split1;
         AdjSpecies S;
         S.cell = sp[i].cell;
@@ -875,13 +893,8 @@ void launch_step_vjp(const GridP &g, const TileInfo &ti, float *const E[3], floa
         const long long words = (sp[i].capacity + 31) / 32;
         hipLaunchKernelGGL(k_adj_fallback, dim3((unsigned)std::min(1024LL, (words + 255) / 256)),
                            dim3(256), 0, s, A, S, words);
-        A.split.n = split2;
-        if (ti.slab)
-            hipLaunchKernelGGL(k_adj_scatter<TileSlab>, blocks(split2), dim3(SCAT_THREADS), 0, s,
-                               A, S);
-        else
-            hipLaunchKernelGGL(k_adj_scatter<TileCube>, blocks(split2), dim3(SCAT_THREADS), 0, s,
-                               A, S);
+        hipLaunchKernelGGL(ti.slab ? scatter_kernel<TileSlab>(groups) : scatter_kernel<TileCube>(groups),
+                           blocks(groups), dim3(SCAT_THREADS), 0, s, A, S);
     }
     const dim3 grid((g.n[0] + 63) / 64, (g.n[1] + 3) / 4, g.n[2]);
     hipLaunchKernelGGL(k_adj_bprime, grid, dim3(64, 4), 0, s, g, lE[0], lE[1], lE[2], lB[0], lB[1],

@@ -148,9 +148,10 @@ struct TileInfo {
 };
 
 // Small grids: `split` workgroups share a tile, each with its own windows and a
-// slice of every species' particles (the windows' sums are integers or have
-// exponents of their own, so nothing depends on the split).  Slice `part` of
-// particles [beg, end), cut at multiples of four slots.
+// slice of every species' particles (the step's window sums are integers of one
+// scale and the adjoint's tile exponents maxima over the slices, so no result
+// depends on the split).  Slice `part` of particles [beg, end), cut at multiples
+// of four slots.
 struct TileSplit {
     int n = 1;
     __device__ void slice(int part, int &beg, int &end) const {
