@@ -1393,6 +1393,7 @@ empic_status empic_step_state(empic_sim *s, const empic_state *src, const empic_
         launch_copy6(from, to, s->g.V, s->stream);
     }
     // species table: set 0 = source state, set 1 = destination state
+    const int32_t *toff[EMPIC_MAX_SPECIES] = {};
     const size_t tw = ((size_t)s->ti.ntiles + 2) * 4;
     for (int i = 0; i < s->nsp; ++i) {
         const SpeciesState &S = s->sp[i];
@@ -1407,8 +1408,13 @@ empic_status empic_step_state(empic_sim *s, const empic_state *src, const empic_
             }
             p.id = st[k]->id[i];
             p.w = S.desc.per_particle_w ? st[k]->w[i] : nullptr;
-            p.tile_off = st[k]->tiles[i];
-            p.count = st[k]->tiles[i] ? st[k]->tiles[i] + s->ti.ntiles + 1 : nullptr;
+            // a species without slots has no arrays in a state: species_params'
+            // offsets and count, which are the handle's own and empty
+            if (S.capacity > 0) {
+                p.tile_off = st[k]->tiles[i];
+                p.count = st[k]->tiles[i] + s->ti.ntiles + 1;
+            }
+            if (k == 0) toff[i] = p.tile_off;
             D.p[k] = p;
         }
         fill_species_consts(D, s->g, S.desc.q, S.desc.m, S.desc.per_particle_w ? 1.0 : S.desc.w);
@@ -1430,10 +1436,6 @@ empic_status empic_step_state(empic_sim *s, const empic_state *src, const empic_
         s->E[a] = dst->E[a];
         s->B[a] = dst->B[a];
     }
-    // a species without slots has no arrays in a state: its own (empty) offsets
-    const int32_t *toff[EMPIC_MAX_SPECIES] = {};
-    for (int i = 0; i < s->nsp; ++i)
-        toff[i] = src->tiles[i] ? src->tiles[i] : s->sp[i].tile_off;
     one_step<float>(s, s->xtable, 0, (int)((1u << s->nsp) - 1u), nullptr, toff);
     for (int a = 0; a < 3; ++a) {
         s->E[a] = E0[a];
