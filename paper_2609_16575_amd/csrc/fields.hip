@@ -923,7 +923,9 @@ template <typename T>
 void launch_laser(const GridP &g, T *const E[3], const empic_laser_desc &L, double t_half,
                   hipStream_t s) {
     const int cz = g.bc[2] != EMPIC_BC_PERIODIC ? g.n[2] + 1 : g.n[2];
-    hipLaunchKernelGGL(k_laser<T>, dim3((g.n[1] + 63) / 64, cz), dim3(64), 0, s, g, E[1], L,
+    empic_laser_desc P = L;
+    if (g.bc[0] == EMPIC_BC_PERIODIC && P.i_s == g.n[0]) P.i_s = 0;  // the same node plane
+    hipLaunchKernelGGL(k_laser<T>, dim3((g.n[1] + 63) / 64, cz), dim3(64), 0, s, g, E[1], P,
                        t_half);
 }
 
