@@ -346,7 +346,7 @@ void launch_sort(const GridP &g, const TileInfo &ti, const SpeciesP &cur, const 
                  int32_t *counts, int32_t *scan_blocks, int32_t *rank, int32_t *tile_off,
                  uint32_t *fault, bool tiles_valid, int32_t *perm, hipStream_t s);
 
-// FP64 plain path.  counts: at least 3 ntiles + 1 words for 8 x 8 x 4 tiles,
+// FP64 plain path.  counts: at least 4 ntiles + 2 words for 8 x 8 x 4 tiles,
 // zero before the first call (and left so in their first ntiles); slots: one
 // word per particle
 void launch_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],

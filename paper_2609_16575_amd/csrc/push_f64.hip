@@ -11,8 +11,8 @@
 // atomics.
 // k_bin_* and k_push_f64_tiles: the particles' slots are first binned by 8 x 8
 // x 4 tiles of cells into an index list (two passes over the positions; the
-// particles themselves stay where they are), then one workgroup per tile
-// pushes its particles from LDS windows of E, B and J.  Global FP64 atomics
+// particles themselves stay where they are), then a workgroup per tile, or per
+// slice of a dense one, pushes its particles from LDS windows of E, B and J.  Global FP64 atomics
 // are what bounds the direct kernel: 24 G/s on scattered addresses, against
 // 1600-2200 G/s for FP64 atomics in LDS.  64^3 cells, 2 x 2.1 M particles: see
 // F64_TILED_MIN below.
@@ -266,7 +266,9 @@ struct Tiles64 {
     int nt[3];
     int ntiles;
     int32_t *counts, *offs, *cursor;  // ntiles, ntiles + 1, ntiles
+    int32_t *more;                    // slices beyond the first of the tiles before, ntiles + 1
     int32_t *perm;                    // slots grouped by tile
+    int slice;                        // particles of one workgroup of the push
 };
 
 // tile of slot p, -1: skipped (NaN)
@@ -321,45 +323,65 @@ __global__ __launch_bounds__(BIN_T) void k_bin(GridP g, Tiles64 t, SpeciesP sp, 
     }
 }
 
-// exclusive scan of the populations into offs and cursor (one workgroup); the
+// exclusive scans of the populations into offs and cursor, and of the slices
+// beyond a tile's first into more (one workgroup, both in one 64-bit scan); the
 // populations are cleared for the next species or step
 __global__ __launch_bounds__(1024) void k_bin_scan(Tiles64 t) {
-    __shared__ int sm[16];
-    int carry = 0;
+    __shared__ unsigned long long sm[16];
+    unsigned long long carry = 0;
     for (int base = 0; base < t.ntiles; base += 1024) {
         const int e = base + threadIdx.x;
-        const int v = e < t.ntiles ? t.counts[e] : 0;
+        const unsigned n = e < t.ntiles ? (unsigned)t.counts[e] : 0u;
+        const unsigned long long v =
+            n ? n | (unsigned long long)((n - 1u) / (unsigned)t.slice) << 32 : 0ull;
         const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-        int x = v;
+        unsigned long long x = v;
         for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(x, o, 64);
+            const unsigned long long y = __shfl_up(x, o, 64);
             if (lane >= o) x += y;
         }
         if (lane == 63) sm[wid] = x;
         __syncthreads();
-        int off = carry, tot = 0;
+        unsigned long long off = carry, tot = 0;
         for (int w = 0; w < 16; ++w) {
             if (w < wid) off += sm[w];
             tot += sm[w];
         }
         __syncthreads();
         if (e < t.ntiles) {
-            t.offs[e] = t.cursor[e] = off + x - v;
+            const unsigned long long b = off + x - v;
+            t.offs[e] = t.cursor[e] = (int32_t)b;
+            t.more[e] = (int32_t)(b >> 32);
             t.counts[e] = 0;
         }
         carry += tot;
     }
-    if (threadIdx.x == 0) t.offs[t.ntiles] = carry;
+    if (threadIdx.x == 0) {
+        t.offs[t.ntiles] = (int32_t)carry;
+        t.more[t.ntiles] = (int32_t)(carry >> 32);
+    }
 }
 
 __global__ __launch_bounds__(256, 2) void k_push_f64_tiles(GridP g, F64Args A, Tiles64 t,
                                                            SpeciesP sp, uint32_t *fault) {
     __shared__ double sF[6 * F64V];
     __shared__ double sJ[3 * J64V];
-    const int nb8 = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);  // XCD-contiguous tiles
+    // first the tiles' first slices, XCD-contiguous, then the others in turn
+    const int nb8 = (t.ntiles + 7) / 8;
+    int tile = ((int)blockIdx.x & 7) * nb8 + ((int)blockIdx.x >> 3), part = 0;
+    if ((int)blockIdx.x >= 8 * nb8) {
+        const int q = (int)blockIdx.x - 8 * nb8;
+        if (q >= t.more[t.ntiles]) return;
+        tile = 0;  // the last tile with more[tile] <= q
+        for (int hi = t.ntiles; hi - tile > 1;) {
+            const int mid = (tile + hi) >> 1;
+            if (t.more[mid] <= q) tile = mid;
+            else hi = mid;
+        }
+        part = q - t.more[tile] + 1;
+    }
     if (tile >= t.ntiles) return;
-    const int beg = t.offs[tile], end = t.offs[tile + 1];
+    const int beg = t.offs[tile] + part * t.slice, end = min(t.offs[tile + 1], beg + t.slice);
     if (beg >= end) return;
     const int tx = tile % t.nt[0], tyz = tile / t.nt[0];
     const int org[3] = {tx * T64X, (tyz % t.nt[1]) * T64Y, (tyz / t.nt[1]) * T64Z};
@@ -548,35 +570,46 @@ F64Args args64(const GridP &g, double *const E[3], double *const Bbar[3], double
 }
 }  // namespace
 
-// From this many particles on the binned path is taken.  One step of 8
-// particles per cell, fresh and after 600 steps of mixing (direct | binned):
-// 55 k particles (4 per cell): 49, 43 | 62, 60 us (its four launches cost more than it saves);
-// 131 k: 94, 77 | 64, 63; 2.1 M: 1133, 868 | 156, 183; 7.1 M: 3914, 2854 |
-// 486, 667.  (2.1 M took 2912 us for the push alone with 64-bit modulo index
-// arithmetic and 24 global atomics per particle.)  The binned push is bound by
-// its scattered 8-byte particle accesses once the plasma has mixed: the
-// storage order is the caller's.
-constexpr long long F64_TILED_MIN = 98304;
+// From this many particles on, and this many per tile, the binned path is taken.
+// One step of 8 particles per cell, fresh and after 600 steps of mixing (direct |
+// binned): 55 k particles (4 per cell): 49, 43 | 62, 60 us (its four launches cost
+// more than it saves); 131 k: 94, 77 | 64, 63; 2.1 M: 1133, 868 | 156, 183; 7.1 M:
+// 3914, 2854 | 486, 667.  (2.1 M took 2912 us for the push alone with 64-bit modulo
+// index arithmetic and 24 global atomics per particle.)  On sparse grids the
+// windows cost more than they save, 256^3: 12 per tile 1684 | 1826 us, 24: 2463 |
+// 2082; 128^3: 12 per tile 158 | 195, 24: 269 | 210; 512 x 2 x 512: 103 | 148, 198 | 153.
+// The binned push is bound by its scattered 8-byte particle accesses once the
+// plasma has mixed: the storage order is the caller's.
+constexpr long long F64_TILED_MIN = 98304, F64_TILE_MIN = 20;
+// A tile's particles are pushed in slices of 1 / F64_SLICES of all of them, by a
+// workgroup each: a plasma that fills a few tiles has them share the chip, an even
+// one of as many tiles is left whole (every slice loads and flushes the windows).
+// Whole tiles | slices for 128, 256, 512 workgroups: 1 M on 8 x 8 x 4 11500 | 166, 143,
+// 136 us; 3.2 M on 16^3 2634 | 473, 550, 516; 2 M in 8^3 cells of 128^3 11076 | 572, 418,
+// 341; 3.2 M on 32^3 542 | 546, 655, 644.
+constexpr long long F64_SLICES = 128, F64_SLICE_MIN = 1024;
 
 void launch_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
                      double *const J[3], const SpeciesP &sp, long long count, int32_t *counts,
                      int32_t *slots, uint32_t *fault, hipStream_t s) {
     if (count <= 0) return;
     const F64Args A = args64(g, E, Bbar, J, sp);
-    if (count < F64_TILED_MIN) {
-        hipLaunchKernelGGL(k_push_f64<false>, dim3(nblk(count, 256)), dim3(256), 0, s, g, A, sp,
-                           count, fault, nullptr);
-        return;
-    }
     Tiles64 t;
     t.nt[0] = (g.n[0] + T64X - 1) / T64X;
     t.nt[1] = (g.n[1] + T64Y - 1) / T64Y;
     t.nt[2] = (g.n[2] + T64Z - 1) / T64Z;
     t.ntiles = t.nt[0] * t.nt[1] * t.nt[2];
+    if (count < F64_TILED_MIN || count < F64_TILE_MIN * t.ntiles) {
+        hipLaunchKernelGGL(k_push_f64<false>, dim3(nblk(count, 256)), dim3(256), 0, s, g, A, sp,
+                           count, fault, nullptr);
+        return;
+    }
     t.counts = counts;
     t.offs = counts + t.ntiles;
     t.cursor = t.offs + t.ntiles + 1;
+    t.more = t.cursor + t.ntiles;
     t.perm = slots;
+    t.slice = (int)(count / F64_SLICES > F64_SLICE_MIN ? count / F64_SLICES : F64_SLICE_MIN);
     const dim3 nb(nblk(count, BIN_T * BIN_PER));
     const bool lds = t.ntiles <= BIN_LDS;
     const unsigned shm = lds ? (unsigned)t.ntiles * 4u : 0u;
@@ -585,8 +618,10 @@ void launch_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
     hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, t);
     hipLaunchKernelGGL(lds ? (k_bin<true, true>) : (k_bin<true, false>), nb, dim3(BIN_T), shm, s, g,
                        t, sp, count);
-    hipLaunchKernelGGL(k_push_f64_tiles, dim3(8 * ((t.ntiles + 7) / 8)), dim3(256), 0, s, g, A, t,
-                       sp, fault);
+    // (the tiles' slices beyond their first are at most count / slice)
+    hipLaunchKernelGGL(k_push_f64_tiles,
+                       dim3((unsigned)(8 * ((t.ntiles + 7) / 8) + count / t.slice)), dim3(256), 0,
+                       s, g, A, t, sp, fault);
 }
 
 void launch_dry_push_f64(const GridP &g, double *const E[3], double *const Bbar[3],
