@@ -1022,6 +1022,13 @@ static double rho_scale(const empic_sim *s, int i) {
     return std::ldexp(1.0, (int)std::fmax(-1000.0, std::fmin(1000.0, e)));
 }
 
+// Charge density of an FP32 species: by tiles where that pays, else directly
+static void rho_f32(empic_sim *s, int i, const SpeciesP &p, double *rho) {
+    if (!launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, s->sp[i].host_count, rho_scale(s, i),
+                           p, rho, nullptr, nullptr, nullptr, nullptr, s->fault, s->stream))
+        launch_rho_f32(s->g, p, rho, s->stream);
+}
+
 empic_status empic_deposit_rho(empic_sim *s, int32_t sp, double *rho_out) {
     EMPIC_GUARD(s);
     if (!rho_out || sp < -1 || sp >= s->nsp) return fail(s, EMPIC_E_ARG, "bad rho arguments");
@@ -1031,9 +1038,8 @@ empic_status empic_deposit_rho(empic_sim *s, int32_t sp, double *rho_out) {
         const SpeciesP p = species_params(s, i, s->sp[i].cur);
         if (fp64(s))
             launch_rho_f64(s->g, p, s->sp[i].host_count, rho_out, s->stream);
-        else if (!launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, rho_scale(s, i), p, rho_out,
-                                    nullptr, nullptr, nullptr, nullptr, s->fault, s->stream))
-            launch_rho_f32(s->g, p, rho_out, s->stream);
+        else
+            rho_f32(s, i, p, rho_out);
     }
     return check_launch(s, "deposit_rho");
 }
@@ -1069,10 +1075,10 @@ empic_status empic_diagnostics(empic_sim *s, empic_diag *out) {
         for (int i = 0; i < s->nsp; ++i) {
             const SpeciesP p = species_params(s, i, s->sp[i].cur);
             double *km = s->partials + (Q_KM + i) * PSTRIDE, *kp = s->partials + (Q_KP + i) * PSTRIDE;
-            if (launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, rho_scale(s, i), p, s->rho_cur,
-                                  E, Bb, km, kp, s->fault, s->stream))
+            if (launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, s->sp[i].host_count,
+                                  rho_scale(s, i), p, s->rho_cur, E, Bb, km, kp, s->fault, s->stream))
                 continue;
-            launch_rho_f32(s->g, p, s->rho_cur, s->stream);
+            rho_f32(s, i, p, s->rho_cur);
             launch_kinetic_f32(p, km, s->stream);
             launch_dry_push_f32(s->g, E, Bb, p, kp, s->fault, s->stream);
         }

@@ -326,14 +326,16 @@ void launch_dry_push_f32(const GridP &g, float *const E[3], float *const Bbar[3]
                          const SpeciesP &sp, double *partial_slot, uint32_t *fault,
                          hipStream_t s);
 void launch_kinetic_f32(const SpeciesP &sp, double *partial_slot, hipStream_t s);
-// Charge density of an FP32 species added to rho (FP64 nodes).  Tile-grouped
-// particles (tiles_valid; false is returned otherwise) are accumulated per tile
+// Charge density of an FP32 species of `count` particles added to rho (FP64
+// nodes).  Tile-grouped particles (tiles_valid; false is returned otherwise, and
+// where the general kernels are faster) are accumulated per tile, at first order
 // in fixed point at `scale` (a power of two with one particle's contribution
 // below 2^48); with E and Bbar (or null) the same pass writes the kinetic
 // energies before and after a push to the partial slots.
-bool launch_diag_tiles(const GridP &g, const TileInfo &ti, bool tiles_valid, double scale,
-                       const SpeciesP &sp, double *rho, float *const E[3], float *const Bbar[3],
-                       double *part_m, double *part_p, uint32_t *fault, hipStream_t s);
+bool launch_diag_tiles(const GridP &g, const TileInfo &ti, bool tiles_valid, long long count,
+                       double scale, const SpeciesP &sp, double *rho, float *const E[3],
+                       float *const Bbar[3], double *part_m, double *part_p, uint32_t *fault,
+                       hipStream_t s);
 void launch_rho_f32(const GridP &g, const SpeciesP &sp, double *rho, hipStream_t s);
 void launch_load_f32(const GridP &g, const SpeciesP &sp, long long count, const double *pos,
                      const double *u, const double *w, const int32_t *ids, uint32_t *fault,

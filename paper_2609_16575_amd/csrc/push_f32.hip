@@ -1358,11 +1358,13 @@ __global__ void k_rho_f32(GridP g, SpeciesP sp, double *rho) {
 // density overflows it) and FP64 at second order, whose 27 weights reach below
 // a fixed-point step where light particles lie beside heavy ones.
 // Bound by LDS atomics and FP64 issue: consecutive lanes hold particles of one
-// cell, so the charge has RHO_REP windows that the lanes take in turn.  The
+// cell, so the charge has REP windows that the lanes take in turn.  The
 // benchmark plasma (2 x 16.8 M): a rho kernel, a kinetic kernel and a push
 // that gathered from global memory took 218 + 83 + 1151 us per species; this
-// one 332 us, 305 with each thread's next particle loaded ahead (0.47 GB of
-// particles: 100 us at a copy's rate; 470 instructions per particle: 230 us).
+// one 332 us, 305 with each thread's next particle loaded ahead (AHEAD; 0.47 GB
+// of particles: 100 us at a copy's rate; 470 instructions per particle: 230 us).
+// Sparse tiles are bound by the latency of a workgroup's phases: the charge
+// alone takes smaller workgroups there, see diag_tiles.
 constexpr int DIAG_T = 512;
 constexpr int DIAG_SLICE = 1 << 14;
 template <int ORDER>
@@ -1398,12 +1400,12 @@ __device__ __forceinline__ DiagSlot diag_load(const SpeciesP &sp, const float *W
     return d;
 }
 // The replicas of a charge window summed and added to the global array
-template <class TL, int ORDER, int REP, int RS>
+template <class TL, int ORDER, int T, int REP, int RS>
 __device__ __forceinline__ void diag_flush(const typename RhoAcc<ORDER>::T *acc,
                                            const int (*sG)[TL::ROWS], double scale, double *rho) {
     constexpr int FWX = TL::FWX, FWY = TL::FWY, FW3 = TL::FW3;
     const double inv = 1.0 / scale;
-    for (int e = threadIdx.x; e < FW3; e += DIAG_T) {
+    for (int e = threadIdx.x; e < FW3; e += T) {
         typename RhoAcc<ORDER>::T v = acc[e];
 #pragma unroll
         for (int k = 1; k < REP; ++k) v += acc[k * RS + e];
@@ -1416,19 +1418,18 @@ __device__ __forceinline__ void diag_flush(const typename RhoAcc<ORDER>::T *acc,
         atomicAdd(rho + gx + gy + gz, RhoAcc<ORDER>::value(v, inv));
     }
 }
-template <class TL, int ORDER, bool KIN>
-__global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, SpeciesP sp,
+template <class TL, int ORDER, bool KIN, int T, int REP, bool AHEAD>
+__global__ __launch_bounds__(T, 4) void k_diag_tiles(GridP g, TileInfo ti, SpeciesP sp,
                                                        double scale, double *rho, FieldPtrs F,
                                                        float r, float r_lo, double *part_m,
                                                        double *part_p, uint32_t *fault) {
     constexpr int TX = TL::TX, TY = TL::TY, TZ = TL::TZ;
     constexpr int FWX = TL::FWX, FWY = TL::FWY, FWZ = TL::FWZ, FW3 = TL::FW3, ROWS = TL::ROWS;
     constexpr int LHI_X = TL::LHI_X, LHI_Y = TL::LHI_Y, LHI_Z = TL::LHI_Z;
-    constexpr int RHO_REP = ORDER == 1 ? 4 : 3;  // as many as leave two workgroups to a CU
     constexpr int RS = FW3 + 9;                  // replicas start in different banks
     typedef RhoAcc<ORDER> Acc;
     typedef typename Acc::T RhoT;
-    __shared__ RhoT acc[RHO_REP * RS];
+    __shared__ RhoT acc[REP * RS];
     __shared__ float sF[KIN ? 6 * FW3 : 1];
     __shared__ int sG[3][ROWS];
     __shared__ double sm[16];
@@ -1448,7 +1449,7 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
         // a particle ahead: the loads of the first are under way with the window's,
         // those of the next one while this one is worked on
         DiagSlot nx;
-        if (beg + tid < end) nx = diag_load<KIN>(sp, WP, beg + tid);
+        if (AHEAD && beg + tid < end) nx = diag_load<KIN>(sp, WP, beg + tid);
         const int tx = tile % ti.nt[0];
         const int tyz = tile / ti.nt[0];
         const int ty = tyz % ti.nt[1], tz = tyz / ti.nt[1];
@@ -1462,14 +1463,14 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
                 sG[a][l] = gi < 0 ? -1 : gi * mul;
             }
         }
-        for (int e = tid; e < RHO_REP * RS; e += DIAG_T) acc[e] = RhoT(0);
+        for (int e = tid; e < REP * RS; e += T) acc[e] = RhoT(0);
         __syncthreads();
         if constexpr (KIN) {
-            constexpr int NR = (FW3 + DIAG_T - 1) / DIAG_T;
+            constexpr int NR = (FW3 + T - 1) / T;
             float tmp[6][NR];
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
-                const int e = tid + k * DIAG_T;
+                const int e = tid + k * T;
                 const int lz = e / (FWX * FWY), r2 = e - lz * (FWX * FWY);
                 const int ly = r2 / FWX, lx = r2 - ly * FWX;
                 int o = -1;
@@ -1483,22 +1484,22 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
             for (int k = 0; k < NR; ++k)
 #pragma unroll
                 for (int c = 0; c < 6; ++c)
-                    if (tid + k * DIAG_T < FW3) sF[c * FW3 + tid + k * DIAG_T] = tmp[c][k];
+                    if (tid + k * T < FW3) sF[c * FW3 + tid + k * T] = tmp[c][k];
             __syncthreads();
         }
-        RhoT *ac = acc + (tid % RHO_REP) * RS;
-        for (int p0 = beg; p0 < end; p0 += DIAG_T) {
+        RhoT *ac = acc + (tid % REP) * RS;
+        for (int p0 = beg; p0 < end; p0 += T) {
             if (ORDER == 1 && p0 != beg && ((p0 - beg) & (DIAG_SLICE - 1)) == 0) {
                 __syncthreads();
-                diag_flush<TL, ORDER, RHO_REP, RS>(acc, sG, scale, rho);
+                diag_flush<TL, ORDER, T, REP, RS>(acc, sG, scale, rho);
                 __syncthreads();
-                for (int e = tid; e < RHO_REP * RS; e += DIAG_T) acc[e] = RhoT(0);
+                for (int e = tid; e < REP * RS; e += T) acc[e] = RhoT(0);
                 __syncthreads();
             }
             const int p = p0 + tid;
             if (p >= end) continue;
-            const DiagSlot cur = nx;
-            if (p + DIAG_T < end) nx = diag_load<KIN>(sp, WP, p + DIAG_T);
+            const DiagSlot cur = AHEAD ? nx : diag_load<KIN>(sp, WP, p);
+            if (AHEAD && p + T < end) nx = diag_load<KIN>(sp, WP, p + T);
             const uint32_t c = cur.c;
             if (c == DEAD) continue;
             const double wp = WP ? (double)cur.w : sp.w_species;
@@ -1572,7 +1573,8 @@ __global__ __launch_bounds__(DIAG_T, 4) void k_diag_tiles(GridP g, TileInfo ti, 
             }
         }
         __syncthreads();
-        diag_flush<TL, ORDER, RHO_REP, RS>(acc, sG, scale, rho);
+        diag_flush<TL, ORDER, T, REP, RS>(acc, sG, scale, rho);
+        if constexpr (!KIN) return;  // a workgroup per tile
         __syncthreads();
     }
     if constexpr (KIN) {
@@ -2113,27 +2115,51 @@ void launch_kinetic_f32(const SpeciesP &sp, double *partial_slot, hipStream_t s)
 }
 
 namespace {
+// The charge alone: up to DIAG_REP_MIN particles per tile in workgroups of half
+// the size with two windows, eight of which share a CU (us per call, 128^3: 122 per
+// tile 57 | 62 with the wide ones, 244: 61 | 68, 488: 68 | 71, 977: 72 | 76; 64^3 with
+// 3906: 60 | 43; and 51, 53, 58, 65 without the load ahead).
+constexpr int DIAG_REP_MIN = 512;
 template <class TL, int ORDER>
-void diag_tiles(const GridP &g, const TileInfo &ti, double scale, const SpeciesP &sp, double *rho,
-                const FieldPtrs *F, double *part_m, double *part_p, uint32_t *fault,
-                hipStream_t s) {
-    // one partial slot per workgroup
-    const int nb = 8 * std::min((ti.ntiles + 7) / 8, PSTRIDE / 8);
+void diag_tiles(const GridP &g, const TileInfo &ti, long long count, double scale,
+                const SpeciesP &sp, double *rho, const FieldPtrs *F, double *part_m,
+                double *part_p, uint32_t *fault, hipStream_t s) {
+    constexpr int REP = ORDER == 1 ? 4 : 3;  // as many as leave two workgroups to a CU
+    const int nt8 = (ti.ntiles + 7) / 8;
     float r, r_lo;
     split_f32(sp.q * g.dt / (2.0 * sp.m), r, r_lo);
-    if (F)
-        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, true>), dim3(nb), dim3(DIAG_T), 0, s, g, ti, sp,
-                           scale, rho, *F, r, r_lo, part_m, part_p, fault);
+    if (F)  // one partial slot per workgroup
+        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, true, DIAG_T, REP, true>),
+                           dim3(8 * std::min(nt8, PSTRIDE / 8)), dim3(DIAG_T), 0, s, g, ti, sp, scale,
+                           rho, *F, r, r_lo, part_m, part_p, fault);
+    else if (count >= DIAG_REP_MIN * (long long)ti.ntiles)
+        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, false, DIAG_T, REP, true>), dim3(8 * nt8),
+                           dim3(DIAG_T), 0, s, g, ti, sp, scale, rho, FieldPtrs{}, r, r_lo, part_m,
+                           part_p, fault);
     else
-        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, false>), dim3(nb), dim3(DIAG_T), 0, s, g, ti, sp,
-                           scale, rho, FieldPtrs{}, r, r_lo, part_m, part_p, fault);
+        hipLaunchKernelGGL((k_diag_tiles<TL, ORDER, false, DIAG_T / 2, 2, false>), dim3(8 * nt8),
+                           dim3(DIAG_T / 2), 0, s, g, ti, sp, scale, rho, FieldPtrs{}, r, r_lo,
+                           part_m, part_p, fault);
 }
 }  // namespace
 
-bool launch_diag_tiles(const GridP &g, const TileInfo &ti, bool tiles_valid, double scale,
-                       const SpeciesP &sp, double *rho, float *const E[3], float *const Bbar[3],
-                       double *part_m, double *part_p, uint32_t *fault, hipStream_t s) {
+// Where tiles hold few particles their windows cost more than they save.  The
+// charge goes straight to global memory below 48 contributions per tile (256^3, 1.5
+// per tile: 66 us against 124 by tiles, 7.6: 187, 151; second order 147, 162 and 567,
+// 248).  The charge and the energies in one pass pay from 100 particles per tile
+// (128^3: 61 per tile 224 us in separate passes, 256 in one; 122: 256, 258; 244: 330,
+// 264; 256^3, 30 per tile: 961, 1294), at second order from 45 (30 per tile: 280, 299;
+// 61: 348, 303); and on grids that the chip takes in two rounds, where what counts
+// is the launches (32^3, 8 per tile: 112, 100).
+bool launch_diag_tiles(const GridP &g, const TileInfo &ti, bool tiles_valid, long long count,
+                       double scale, const SpeciesP &sp, double *rho, float *const E[3],
+                       float *const Bbar[3], double *part_m, double *part_p, uint32_t *fault,
+                       hipStream_t s) {
     if (!tiles_valid || sp.capacity <= 0) return false;
+    const int order = g.shape_order;
+    const long long few = (long long)ti.ntiles * (order == 2 ? 45 : 100);
+    if (E && count < few && ti.ntiles > 1024) return false;
+    if (!E && count * (order == 2 ? 27 : 8) < 48LL * ti.ntiles) return false;
     FieldPtrs F{};
     if (E)
         for (int a = 0; a < 3; ++a) {
@@ -2141,10 +2167,10 @@ bool launch_diag_tiles(const GridP &g, const TileInfo &ti, bool tiles_valid, dou
             F.Bb[a] = Bbar[a];
         }
     const FieldPtrs *f = E ? &F : nullptr;
-    if (ti.slab) diag_tiles<TileSlab, 1>(g, ti, scale, sp, rho, f, part_m, part_p, fault, s);
+    if (ti.slab) diag_tiles<TileSlab, 1>(g, ti, count, scale, sp, rho, f, part_m, part_p, fault, s);
     else if (g.shape_order == 2)
-        diag_tiles<TileCube2, 2>(g, ti, scale, sp, rho, f, part_m, part_p, fault, s);
-    else diag_tiles<TileCube, 1>(g, ti, scale, sp, rho, f, part_m, part_p, fault, s);
+        diag_tiles<TileCube2, 2>(g, ti, count, scale, sp, rho, f, part_m, part_p, fault, s);
+    else diag_tiles<TileCube, 1>(g, ti, count, scale, sp, rho, f, part_m, part_p, fault, s);
     return true;
 }
 
