@@ -445,7 +445,7 @@ void one_step(empic_sim *s, const DevSpecies *tbl = nullptr, int rd_mask = -1, i
 // single step is left to one_step.
 template <typename T>
 int vacuum_steps(empic_sim *s, int nsteps) {
-    if (s->nsp > 0 || s->window.enabled || !vacuum_fits(s->g)) return 0;
+    if (s->nsp > 0 || s->window.enabled || !vacuum_fits<T>(s->g)) return 0;
     const bool absorbing = s->g.bc[0] == EMPIC_BC_ABSORBING || s->g.bc[1] == EMPIC_BC_ABSORBING ||
                            s->g.bc[2] == EMPIC_BC_ABSORBING;
     T *E[3], *B[3], *J[3], *E2[3], *B2[3];

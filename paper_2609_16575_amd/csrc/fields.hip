@@ -250,9 +250,10 @@ __global__ __launch_bounds__(PT_THREADS) void k_ampere(
 // Bound by memory: 48 bytes per point and step, where the two point kernels
 // move 72 (the halos come from the XCD's L2, whose workgroups share a range of
 // z).  Out of place the arrays take twice the room in the memory-side cache,
-// which the point kernels live on: 91 x 46 x 3001, 224 -> 202 us per step, and not
-// by the ratio of the bytes; nontemporal accesses lose what is left of it (249).
-// The same expressions as k_faraday and k_ampere, so the same bits.
+// which the point kernels live on (vacuum_fits): 91 x 46 x 3001, 224 -> 202 us per
+// step, and not by the ratio of the bytes; nontemporal accesses lose what is left
+// of it (249).  The same expressions as k_faraday and k_ampere and the same bits,
+// so that a run does not depend on how its steps are grouped into calls.
 constexpr int VX = 32, VY = 16, VT = VX * VY;
 
 template <typename T>
@@ -766,14 +767,45 @@ void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], 
                        Jf ? Jf[2] : nullptr, jinv);
 }
 
-// Two million points and a patch's extent along y and z: below, the march along
-// z is latency (31 x 16 x 1001: 22 us per step against 18 for the two point
-// kernels; 1024 x 64 x 16: 20 against 17; 46 x 23 x 1501: 31 against 32; 128^3: 24
-// against 29; 61 x 31 x 2001: 47 against 60; 91 x 46 x 3001: 202 against 224;
-// 256^3: 248 against 317, in FP64 486 against 576), and a thin axis leaves
-// threads idle or doubles the planes worked.
+// Patches and chunks of planes of k_vacuum, and the fraction of their points that
+// lies on the grid
+struct VacGrid {
+    int nbx, nby, nbz, zc;
+    double used;
+};
+static VacGrid vacuum_grid(const GridP &g) {
+    VacGrid v;
+    v.nbx = (g.ext[0] + VX - 2) / (VX - 1);
+    v.nby = (g.ext[1] + VY - 2) / (VY - 1);
+    // 16 planes per workgroup where that leaves two workgroups per CU, else 8: 61 x
+    // 31 x 2001 (756 of 16) 47 us per step with 16 and 54 with 8, 46 x 23 x 1501
+    // (376 of 16) 41 and 31, 91 x 46 x 3001 (2256) 202 and 197; with 4 and with
+    // 32 slower than the better of these everywhere.
+    v.zc = (long long)v.nbx * v.nby * ((g.ext[2] + 15) / 16) >= 512 ? 16 : 8;
+    v.nbz = (g.ext[2] + v.zc - 1) / v.zc;
+    v.used = (double)g.V / ((double)v.nbx * (VX - 1) * v.nby * (VY - 1) * v.nbz * v.zc);
+    return v;
+}
+
+// What decides is the memory-side cache (256 MiB): the point kernels work in place
+// on E and B, k_vacuum on two sets of them.  One pass pays where both sets stay in
+// the cache and the grid is large enough for the march along z, and where not
+// even one does; between, it leaves the cache and they do not.  It also has to fill
+// its patches, the less so the further E and B exceed the cache.  Point kernels |
+// one pass, us per step, FP32: 1.0 M points 17 | 21, 2.1 M 30 | 27, 4.1 M 50 | 46, 5.2 M
+// 62 | 74, 8.0 M 91 | 110, 10.5 M 121 | 132, 11.5 M 182 | 164, 12.5 M 209 | 164, 17 M
+// 276 | 200; with 70 % of the patches used 4.1 M 50 | 58, 12.5 M 201 | 205, 17 M 266 | 252;
+// with 57 % 12.5 M 209 | 199, 17 M 273 | 246; 6 x 512 x 1024 (19 %) 41 | 111.  FP64: 2.1 M
+// 44 | 44, 4.0 M 78 | 118, 6.0 M 186 | 152, 12.5 M 368 | 303; with 70 % 6.0 M 184 | 188, 12.5 M
+// 348 | 326; with 57 % 8.0 M 232 | 240, 17 M 518 | 492.
+template <typename T>
 bool vacuum_fits(const GridP &g) {
-    return g.V >= (1ll << 21) && g.ext[1] >= VY - 1 && g.ext[2] >= 16;
+    if (g.ext[2] < 16) return false;
+    constexpr double CACHE = 256.0 * (1 << 20);
+    const double one = 6.0 * sizeof(T) * (double)g.V;  // bytes of E and B
+    const bool both_fit = sizeof(T) == 4 && g.V >= (1ll << 21) && 2.0 * one <= 0.75 * CACHE;
+    if (!both_fit && one <= CACHE) return false;
+    return vacuum_grid(g).used >= (one > 1.5 * CACHE ? 0.55 : 0.72);
 }
 
 // A step without particles of E, B into Eo, Bo (J zeroed when given).
@@ -790,16 +822,10 @@ void launch_vacuum(const GridP &g, T *const E[3], T *const B[3], T *const Eo[3],
     }
     F.planes = mur_planes;
     F.pstride = plane_stride;
-    const int nbx = (g.ext[0] + VX - 2) / (VX - 1), nby = (g.ext[1] + VY - 2) / (VY - 1);
-    // 16 planes per workgroup where that leaves two workgroups per CU, else 8: 61 x
-    // 31 x 2001 (756 of 16) 47 us per step with 16 and 54 with 8, 46 x 23 x 1501
-    // (376 of 16) 41 and 31, 91 x 46 x 3001 (2256) 202 and 197; with 4 and with
-    // 32 slower than the better of these everywhere.
-    const int zc = (long long)nbx * nby * ((g.ext[2] + 15) / 16) >= 512 ? 16 : 8;
-    const int nbz = (g.ext[2] + zc - 1) / zc;
-    const long long nb = (long long)nbx * nby * nbz;
-    hipLaunchKernelGGL(k_vacuum<T>, dim3((unsigned)((nb + 7) / 8 * 8)), dim3(VT), 0, s, g, F, nbx,
-                       nby, nbz, zc);
+    const VacGrid v = vacuum_grid(g);
+    const long long nb = (long long)v.nbx * v.nby * v.nbz;
+    hipLaunchKernelGGL(k_vacuum<T>, dim3((unsigned)((nb + 7) / 8 * 8)), dim3(VT), 0, s, g, F,
+                       v.nbx, v.nby, v.nbz, v.zc);
 }
 
 void launch_copy6(const float *const src[6], float *const dst[6], long long n, hipStream_t s) {
@@ -943,6 +969,7 @@ void launch_field_energy(const GridP &g, T *const E[3], T *const B[3], double *p
     template void launch_ampere<T>(const GridP &, T *const[3], T *const[3], T *const[3],       \
                                    JMode, bool, const long long *const[3], double,             \
                                    hipStream_t);                                               \
+    template bool vacuum_fits<T>(const GridP &);                                               \
     template void launch_vacuum<T>(const GridP &, T *const[3], T *const[3], T *const[3],       \
                                    T *const[3], T *const[3], T *, long long, hipStream_t);     \
     template void launch_mur_apply<T>(const GridP &, T *const[3], const T *, long long,        \

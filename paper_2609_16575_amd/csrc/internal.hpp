@@ -270,6 +270,7 @@ template <typename T>
 void launch_ampere(const GridP &g, T *const E[3], T *const B[3], T *const J[3], JMode mode,
                    bool write_J, const long long *const Jf[3], double jinv, hipStream_t s);
 // a whole step without particles, out of place, on grids where one pass pays
+template <typename T>
 bool vacuum_fits(const GridP &g);
 template <typename T>
 void launch_vacuum(const GridP &g, T *const E[3], T *const B[3], T *const Eo[3], T *const Bo[3],
