@@ -524,7 +524,7 @@ __device__ __forceinline__ T filter_point(T lo, T mid, T hi, bool comp) {
     return a * lo + b * mid + a * hi;
 }
 
-// One pass along axis AX (filters too wide for k_filter_tile)
+// One pass along axis AX (where filter_by_patches says no)
 template <typename T, int AX>
 __global__ __launch_bounds__(PT_THREADS) void k_filter_pass(
     GridP g, const T *__restrict__ s0, const T *__restrict__ s1, const T *__restrict__ s2,
@@ -859,6 +859,29 @@ void launch_mur_apply(const GridP &g, T *const E[3], const T *planes, long long 
 }
 
 namespace {
+// Filters of up to FTILE_M passes per axis can go through the patch kernel: both its
+// buffers fit the 64 KB of static LDS (M = 4 in FP32: 60 KB; M = 2 in FP64: 54 KB).
+// It does M passes on every window point, so it pays where all workgroups are
+// resident at once, and else where the windows, with their halos and what hangs
+// over the grid's edge, hold few times the grid's points.  Pass by pass | patches, us
+// per step, FP32: 1 pass, 128^3 (2.0 times) 119 | 107, 512 x 4 x 256 (4.0) 56 | 54, 512 x 2 x
+// 512 (8.0) 50 | 58; 2 passes, 128^3 (3.4) 151 | 142, 40 x 128 x 128 (5.4) 79 | 78, 512 x 4 x
+// 256 (6.8) 68 | 74, 2 x 512 x 512 (54) 73 | 254; 3, 64^3 (5.2, resident) 62 | 53, 128^3 185 |
+// 228; 4, 48^3 (7.5, resident) 77 | 71, 64^3 (not) 72 | 83, 128^3 218 | 412.  FP64: 1
+// pass, 512 x 6 x 256 (2.7) 89 | 89, 40 x 128 x 128 (3.2) 85 | 86, 512 x 4 x 256 (4.0) 76 | 82; 2, 32^3
+// (3.4, resident) 54 | 53, 128^3 191 | 244.
+template <typename T>
+bool filter_by_patches(const GridP &g, int M) {
+    constexpr int FTILE_M = sizeof(T) == 4 ? 4 : 2;
+    constexpr long long LDS = 160 * 1024, CUS = 256;
+    if (M > FTILE_M) return false;
+    const long long nt = (long long)((g.ext[0] + FTX - 1) / FTX) * ((g.ext[1] + FTY - 1) / FTY) *
+                         ((g.ext[2] + FTZ - 1) / FTZ);
+    const long long window = (FTX + 2 * M) * (FTY + 2 * M) * (long long)(FTZ + 2 * M);
+    if (3 * nt <= CUS * (LDS / (2 * window * (long long)sizeof(T)))) return true;
+    return (double)(nt * window) <= (sizeof(T) == 4 ? 5.0 : 2.7) * (double)g.V;
+}
+
 template <typename T, int M>
 void filter_tile(const GridP &g, const FilterPtr<T> &P, int passes, double jinv, hipStream_t s) {
     const int nt = ((g.ext[0] + FTX - 1) / FTX) * ((g.ext[1] + FTY - 1) / FTY) *
@@ -872,16 +895,12 @@ void filter_tile(const GridP &g, const FilterPtr<T> &P, int passes, double jinv,
 }
 }  // namespace
 
-// Up to FTILE_M passes per axis go through the patch kernel: both its buffers
-// fit the 64 KB of static LDS (M = 4 in FP32: 60 KB; M = 2 in FP64: 54 KB), and
-// the work on the halos, (1 + 2 M/32)(1 + 2 M/8)(1 + 2 M/4) times the patch,
-// stays below what 3 M launches cost.  Wider filters run pass by pass.
+// The whole filter by patches (filter_by_patches), or pass by pass
 template <typename T>
 void launch_filter(const GridP &g, T *const S[3], const long long *const Jf[3], double jinv,
                    T *const F[3], T *const tmp[3], int passes, int compensate, hipStream_t s) {
-    constexpr int FTILE_M = sizeof(T) == 4 ? 4 : 2;
     const int M = passes + (compensate ? 1 : 0);
-    if (M <= FTILE_M) {
+    if (filter_by_patches<T>(g, M)) {
         FilterPtr<T> P{};
         const bool inplace = !Jf && S[0] == F[0];
         for (int c = 0; c < 3; ++c) {
