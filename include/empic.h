@@ -225,7 +225,8 @@ empic_status empic_create_static(const empic_grid_desc *g, int32_t max_species,
 
 /* Bind the six field arrays and the current density, each ext0*ext1*ext2
  * elements of float (FP32_CELLREL) or double (FP64_PLAIN).  E = E^n,
- * B = B^{n-1/2}; J is written by every step (J^{n+1/2} of the last step). */
+ * B = B^{n-1/2}; a call of empic_step leaves in J the J^{n+1/2} of its last
+ * step (the steps before it need not store theirs). */
 empic_status empic_bind_fields(empic_sim *s, void *const E[3], void *const B[3],
                                void *const J[3]);
 

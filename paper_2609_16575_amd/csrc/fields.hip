@@ -10,12 +10,14 @@
 //
 // Bytes per cell (FP32): Faraday reads E, B (24) and writes B, Bbar (24) and
 // zeroes the int64 sums of J (24); Ampere reads those, E and B (48) and
-// writes E, J (24).  Without particles there is no Bbar and there are no
-// sums: 36 and 48.
-// Bound by HBM.  The vacuum waveguide on 91 x 46 x 3001 nodes: 0.645 ms per
-// step with one 64 x 4 workgroup per patch of rows (the second of two per
-// row 42 % full), the sums zeroed and read, and the Mur and PEC planes in
-// kernels of their own; 0.255 ms now, 4.2 TB/s (a large copy: 4.7).
+// writes E (12), and J (12) in the last step of a call.  Without particles there
+// is no Bbar and there are no sums: 36 and 36 (+12), or 48 in one pass where
+// k_vacuum takes the step (vacuum_fits).
+// Bound by HBM and the memory-side cache.  The vacuum waveguide on 91 x 46 x 3001
+// nodes: 0.645 ms per step with one 64 x 4 workgroup per patch of rows (the second
+// of two per row 42 % full), the sums zeroed and read, J written every step and the
+// Mur and PEC planes in kernels of their own; 0.224 with the two point kernels on
+// the flat index, 0.202 in one pass (3.0 TB/s; a large copy: 4.7).
 #include <cmath>
 #include <utility>
 

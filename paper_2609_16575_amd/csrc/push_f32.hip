@@ -19,7 +19,7 @@
 //      2.5), the relativistic Boris push (Sec. 2.4), the move and the ZigZag
 //      deposit (Sec. 2.5): 12 int64 LDS atomics per straight segment (24 for
 //      a particle crossing a cell face),
-//   4. adds the non-zero LDS current to global J with float atomics.
+//   4. adds the non-zero LDS current to the global int64 sums of J.
 // Particles that drifted more than MARGIN cells out of their tile since the
 // last sort are handled entirely through global memory (rare, counted).
 // Particles are read from one buffer set and written to another (the same
@@ -49,7 +49,7 @@ struct FusedArgs {
     unsigned cur_mask;      // bit s: buffer set species s is read from
     unsigned wr_mask;       // bit s: buffer set species s is written to (the same for a step in place)
     float dtd[3], dtd_lo[3];  // dt / d_a as FP32 pairs (split_f32)
-    double jscale, jinv;    // fixed-point scale of the current (LDS window and Jf) and its inverse
+    double jscale;          // fixed-point scale of the current (LDS window and Jf)
     uint32_t *fault;
     unsigned long long *fallback;  // cumulative count of out-of-window particles
     uint32_t *fb_mask;             // bit p of species s's words: slot p is out of its window
@@ -246,7 +246,6 @@ __device__ __forceinline__ void load_batch(const SpeciesP &S, int base, Batch<P>
 #pragma unroll
     for (int k = 0; k < P; ++k) b.w[k] = 1.f;
     if (S.per_particle_w) b.w = __builtin_nontemporal_load((const VF *)((const gfloat *)S.w + base));
-
 }
 
 // Mid-point and displacement of the second ZigZag segment of a move from
@@ -325,7 +324,8 @@ struct TileCtx {
 // segment.  A full queue makes the particle deposit its second segment at
 // once.
 //
-// On the benchmark plasma (528 us per launch) the kernel sits between three
+// On the benchmark plasma, freshly sorted (528 us per launch; 565 to 590 over the
+// steps between its adaptive sorts), the kernel sits between three
 // bounds: its 1.96 GB take 413 us at a copy's rate (4.7 TB/s; 403 us measured
 // without the gathers and the LDS adds), its VALU instructions about 400 us
 // and its LDS accesses about 300 us, overlapped by 16 waves per CU.  The
@@ -1099,9 +1099,10 @@ __device__ __forceinline__ int nth_bit(uint32_t w, int k) {
 // chain of gathers, so what counts is how many are in flight: with each lane
 // walking its own word's bits, the wakefield run's pass (particles half a
 // cell per step, whole words marked in a few tiles) had two waves per CU at
-// work: 210 us per step on average, 57 us now.  The counts and the tile list are cleared by the next step's
-// Faraday kernel (a ticket for the last workgroup, a returning atomic of every
-// workgroup on one word, cost more than the pass itself in most steps).
+// work: 210 us per step on average, 57 us now.  The counts and the tile list are
+// cleared by the next step's Faraday kernel (a ticket for the last workgroup, a
+// returning atomic of every workgroup on one word, cost more than the pass itself
+// in most steps).
 constexpr int FB_WPT = 160;  // words per item stride: the 129 of a 4096-particle tile
 template <int ORDER>
 __global__ __launch_bounds__(256) void k_push_fallback(FusedArgs A) {
@@ -2069,7 +2070,6 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
     A.cur_mask = cur_mask;
     A.wr_mask = wr_mask;
     A.jscale = jscale;
-    A.jinv = 1.0 / jscale;
     A.fault = fault;
     A.fallback = fallback;
     A.fb_mask = fb_mask;
@@ -2094,7 +2094,6 @@ void launch_push_fused(const GridP &g, const TileInfo &ti, float *const E[3],
         launch_fused<TileFold, 1>(A, nb, s, ev_start, ev_stop);
     else if (ti.slab)
         launch_fused<TileSlab, 1>(A, nb, s, ev_start, ev_stop);  // order 2 is refused on slab grids
-
     else if (g.shape_order == 2)
         launch_fused<TileCube2, 2>(A, nb, s, ev_start, ev_stop);
     else
