@@ -15,7 +15,7 @@ FP64 step on the same workload is reported beside it.  The dominant kernel is
 the fused FP32 particle kernel; its roofline entry uses the algorithmic bytes
 56 per particle (28 read + 28 written) + 36 per cell (E and centred B read,
 J written) per launch over its HIP-event-timed average duration.  It reaches
-about 43 % of the 8 TB/s peak, short of a 50 % target: the kernel is
+41 to 44 % of the 8 TB/s peak by run, short of a 50 % target: the kernel is
 co-limited by VALU issue (~394 instructions per particle) and its LDS
 atomics rather than by HBM (its traffic is within 7 % of the algorithmic
 bytes).  The "adjoint" entry times a 50-step forward + adjoint on a 128^3 anisotropic
