@@ -6,6 +6,7 @@
 // KEMPIC-3D) and converts kernel fault words and HIP errors into status codes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -130,7 +131,8 @@ struct SpeciesState {
     int cur = 0;
     int32_t *tile_off = nullptr;  // ntiles + 1
     int32_t *dcount = nullptr;    // device slot count
-    long long host_count = 0;
+    long long host_count = 0;     // particles loaded
+    long long slots = 0;          // slots that may be in use: loaded, injected, a loaded state's
     bool tiles_valid = false;     // particles grouped by the tile offsets of a previous sort
     double wmax = 0.0;            // largest |weight| (species w, or the loaded per-particle max)
     long long next_id = 0;        // id of the next injected particle
@@ -512,7 +514,10 @@ bool window_step(empic_sim *s) {
             nc[a] = W.cells;
             launch_inject(cur, lo, nc, S.inj_per, (float)S.inj_w, (int)S.next_id, reserve, s->fault,
                           s->stream);
-            S.next_id += (long long)nc[0] * S.inj_per[0] * nc[1] * S.inj_per[1] * nc[2] * S.inj_per[2];
+            const long long m =
+                (long long)nc[0] * S.inj_per[0] * nc[1] * S.inj_per[1] * nc[2] * S.inj_per[2];
+            S.next_id += m;
+            S.slots = std::min(S.capacity, S.slots + m);
         }
         S.tiles_valid = false;
     }
@@ -798,7 +803,7 @@ empic_status empic_add_species(empic_sim *s, const empic_species_desc *desc, int
     S.has_alt = buf1 != nullptr;
     if (buf1) S.buf[1] = *buf1;
     S.cur = 0;
-    S.host_count = 0;
+    S.host_count = S.slots = 0;
     launch_fill_i32(S.tile_off, s->ti.ntiles + 2, 0, s->stream);  // offsets and count
     const int id = s->nsp;
     s->nsp += 1;
@@ -831,7 +836,7 @@ empic_status empic_load_particles_f64(empic_sim *s, int32_t sp, int64_t count,
     } else {
         launch_load_f32(s->g, p, count, pos_xyz, u_xyz, w, ids, s->fault, s->stream);
     }
-    S.host_count = count;
+    S.host_count = S.slots = count;
     S.next_id = count;
     S.tiles_valid = false;
     s->need_sort = true;
@@ -1024,8 +1029,8 @@ static double rho_scale(const empic_sim *s, int i) {
 
 // Charge density of an FP32 species: by tiles where that pays, else directly
 static void rho_f32(empic_sim *s, int i, const SpeciesP &p, double *rho) {
-    if (!launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, s->sp[i].host_count, rho_scale(s, i),
-                           p, rho, nullptr, nullptr, nullptr, nullptr, s->fault, s->stream))
+    if (!launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, s->sp[i].slots, rho_scale(s, i), p, rho,
+                            nullptr, nullptr, nullptr, nullptr, s->fault, s->stream))
         launch_rho_f32(s->g, p, rho, s->stream);
 }
 
@@ -1075,7 +1080,7 @@ empic_status empic_diagnostics(empic_sim *s, empic_diag *out) {
         for (int i = 0; i < s->nsp; ++i) {
             const SpeciesP p = species_params(s, i, s->sp[i].cur);
             double *km = s->partials + (Q_KM + i) * PSTRIDE, *kp = s->partials + (Q_KP + i) * PSTRIDE;
-            if (launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, s->sp[i].host_count,
+            if (launch_diag_tiles(s->g, s->ti, s->sp[i].tiles_valid, s->sp[i].slots,
                                   rho_scale(s, i), p, s->rho_cur, E, Bb, km, kp, s->fault, s->stream))
                 continue;
             rho_f32(s, i, p, s->rho_cur);
@@ -1241,8 +1246,11 @@ empic_status empic_load_state(empic_sim *s, const empic_state *src) {
     if (fp64(s)) return fail(s, EMPIC_E_UNSUPPORTED, "states are for the FP32 path");
     const empic_status st = copy_state(s, src, false);
     if (st != EMPIC_OK) return st;
-    // a saved state is grouped by its own tile offsets
-    for (int i = 0; i < s->nsp; ++i) s->sp[i].tiles_valid = true;
+    // a saved state is grouped by its own tile offsets; its count stays on the device
+    for (int i = 0; i < s->nsp; ++i) {
+        s->sp[i].tiles_valid = true;
+        s->sp[i].slots = s->sp[i].capacity;
+    }
     s->need_sort = false;
     s->rho_prev_step = -1;
     return EMPIC_OK;
