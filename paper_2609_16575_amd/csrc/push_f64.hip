@@ -381,7 +381,8 @@ __global__ __launch_bounds__(256, 2) void k_push_f64_tiles(GridP g, F64Args A, T
         part = q - t.more[tile] + 1;
     }
     if (tile >= t.ntiles) return;
-    const int beg = t.offs[tile] + part * t.slice, end = min(t.offs[tile + 1], beg + t.slice);
+    // (beg + slice, and the loop's last q, can pass 2^31 - 1)
+    const int beg = t.offs[tile] + part * t.slice, end = beg + min(t.offs[tile + 1] - beg, t.slice);
     if (beg >= end) return;
     const int tx = tile % t.nt[0], tyz = tile / t.nt[0];
     const int org[3] = {tx * T64X, (tyz % t.nt[1]) * T64Y, (tyz / t.nt[1]) * T64Z};
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(256, 2) void k_push_f64_tiles(GridP g, F64Args A, T
     double *U[3] = {(double *)sp.u[0], (double *)sp.u[1], (double *)sp.u[2]};
     const double *W = sp.per_particle_w ? (const double *)sp.w : nullptr;
     uint32_t bits = 0;
-    for (int q = beg + tid; q < end; q += 256) {
+    for (unsigned q = (unsigned)(beg + tid); q < (unsigned)end; q += 256u) {
         const int p = t.perm[q];
         double pos[3], un[3];
 #pragma unroll
