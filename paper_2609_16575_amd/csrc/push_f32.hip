@@ -1368,6 +1368,8 @@ __global__ void k_rho_f32(GridP g, SpeciesP sp, double *rho) {
 // alone takes smaller workgroups there, see diag_tiles.
 constexpr int DIAG_T = 512;
 constexpr int DIAG_SLICE = 1 << 14;
+
+// An entry of a charge window
 template <int ORDER>
 struct RhoAcc {
     typedef unsigned long long T;
@@ -1384,6 +1386,7 @@ struct RhoAcc<2> {
     static __device__ __forceinline__ T of(double v, double) { return v; }
     static __device__ __forceinline__ double value(T v, double) { return v; }
 };
+
 struct DiagSlot {
     uint32_t c;
     float o[3], u[3], w;
@@ -1400,6 +1403,7 @@ __device__ __forceinline__ DiagSlot diag_load(const SpeciesP &sp, const float *W
     }
     return d;
 }
+
 // The replicas of a charge window summed and added to the global array
 template <class TL, int ORDER, int T, int REP, int RS>
 __device__ __forceinline__ void diag_flush(const typename RhoAcc<ORDER>::T *acc,
@@ -1419,11 +1423,12 @@ __device__ __forceinline__ void diag_flush(const typename RhoAcc<ORDER>::T *acc,
         atomicAdd(rho + gx + gy + gz, RhoAcc<ORDER>::value(v, inv));
     }
 }
+
 template <class TL, int ORDER, bool KIN, int T, int REP, bool AHEAD>
 __global__ __launch_bounds__(T, 4) void k_diag_tiles(GridP g, TileInfo ti, SpeciesP sp,
-                                                       double scale, double *rho, FieldPtrs F,
-                                                       float r, float r_lo, double *part_m,
-                                                       double *part_p, uint32_t *fault) {
+                                                     double scale, double *rho, FieldPtrs F,
+                                                     float r, float r_lo, double *part_m,
+                                                     double *part_p, uint32_t *fault) {
     constexpr int TX = TL::TX, TY = TL::TY, TZ = TL::TZ;
     constexpr int FWX = TL::FWX, FWY = TL::FWY, FWZ = TL::FWZ, FW3 = TL::FW3, ROWS = TL::ROWS;
     constexpr int LHI_X = TL::LHI_X, LHI_Y = TL::LHI_Y, LHI_Z = TL::LHI_Z;
@@ -2115,9 +2120,9 @@ void launch_kinetic_f32(const SpeciesP &sp, double *partial_slot, hipStream_t s)
 
 namespace {
 // The charge alone: up to DIAG_REP_MIN particles per tile in workgroups of half
-// the size with two windows, eight of which share a CU (us per call, 128^3: 122 per
-// tile 57 | 62 with the wide ones, 244: 61 | 68, 488: 68 | 71, 977: 72 | 76; 64^3 with
-// 3906: 60 | 43; and 51, 53, 58, 65 without the load ahead).
+// the size with two windows and no load ahead, eight of which share a CU (us per
+// call, 128^3: 122 per tile 53 | 62 with the wide ones, 244: 58 | 68, 488: 65 | 71, 977:
+// 76 | 76; 64^3 with 3906: 61 | 43; with the load ahead 57, 61, 68, 72, 60).
 constexpr int DIAG_REP_MIN = 512;
 template <class TL, int ORDER>
 void diag_tiles(const GridP &g, const TileInfo &ti, long long count, double scale,
